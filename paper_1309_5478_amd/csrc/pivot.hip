@@ -1,8 +1,8 @@
 // The learned pivot: a small network predicting, from statistics of a strided
 // row sample, where the k-th smallest entry of a row lies, so that the first
 // partition pass of the quick multi-select keeps just over k keys.  Kernels for
-// features, inference, and training (forward/backward per sample, fixed-order
-// weight-gradient sums, Adam on FP32 master weights with a BF16 copy), and the
+// features, inference, and training (forward, backward and fixed-order
+// weight-gradient sums per tile of samples, Adam on FP32 master weights with a BF16 copy), and the
 // C ABI around them (weights in/out, file save/load).
 #include <cmath>
 #include <cstdio>
@@ -69,84 +69,183 @@ __global__ __launch_bounds__(256) void net_predict_kernel(const float *__restric
     if (lane_id() == 0) out[r] = y;
 }
 
-// Training, pass 1: one thread per sample, forward and backward through the
-// network with the BF16-rounded weights `wr` (stored as FP32), FP32 arithmetic
-// in a fixed order.  Writes the activations H1, H2 (B x 64), the back-propagated
-// signals D1, D2 (B x 64), dL/dy_hat and the per-sample pinball loss.
-__global__ __launch_bounds__(256) void net_fwd_bwd_kernel(const float *__restrict__ X, const float *__restrict__ y,
-                                                          int64_t B, const float *__restrict__ wr, float q,
-                                                          float *__restrict__ H1, float *__restrict__ H2,
-                                                          float *__restrict__ D1, float *__restrict__ D2,
-                                                          float *__restrict__ dy, float *__restrict__ lossv) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    float x[kNetIn];
+// Training: forward, backward and the weight gradient of a tile of kGradTile
+// samples at a time per workgroup, with the BF16-rounded weights `wr` (stored as
+// FP32), FP32 arithmetic in a fixed order.  The weights and a tile's activations
+// live in LDS; each thread holds its share of the 4801 weight gradients in
+// registers over the workgroup's tiles (blockIdx.x, + gridDim.x, ...), and the
+// workgroup leaves one row of partial sums (the gradients, then the loss).
+// 115 MFLOP of a batch of 4096 are nothing to the chip: what bounds the pass is
+// the latency of its dependent sums, so the batch is cut into as many
+// workgroups as there are CUs and no sum runs over more than a tile's samples
+// or 64 units.  (One thread per sample, then one per parameter walking the whole
+// batch, with the activations in global memory: 1337 us a call at 4096 samples;
+// this form: 17 us.)
+constexpr int kGradTile = 16;
+constexpr int kGradMaxGrid = 256;
+constexpr int kGradRow = (kNetParams + 1 + 31) / 32 * 32;  // floats per partial row: gradients, loss, padding
+constexpr int kGradLd = kNetHidden + 4;  // LDS row stride: 16-byte aligned, 16 consecutive rows on distinct banks
+
+__global__ __launch_bounds__(256) void net_grad_tile_kernel(const float *__restrict__ X, const float *__restrict__ y,
+                                                            int64_t B, const float *__restrict__ wr, float q,
+                                                            float *__restrict__ part) {
+    __shared__ __align__(16) float sW2[kNetHidden][kGradLd], sW2T[kNetHidden][kGradLd];
+    __shared__ __align__(16) float sW1[kNetHidden][kNetIn + 4];
+    __shared__ __align__(16) float sx[kGradTile][kNetIn];
+    __shared__ __align__(16) float h1[kGradTile][kGradLd], h2[kGradTile][kGradLd];
+    __shared__ __align__(16) float d1[kGradTile][kGradLd], d2[kGradTile][kGradLd];
+    __shared__ float sdy[kGradTile], slv[kGradTile];
+    const uint32_t tid = threadIdx.x, u = tid % kNetHidden, g = tid / kNetHidden;  // unit, group of samples
+    constexpr uint32_t SPT = kGradTile / 4;                                       // samples per thread
+    for (uint32_t p = tid; p < (uint32_t)(kNetHidden * kNetHidden); p += 256) {
+        const float w = wr[kOffW2 + p];
+        sW2[p / kNetHidden][p % kNetHidden] = w;
+        sW2T[p % kNetHidden][p / kNetHidden] = w;
+    }
+    for (uint32_t p = tid; p < (uint32_t)(kNetHidden * kNetIn); p += 256) sW1[p / kNetIn][p % kNetIn] = wr[kOffW1 + p];
+    const float b1 = wr[kOffB1 + u], b2 = wr[kOffB2 + u], w3 = wr[kOffW3 + u], b3 = wr[kOffB3];
+    float gW2[16], gW1[2] = {0.f, 0.f}, gv = 0.f;
 #pragma unroll
-    for (int i = 0; i < kNetIn; ++i) x[i] = X[b * kNetIn + i];
-    float *h1 = H1 + b * kNetHidden, *h2 = H2 + b * kNetHidden;
-    float *d1 = D1 + b * kNetHidden, *d2 = D2 + b * kNetHidden;
-    for (int j = 0; j < kNetHidden; ++j) {
-        float z = wr[kOffB1 + j];
+    for (int t = 0; t < 16; ++t) gW2[t] = 0.f;
+    const int64_t tiles = (B + kGradTile - 1) / kGradTile;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t s0 = tile * kGradTile;
+        __syncthreads();  // weights stored; every thread is done with the previous tile
+        if (tid < kGradTile * kNetIn) {
+            const int64_t e = s0 * kNetIn + tid;
+            sx[tid / kNetIn][tid % kNetIn] = e < B * kNetIn ? X[e] : 0.f;
+        }
+        __syncthreads();
+        // unit u of SPT samples; a sample beyond the batch has zero activations
 #pragma unroll
-        for (int i = 0; i < kNetIn; ++i) z = fmaf(wr[kOffW1 + j * kNetIn + i], x[i], z);
-        h1[j] = z > 0.f ? z : 0.f;
+        for (uint32_t t = 0; t < SPT; ++t) {
+            const uint32_t s = g * SPT + t;
+            float z = b1;
+#pragma unroll
+            for (int i = 0; i < kNetIn; ++i) z = fmaf(sW1[u][i], sx[s][i], z);
+            h1[s][u] = z > 0.f && s0 + s < B ? z : 0.f;
+        }
+        __syncthreads();
+        {
+            float z[SPT];
+#pragma unroll
+            for (uint32_t t = 0; t < SPT; ++t) z[t] = b2;
+#pragma unroll 4
+            for (int i = 0; i < kNetHidden; i += 4) {
+                const f32x4 w = *reinterpret_cast<const f32x4 *>(&sW2[u][i]);
+#pragma unroll
+                for (uint32_t t = 0; t < SPT; ++t) {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(&h1[g * SPT + t][i]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[t] = fmaf(w[e], a[e], z[t]);
+                }
+            }
+#pragma unroll
+            for (uint32_t t = 0; t < SPT; ++t)
+                h2[g * SPT + t][u] = z[t] > 0.f && s0 + g * SPT + t < B ? z[t] : 0.f;
+        }
+        __syncthreads();
+        // the output sum in unit order, one thread per sample: the sign of
+        // y - y_hat decides the gradient
+        if (tid < (uint32_t)kGradTile) {
+            float dy = 0.f, lv = 0.f;
+            if (s0 + tid < B) {
+                float yh = 0.f;
+                for (int j = 0; j < kNetHidden; ++j) yh = fmaf(wr[kOffW3 + j], h2[tid][j], yh);
+                yh += b3;
+                const float r = y[s0 + tid] - yh;
+                lv = r >= 0.f ? q * r : (q - 1.0f) * r;
+                dy = (r > 0.f ? -q : (r < 0.f ? 1.0f - q : 0.f)) / (float)B;
+            }
+            sdy[tid] = dy;
+            slv[tid] = lv;
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t t = 0; t < SPT; ++t) {
+            const uint32_t s = g * SPT + t;
+            d2[s][u] = h2[s][u] > 0.f ? sdy[s] * w3 : 0.f;
+        }
+        __syncthreads();
+        {
+            float z[SPT];
+#pragma unroll
+            for (uint32_t t = 0; t < SPT; ++t) z[t] = 0.f;
+#pragma unroll 4
+            for (int j = 0; j < kNetHidden; j += 4) {
+                const f32x4 w = *reinterpret_cast<const f32x4 *>(&sW2T[u][j]);
+#pragma unroll
+                for (uint32_t t = 0; t < SPT; ++t) {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(&d2[g * SPT + t][j]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[t] = fmaf(a[e], w[e], z[t]);
+                }
+            }
+#pragma unroll
+            for (uint32_t t = 0; t < SPT; ++t) d1[g * SPT + t][u] = h1[g * SPT + t][u] > 0.f ? z[t] : 0.f;
+        }
+        __syncthreads();
+        // weight gradients: W2 entries (j = 16 g .. + 15, i = u), W1 entries
+        // tid and tid + 256, and one bias / output weight / loss sum per thread
+#pragma unroll 4
+        for (int s = 0; s < kGradTile; ++s) {
+            const float a = h1[s][u];
+#pragma unroll
+            for (int t = 0; t < 16; t += 4) {
+                const f32x4 d = *reinterpret_cast<const f32x4 *>(&d2[s][16 * g + t]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) gW2[t + e] = fmaf(d[e], a, gW2[t + e]);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const uint32_t e = tid + 256 * t;
+                gW1[t] = fmaf(d1[s][e / kNetIn], sx[s][e % kNetIn], gW1[t]);
+            }
+            if (g == 0) gv += d1[s][u];
+            else if (g == 1) gv += d2[s][u];
+            else if (g == 2) gv = fmaf(sdy[s], h2[s][u], gv);
+            else if (u == 0) gv += sdy[s];
+            else if (u == 1) gv += slv[s];
+        }
     }
-    float yh = 0.f;
-    for (int j = 0; j < kNetHidden; ++j) {
-        float z = wr[kOffB2 + j];
-        for (int i = 0; i < kNetHidden; ++i) z = fmaf(wr[kOffW2 + j * kNetHidden + i], h1[i], z);
-        const float hj = z > 0.f ? z : 0.f;
-        h2[j] = hj;
-        yh = fmaf(wr[kOffW3 + j], hj, yh);
-    }
-    yh += wr[kOffB3];
-    const float u = y[b] - yh;
-    lossv[b] = u >= 0.f ? q * u : (q - 1.0f) * u;
-    const float g = (u > 0.f ? -q : (u < 0.f ? 1.0f - q : 0.f)) / (float)B;
-    dy[b] = g;
-    for (int j = 0; j < kNetHidden; ++j) d2[j] = h2[j] > 0.f ? g * wr[kOffW3 + j] : 0.f;
-    for (int i = 0; i < kNetHidden; ++i) {
-        float s = 0.f;
-        for (int j = 0; j < kNetHidden; ++j) s = fmaf(d2[j], wr[kOffW2 + j * kNetHidden + i], s);
-        d1[i] = h1[i] > 0.f ? s : 0.f;
-    }
+    float *o = part + (size_t)blockIdx.x * kGradRow;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) o[kOffW2 + (16 * g + t) * kNetHidden + u] = gW2[t];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) o[kOffW1 + tid + 256 * t] = gW1[t];
+    if (g == 0) o[kOffB1 + u] = gv;
+    else if (g == 1) o[kOffB2 + u] = gv;
+    else if (g == 2) o[kOffW3 + u] = gv;
+    else if (u == 0) o[kOffB3] = gv;
+    else if (u == 1) o[kNetParams] = gv;
 }
 
-// Training, pass 2: one thread per parameter, sum over the batch in sample
-// order (deterministic).  Thread kNetParams writes the mean loss.
-__global__ __launch_bounds__(256) void net_wgrad_kernel(const float *__restrict__ X, const float *__restrict__ H1,
-                                                        const float *__restrict__ H2, const float *__restrict__ D1,
-                                                        const float *__restrict__ D2, const float *__restrict__ dy,
-                                                        const float *__restrict__ lossv, int64_t B,
-                                                        float *__restrict__ grad, float *__restrict__ loss) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kNetParams) return;
+// Sums the partial rows, in a fixed order: 32 columns per workgroup, eight
+// threads per column over every eighth row, then their sums in order.  Column
+// kNetParams is the loss (its mean is written).
+__global__ __launch_bounds__(256) void net_grad_sum_kernel(const float *__restrict__ part, int rows, int64_t B,
+                                                           float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ float sm[8][32];
+    const uint32_t c = threadIdx.x % 32, r0 = threadIdx.x / 32, p = blockIdx.x * 32 + c;
     float s = 0.f;
-    if (p == kNetParams) {
-        for (int64_t b = 0; b < B; ++b) s += lossv[b];
-        if (loss) *loss = s / (float)B;
-        return;
+    if (p <= (uint32_t)kNetParams) {
+#pragma unroll 8
+        for (int r = (int)r0; r < rows; r += 8) s += part[(size_t)r * kGradRow + p];
     }
-    if (p < kOffB1) {
-        const int j = p / kNetIn, i = p % kNetIn;
-        for (int64_t b = 0; b < B; ++b) s = fmaf(D1[b * kNetHidden + j], X[b * kNetIn + i], s);
-    } else if (p < kOffW2) {
-        const int j = p - kOffB1;
-        for (int64_t b = 0; b < B; ++b) s += D1[b * kNetHidden + j];
-    } else if (p < kOffB2) {
-        const int j = (p - kOffW2) / kNetHidden, i = (p - kOffW2) % kNetHidden;
-        for (int64_t b = 0; b < B; ++b) s = fmaf(D2[b * kNetHidden + j], H1[b * kNetHidden + i], s);
-    } else if (p < kOffW3) {
-        const int j = p - kOffB2;
-        for (int64_t b = 0; b < B; ++b) s += D2[b * kNetHidden + j];
-    } else if (p < kOffB3) {
-        const int j = p - kOffW3;
-        for (int64_t b = 0; b < B; ++b) s = fmaf(dy[b], H2[b * kNetHidden + j], s);
-    } else {
-        for (int64_t b = 0; b < B; ++b) s += dy[b];
-    }
-    grad[p] = s;
+    sm[r0][c] = s;
+    __syncthreads();
+    if (r0 != 0 || p > (uint32_t)kNetParams) return;
+    for (int t = 1; t < 8; ++t) s += sm[t][c];
+    if (p < (uint32_t)kNetParams) grad[p] = s;
+    else if (loss) *loss = s / (float)B;
 }
+
+static int grad_grid(int64_t B) {
+    const int64_t tiles = (B + kGradTile - 1) / kGradTile;
+    return tiles < kGradMaxGrid ? (int)tiles : kGradMaxGrid;
+}
+// Workspace of one gradient pass: a partial row per workgroup.
+static size_t grad_ws_bytes(int64_t B) { return (size_t)grad_grid(B) * kGradRow * sizeof(float) + 1024; }
 
 // Adam on the FP32 master weights, then the BF16 copy (and its FP32 image).
 __global__ __launch_bounds__(256) void net_adam_kernel(float *__restrict__ theta, float *__restrict__ m,
@@ -426,14 +525,14 @@ static knn_status_t grad_common(knn_handle_t h, const char *fn, const float *fea
     if (!h->has_net) return hfail(h, KNN_ERROR_INVALID_VALUE, std::string(fn) + ": no pivot network loaded");
     hipSetDevice(h->device);
     void *ws = nullptr;
-    const size_t per = (size_t)B * kNetHidden;
-    knn_status_t st = ensure_ws(h, (4 * per + 2 * (size_t)B) * sizeof(float) + 1024, stream, &ws);
+    knn_status_t st = ensure_ws(h, grad_ws_bytes(B), stream, &ws);
     if (st != KNN_SUCCESS) return st;
-    float *H1 = static_cast<float *>(ws), *H2 = H1 + per, *D1 = H2 + per, *D2 = D1 + per, *dy = D2 + per, *lv = dy + B;
-    hipLaunchKernelGGL(net_fwd_bwd_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, feats, targets, B,
-                       h->net_theta_r, q, H1, H2, D1, D2, dy, lv);
-    hipLaunchKernelGGL(net_wgrad_kernel, dim3((kNetParams + 1 + 255) / 256), dim3(256), 0, stream, feats, H1, H2, D1,
-                       D2, dy, lv, B, grad, loss);
+    float *part = static_cast<float *>(ws);
+    const int grid = grad_grid(B);
+    hipLaunchKernelGGL(net_grad_tile_kernel, dim3((unsigned)grid), dim3(256), 0, stream, feats, targets, B,
+                       h->net_theta_r, q, part);
+    hipLaunchKernelGGL(net_grad_sum_kernel, dim3((kNetParams + 1 + 31) / 32), dim3(256), 0, stream, part, grid, B, grad,
+                       loss);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hfail(h, KNN_ERROR_DEVICE, std::string(fn) + ": " + hipGetErrorString(e));
     return KNN_SUCCESS;
@@ -585,8 +684,7 @@ knn_status_t knn_pivot_train(knn_handle_t h, const char *out_path, uint64_t seed
     const int64_t n = h->ex_n, B = n < kTrainBatch ? n : kTrainBatch;
     // workspace: the gradient pass's region first (grad_common uses it from the
     // start), then the batch
-    const size_t per = (size_t)B * kNetHidden;
-    const size_t gbytes = ((4 * per + 2 * (size_t)B) * sizeof(float) + 1024 + 255) & ~size_t(255);
+    const size_t gbytes = (grad_ws_bytes(B) + 255) & ~size_t(255);
     void *ws = nullptr;
     st = ensure_ws(h, gbytes + (size_t)B * (kNetIn + 1) * sizeof(float) + 512, s, &ws);
     if (st != KNN_SUCCESS) return st;
