@@ -145,6 +145,113 @@ __global__ __launch_bounds__(256) void sqnorm_kernel(const float *__restrict__ X
     }
 }
 
+// ---- FP32 operands as two FP16 halves ----------------------------------------
+// The point scaled by 2^e, its largest finite magnitude into [2^14, 2^15) (e in
+// [-113, 100]; 0 for a zero point), each element as h = FP16(x 2^e) and l =
+// FP16(x 2^e - h), both to nearest even; the subtraction is exact.  A
+// non-finite element keeps its infinity or NaN in h with l = 0.  The squared
+// norms come from the same read, in sqnorm_kernel's order.  Memory-bound: 4 d
+// bytes read (the second pass over a row finds it in L1) and 4 d written per
+// point, against the d^2-fold work of the product it feeds.
+template <int G, bool VEC>
+__global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict__ X, int64_t n, int d,
+                                                         unsigned char *__restrict__ out, int64_t ldo,
+                                                         float *__restrict__ scale_out, float *__restrict__ norm,
+                                                         unsigned int *__restrict__ max_bits) {
+    constexpr int PPW = kWave / G;
+    __shared__ float wmax[256 / kWave];
+    const uint32_t lane = lane_id(), sub = lane % G, grp = lane / G, wave = threadIdx.x / kWave;
+    const int64_t stride = (int64_t)gridDim.x * (256 / kWave) * PPW;
+    const int dp = (d + 31) / 32 * 32;
+    float mx = 0.f;
+    for (int64_t base = ((int64_t)blockIdx.x * (256 / kWave) + wave) * PPW; base < n; base += stride) {
+        const int64_t i = base + grp;
+        const bool in = i < n;
+        const float *x = X + (in ? i : n - 1) * d;
+        float s = 0.f, am = 0.f;
+        auto see = [&](float v) {
+            s = fmaf(v, v, s);
+            const float a = fabsf(v);
+            if (a <= 3.4028235e38f) am = fmaxf(am, a);  // finite magnitudes only
+        };
+        if (VEC) {
+            for (int t = (int)sub * 4; t < d; t += G * 4) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(x + t);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) see(v[c]);
+            }
+        } else {
+            for (int t = (int)sub; t < d; t += G) see(x[t]);
+        }
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) {
+            s += __shfl_xor(s, off);
+            am = fmaxf(am, __shfl_xor(am, off));
+        }
+        int e = 0;
+        if (am > 0.f) {
+            int E;
+            (void)frexpf(am, &E);  // am = f 2^E, f in [0.5, 1)
+            e = 15 - E;
+            e = e < -113 ? -113 : (e > 100 ? 100 : e);
+        }
+        const float up = ldexpf(1.0f, e);
+        if (in && sub == 0) {
+            scale_out[i] = ldexpf(1.0f, -e);
+            if (norm) norm[i] = s;
+        }
+        if (in) mx = fmaxf(mx, s);
+        unsigned char *o = out + (in ? i : n - 1) * ldo;
+        auto halves = [&](float v, _Float16 &hi, _Float16 &lo) {
+            const float y = v * up;
+            hi = (_Float16)y;
+            const float r = y - (float)hi;
+            lo = r == r ? (_Float16)r : (_Float16)0.f;  // (inf - inf and NaN: no low half)
+        };
+        typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+        if (VEC) {
+            for (int t = (int)sub * 4; t < dp; t += G * 4) {
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                if (t < d) v = *reinterpret_cast<const f32x4 *>(x + t);
+                f16x4 hi, lo;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    _Float16 a, b;
+                    halves(v[c], a, b);
+                    hi[c] = a;
+                    lo[c] = b;
+                }
+                unsigned char *p = o + (t / 32) * 128 + (t % 32) * 2;
+                if (in) {
+                    *reinterpret_cast<f16x4 *>(p) = hi;
+                    *reinterpret_cast<f16x4 *>(p + 64) = lo;
+                }
+            }
+        } else {
+            for (int t = (int)sub; t < dp; t += G) {
+                _Float16 a, b;
+                halves(t < d ? x[t] : 0.f, a, b);
+                unsigned char *p = o + (t / 32) * 128 + (t % 32) * 2;
+                if (in) {
+                    *reinterpret_cast<_Float16 *>(p) = a;
+                    *reinterpret_cast<_Float16 *>(p + 64) = b;
+                }
+            }
+        }
+    }
+    if (max_bits) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        if (lane == 0) wmax[wave] = mx;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float m = wmax[0];
+            for (int w = 1; w < 256 / kWave; ++w) m = fmaxf(m, wmax[w]);
+            atomicMax(max_bits, __float_as_uint(m));
+        }
+    }
+}
+
 // Lanes per point or candidate for a row length d: the power of two covering
 // its 16-byte chunks (or its elements), at most a wave.
 static int lanes_for(int d, bool vec) {
@@ -493,6 +600,36 @@ hipError_t launch_sqnorm(const float *X, int64_t n, int d, float *out, unsigned 
         case 16: launch_sqnorm_g<16>(X, n, d, out, max_bits, vec, stream); break;
         case 32: launch_sqnorm_g<32>(X, n, d, out, max_bits, vec, stream); break;
         default: launch_sqnorm_g<64>(X, n, d, out, max_bits, vec, stream); break;
+    }
+    return hipGetLastError();
+}
+
+template <int G>
+static void launch_split_g(const float *X, int64_t n, int d, void *out, float *sc, float *norm, unsigned int *max_bits,
+                           bool vec, hipStream_t stream) {
+    constexpr int PPW = kWave / G;
+    int64_t blocks = (n + 4 * PPW - 1) / (4 * PPW);
+    if (blocks > 8192) blocks = 8192;
+    unsigned char *o = static_cast<unsigned char *>(out);
+    const int64_t ldo = split_row_bytes(d);
+    if (vec)
+        hipLaunchKernelGGL((split_rows_kernel<G, true>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, o, ldo,
+                           sc, norm, max_bits);
+    else
+        hipLaunchKernelGGL((split_rows_kernel<G, false>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, o, ldo,
+                           sc, norm, max_bits);
+}
+
+hipError_t launch_split(const float *X, int64_t n, int d, void *out, float *scale_out, float *norm,
+                        unsigned int *max_bits, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    const bool vec = d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
+    // (the lane grouping of launch_sqnorm, so that the norms are the same bits)
+    switch (lanes_for(d, vec)) {
+        case 16: launch_split_g<16>(X, n, d, out, scale_out, norm, max_bits, vec, stream); break;
+        case 32: launch_split_g<32>(X, n, d, out, scale_out, norm, max_bits, vec, stream); break;
+        case 64: launch_split_g<64>(X, n, d, out, scale_out, norm, max_bits, vec, stream); break;
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

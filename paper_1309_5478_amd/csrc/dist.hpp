@@ -6,12 +6,17 @@
 namespace knn {
 
 enum : int { kEpiDense = 0, kEpiFilter = 1 };
-enum : int { kPrecF32 = 0, kPrecBF16 = 1, kPrecFP8 = 2 };
+// (kPrecSplit: FP32 operands as two FP16 halves, see gemm_pipe.hip; a form of the
+// operands inside the library, not a caller's precision)
+enum : int { kPrecF32 = 0, kPrecBF16 = 1, kPrecFP8 = 2, kPrecSplit = 3 };
 enum : int { kTileSmall = 0, kTileWide = 1, kTileBig = 2, kTileSmall1 = 3 };
 
 // Quantised operands (BF16 / FP8): rows padded with zeros to a multiple of
 // kQuantPad elements, so every 128-byte k-chunk load is in bounds.
 constexpr int kQuantPad = 128;
+// Split operands: rows of 128-byte chunks, each the high halves of 32 elements
+// and then their low halves, zero-padded to a whole chunk.
+inline int64_t split_row_bytes(int d) { return ((int64_t)d + 31) / 32 * 128; }
 
 struct DistArgs {
     const float *Q;        // m x d queries
@@ -34,9 +39,9 @@ struct DistArgs {
     uint32_t *cnt;
     uint64_t *cand;
     int cap;
-    // operand precision; for BF16 / FP8 the product reads Qq / Cq (row stride
-    // ldq bytes) and, for FP8, undoes the per-row power-of-two scales
-    // qscale_i * cscale_j in the epilogue
+    // operand precision; for BF16 / FP8 / split operands the product reads Qq / Cq
+    // (row stride ldq bytes) and, for FP8 and split ones, undoes the per-row
+    // power-of-two scales qscale_i * cscale_j in the epilogue
     int prec;
     const void *Qq;
     const void *Cq;
@@ -51,6 +56,9 @@ struct DistArgs {
     // every kept key is appended to its row in the product itself.
     void *stage = nullptr;
     int64_t stage_bytes = 0;
+    // FILTER on the pipelined product only: corpus index of column 0 (the corpus
+    // passes in blocks of columns)
+    int64_t col_base = 0;
     // filled by the launcher
     uint32_t tiles_m, tiles_n;
 };
@@ -94,11 +102,23 @@ hipError_t launch_dist_gemm_queue(const DistArgs *jobs, const GemmItem *items, i
 // and its launch.  launch_dist_gemm uses it where it applies.
 bool gemm_sk_applies(const DistArgs &a, int epi);
 hipError_t launch_dist_gemm_sk(const DistArgs &a, hipStream_t stream);
+// The pipelined product on 256 x 256 tiles (gemm_pipe.hip): whether it serves `a`
+// (KNN_GEMM_PIPE=0 turns it off for BF16 and FP8), and its launch.
+// launch_dist_gemm uses it where it applies.
+bool gemm_pipe_applies(const DistArgs &a, int epi);
+hipError_t launch_dist_gemm_pipe(const DistArgs &a, int epi, hipStream_t stream);
+// Compute units of the current device.
+int device_cus();
 // Tile shape launch_dist_gemm uses for `a` (kTile*).
 int gemm_tile_choice(const DistArgs &a);
 // Squared norms of n rows of d floats into out; with max_bits (non-null, zero or
 // a smaller value at launch) the largest norm's FP32 bits are folded in too.
 hipError_t launch_sqnorm(const float *X, int64_t n, int d, float *out, unsigned int *max_bits, hipStream_t stream);
+// The two-half operands of n rows of d floats (rows of split_row_bytes(d) bytes)
+// with their scales 2^-e, and in the same read the squared norms (norm and
+// max_bits as launch_sqnorm's, the same bits; norm may be null).  d >= 64.
+hipError_t launch_split(const float *X, int64_t n, int d, void *out, float *scale_out, float *norm,
+                        unsigned int *max_bits, hipStream_t stream);
 hipError_t launch_gather_rows(const float *src, int64_t n, int d, const int32_t *idx, int64_t rows, float *dst,
                               const float *norms, float *dst_norms, hipStream_t stream);
 hipError_t launch_flag_rows(const uint32_t *cnt, int64_t m, uint32_t need, uint32_t cap, int force, uint32_t *nflag,

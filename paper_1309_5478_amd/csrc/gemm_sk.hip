@@ -310,18 +310,6 @@ __global__ __launch_bounds__(256) void sk_append_kernel(SkStage st, uint64_t nwa
 }
 
 // ---- host side --------------------------------------------------------------
-static int device_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                                    hipSuccess || n < 1)
-            n = 256;
-        cus = n;
-    }
-    return cus;
-}
-
 bool gemm_sk_applies(const DistArgs &a, int epi) {
     if (epi != kEpiFilter || (a.prec != kPrecBF16 && a.prec != kPrecFP8)) return false;
     if (const char *e = std::getenv("KNN_GEMM_SK"))

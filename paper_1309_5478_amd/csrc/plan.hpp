@@ -31,6 +31,10 @@ struct Carve {
 constexpr int kSampleCols = 2048;
 constexpr int kSampleColsMax = 16384;
 constexpr int64_t kRowBlock = 32768;
+// split operands of the corpus held at a time (a larger corpus passes in blocks
+// of columns, split again for every block of rows: 8 bytes moved per element
+// against 2 Mb flops)
+constexpr size_t kSplitBytes = size_t(8) << 30;
 constexpr size_t kDenseBytes = size_t(1) << 30;  // materialised distance block budget
 
 struct Plan {
@@ -43,6 +47,8 @@ struct Plan {
     bool graph, unfused;
     int force;
     int force_rerun;
+    bool split;        // FP32 product on two-half operands (ldq: bytes per split row)
+    int64_t Nb;        // corpus points whose operands are held at a time
     // fused
     int S;
     bool gathered;
@@ -98,6 +104,16 @@ inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
             b.Qfq = c.take<char>((size_t)p.Fb * p.ldq);
             b.qfs = c.take<float>(p.Fb);
         }
+    }
+    if (p.split) {
+        b.Cq = c.take<char>((size_t)p.Nb * p.ldq);
+        b.cs = c.take<float>(p.Nb);
+        if (!p.graph || p.Nb < p.n) {
+            b.Qq = c.take<char>((size_t)p.Mb * p.ldq);
+            b.qs = c.take<float>(p.Mb);
+        }
+        b.Csq = c.take<char>((size_t)p.S * p.ldq);
+        b.css = c.take<float>(p.S);
     }
     size_t selws = 0;
     {
@@ -200,6 +216,37 @@ inline hipError_t select_dense(const float *D, int64_t rows, int64_t cols, int64
     return launch_select(a, cap, select_grid(cap, rows, num_cu), ws, stream);
 }
 
+// Puts an FP32 plan's products on two-half operands (gemm_pipe.hip) where they
+// are at least as exact as the FP32 matrix instruction (d >= 64, measured there)
+// and pay: from 128 rows on (making the operands moves 8 bytes per corpus
+// element, about what 150 rows of the FP32 product take) and once the filter has
+// about a 256 x 256 tile per CU (16 x 16 tiles at n = m = 4096; fewer leave CUs
+// idle that smaller FP32 tiles use).  Only the filtered path: a corpus no larger
+// than its sample is too small.
+// KNN_GEMM_SPLIT=0 turns it off, KNN_SPLIT_BYTES caps the operands held (tests).
+inline void plan_split(Plan &p) {
+    if (p.prec != kPrecF32 || p.unfused || !p.gathered || p.d < 64 || p.m < 128) return;
+    const int64_t bytes = split_row_bytes(p.d);
+    const int64_t rows = p.m < p.Mb ? p.m : p.Mb;
+    if (bytes > (1 << 22) || ((rows + 255) / 256) * ((p.n + 255) / 256) < 192) return;
+    if (const char *e = std::getenv("KNN_GEMM_SPLIT"))
+        if (e[0] == '0') return;
+    if (std::getenv("KNN_GEMM_TILE")) return;  // a tile of the FP32 product is asked for
+    size_t budget = kSplitBytes;
+    if (const char *e = std::getenv("KNN_SPLIT_BYTES")) {
+        const long long v = std::atoll(e);
+        if (v > 0) budget = (size_t)v;
+    }
+    int64_t nb = (int64_t)(budget / (size_t)bytes) / 256 * 256;
+    if (nb < 256) nb = 256;
+    p.Nb = nb < p.n ? nb : p.n;
+    p.ldq = bytes;
+    p.split = true;
+    // three times the terms, each with a rounding (one accumulation of 3 d
+    // products); both operands within 2^-23 of themselves; low x low left out
+    p.rel = (float)(std::ldexp(1.0, -21) + 3.0 * p.gamma);
+}
+
 // The plan of one search / graph call: candidate oversampling, threshold sample,
 // list capacity, row blocking.  Mb_limit caps the rows per block.
 inline Plan make_plan(int64_t m, int64_t n, int d, int k, bool graph, const knn_options_t *opt, int64_t Mb_limit) {
@@ -210,6 +257,7 @@ inline Plan make_plan(int64_t m, int64_t n, int d, int k, bool graph, const knn_
     p.d = d;
     p.k = k;
     p.graph = graph;
+    p.Nb = n;
     int over = opt && opt->oversample > 0 ? opt->oversample : 4;
     int64_t kk = (int64_t)k * over;
     if (kk > kSelectMaxK) kk = kSelectMaxK;

@@ -74,11 +74,18 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     int smode = opt ? opt->pivot : kPivotSample;
     if (smode == kPivotLearned && !net) smode = kPivotSample;
     Plan p = make_plan(m, n, d, k, graph, opt, m);
+    if (!autotune_enabled(opt)) plan_split(p);  // (autotuning times the FP32 tiles)
     Bufs b;
-    Carve sizing{nullptr};
-    size_t bytes = carve(sizing, p, b, num_cu);
+    auto need = [&]() {
+        Carve sizing{nullptr};
+        return carve(sizing, p, b, num_cu);
+    };
     void *ws = nullptr;
-    knn_status_t st = ensure_ws(h, bytes, stream, &ws);
+    knn_status_t st = ensure_ws(h, need(), stream, &ws);
+    if (st == KNN_ERROR_OUT_OF_MEMORY && p.split) {  // no room for the split operands
+        p = make_plan(m, n, d, k, graph, opt, m);
+        st = ensure_ws(h, need(), stream, &ws);
+    }
     if (st != KNN_SUCCESS) return st;
     Carve real{static_cast<char *>(ws)};
     carve(real, p, b, num_cu);
@@ -91,8 +98,13 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     } while (0)
 
     KNN_TRY(launch_fill_u32(b.cmax2, 1, 0u, stream));
-    KNN_TRY(launch_sqnorm(C, n, d, b.cnorm, b.cmax2, stream));
-    KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
+    // split operands of the whole corpus: made once, with the norms
+    const bool whole = p.split && p.Nb >= n;
+    if (whole) KNN_TRY(launch_split(C, n, d, b.Cq, b.cs, b.cnorm, b.cmax2, stream));
+    else KNN_TRY(launch_sqnorm(C, n, d, b.cnorm, b.cmax2, stream));
+    const float *qn2 = b.qn2;  // a graph's queries are its corpus
+    if (graph) qn2 = b.cnorm;
+    else if (!p.split) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
     const void *Qq = nullptr, *Cq = nullptr;
     const float *qsc = nullptr, *csc = nullptr;
     if (p.prec != kPrecF32) {
@@ -108,8 +120,12 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             qsc = b.qs;
         }
     }
+    if (whole && graph) {
+        Qq = b.Cq;
+        qsc = b.cs;
+    }
     auto set_prec = [&](DistArgs &a, const void *qq, const float *qs, const void *cq, const float *cs) {
-        a.prec = p.prec;
+        a.prec = p.split ? kPrecSplit : p.prec;
         a.Qq = qq;
         a.Cq = cq;
         a.ldq = p.ldq;
@@ -137,7 +153,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         const float *Qb = Q + i0 * d;
         if (certify) {
             if (refix) KNN_TRY(launch_fill_u32(b.nu, 1, 0u, stream));
-            CertifyArgs ca{keys, mb, p.kk, k, b.qn2 + i0, b.cmax2, p.rel, p.gamma, stats_ptr(h) + kStatUncertified,
+            CertifyArgs ca{keys, mb, p.kk, k, qn2 + i0, b.cmax2, p.rel, p.gamma, stats_ptr(h) + kStatUncertified,
                            refix ? b.ulist : nullptr, b.nu, b.tfix, refix && p.force_rerun};
             KNN_TRY(launch_certify(ca, stream));
         }
@@ -235,6 +251,10 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             KNN_TRY(launch_quantize(b.Cs, p.S, d, p.prec, b.Csq, b.css, stream));
             Csq = b.Csq;
             css = b.css;
+        } else if (p.split) {
+            KNN_TRY(launch_split(b.Cs, p.S, d, b.Csq, b.css, nullptr, nullptr, stream));
+            Csq = b.Csq;
+            css = b.css;
         }
     }
     // tile shape of the fused product: measured once per shape class when
@@ -278,6 +298,14 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     for (int64_t i0 = 0; i0 < m; i0 += p.Mb) {
         const int64_t mb = m - i0 < p.Mb ? m - i0 : p.Mb;
         const float *Qb = Q + i0 * d;
+        // this block's split operands (the corpus's, where that is the same)
+        const void *Qbq = qrow(i0);
+        const float *qbs = qsrow(i0);
+        if (p.split && !Qbq) {
+            KNN_TRY(launch_split(Qb, mb, d, b.Qq, b.qs, graph ? nullptr : b.qn2 + i0, nullptr, stream));
+            Qbq = b.Qq;
+            qbs = b.qs;
+        }
         // 1. thresholds from the sample
         DistArgs sa{};
         sa.Q = Qb;
@@ -289,7 +317,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         sa.self_offset = (graph && !p.gathered) ? i0 : -1;
         sa.out = b.Ds;
         sa.ldo = p.S;
-        set_prec(sa, qrow(i0), qsrow(i0), Csq, css);
+        set_prec(sa, Qbq, qbs, Csq, css);
         if (!p.gathered) KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
         KNN_TRY(launch_dist_gemm(sa, kEpiDense, stream));
         if (!p.gathered) KNN_TRY(timer.end(stream));
@@ -324,9 +352,16 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         fa.tile = ftile;
         fa.stage = b.stage;
         fa.stage_bytes = (int64_t)b.stage_bytes;
-        set_prec(fa, qrow(i0), qsrow(i0), Cq, csc);
+        set_prec(fa, Qbq, qbs, p.split ? b.Cq : Cq, p.split ? b.cs : csc);
         KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
-        KNN_TRY(launch_dist_gemm(fa, kEpiFilter, stream));
+        for (int64_t c0 = 0; c0 < n; c0 += p.Nb) {  // (one block unless split operands are capped)
+            fa.n = n - c0 < p.Nb ? n - c0 : p.Nb;
+            fa.cnorm = b.cnorm + c0;
+            fa.col_base = c0;
+            if (p.split && !whole)
+                KNN_TRY(launch_split(C + c0 * d, fa.n, d, b.Cq, b.cs, nullptr, nullptr, stream));
+            KNN_TRY(launch_dist_gemm(fa, kEpiFilter, stream));
+        }
         KNN_TRY(timer.end(stream));
         KNN_TRY(launch_sum_u32(b.cnt, mb, stats_ptr(h) + kStatCandidates, stream));
         // 3. exact re-do of rows whose candidate list is unusable
@@ -352,7 +387,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             da.row_ids = b.flags + f0;
             da.out = b.Df;
             da.ldo = n;
-            set_prec(da, b.Qfq, b.qfs, Cq, csc);
+            if (!p.split) set_prec(da, b.Qfq, b.qfs, Cq, csc);
             KNN_TRY(launch_dist_gemm(da, kEpiDense, stream));
             KNN_TRY(select_dense(b.Df, fb, n, n, p.kk, b.fv, b.fi, b.selws, num_cu, smode, net, stream));
             KNN_TRY(launch_scatter_fallback(b.flags + f0, fb, b.fv, b.fi, p.kk, b.cand, b.cnt, p.cap, stream));

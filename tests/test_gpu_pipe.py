@@ -1,0 +1,110 @@
+"""The pipelined 256 x 256 product (gemm_pipe.hip) against the paths it stands
+in for.
+
+FP32 results are the exact k nearest by the FP32 direct-form distance whatever
+product ranks the candidates, so the product on two-half operands and the FP32
+matrix instruction (KNN_GEMM_SPLIT=0) must agree bit for bit, on every kind of
+data.  BF16 and FP8 form the same key bits on either tile (KNN_GEMM_PIPE=0)."""
+import os
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    return t
+
+
+@pytest.fixture(scope="module")
+def h(torch):
+    import paper_1309_5478_amd as knn
+    return knn.Handle(0)
+
+
+def points(kind, n, d, seed):
+    r = np.random.default_rng(seed)
+    if kind == "uniform":
+        return r.random((n, d), dtype=np.float32)
+    x = r.normal(0, 1, (n, d)).astype(np.float32)
+    if kind == "gmm":
+        mu = (2 * r.normal(0, 1, (16, d))).astype(np.float32)
+        return x + mu[r.integers(0, 16, n)]
+    if kind == "lognormal":              # magnitudes over many binades
+        return (np.exp(3 * x) * np.sign(r.normal(0, 1, (n, d)))).astype(np.float32)
+    if kind == "scales":                 # points of very different norms, zero points
+        x *= np.exp2(r.integers(-40, 40, (n, 1))).astype(np.float32)
+        x[::97] = 0.0
+        return x
+    if kind == "dups":                   # many exact duplicates
+        return x[r.integers(0, max(n // 5, 1), n)]
+    assert kind == "nonfinite"
+    x[5, 3], x[n // 2, 0], x[n - 1, d - 1] = np.inf, np.nan, -np.inf
+    return x
+
+
+def both(env, off, fn):
+    a = fn()
+    os.environ[env] = off
+    try:
+        b = fn()
+    finally:
+        del os.environ[env]
+    return a, b
+
+
+def same(a, b):
+    for x, y in zip(a, b):
+        assert np.array_equal(x.cpu().numpy().view(np.uint32), y.cpu().numpy().view(np.uint32))
+
+
+# (m, n, d, k): row and column remainders of a tile, the smallest d and m, odd d,
+# one k-chunk and a ragged last one, lists that overflow (k = 256 of 20011)
+SHAPES = [(4096, 4099, 64, 5), (128, 49153, 65, 3), (129, 60001, 100, 10), (257, 30000, 128, 16),
+          (4097, 5003, 96, 33), (1000, 20011, 64, 256), (700, 40000, 1000, 20)]
+
+
+@pytest.mark.parametrize("kind", ["uniform", "gmm", "lognormal", "scales", "dups", "nonfinite"])
+@pytest.mark.parametrize("m,n,d,k", SHAPES[:2])
+def test_split_matches_fp32_kinds(h, torch, kind, m, n, d, k):
+    print(f"split {kind} {m}x{n}x{d} k={k}", flush=True)
+    Q = torch.from_numpy(points(kind, m, d, 1)).cuda()
+    C = torch.from_numpy(points(kind, n, d, 2)).cuda()
+    a, b = both("KNN_GEMM_SPLIT", "0", lambda: h.search(Q, C, k))
+    same(a, b)
+
+
+@pytest.mark.parametrize("m,n,d,k", SHAPES[2:])
+def test_split_matches_fp32_shapes(h, torch, m, n, d, k):
+    print(f"split {m}x{n}x{d} k={k}", flush=True)
+    Q = torch.from_numpy(points("gmm", m, d, 3)).cuda()
+    C = torch.from_numpy(points("gmm", n, d, 4)).cuda()
+    for metric in ("sqeuclidean", "pearson"):
+        a, b = both("KNN_GEMM_SPLIT", "0", lambda: h.search(Q, C, k, metric=metric))
+        same(a, b)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_split_in_column_blocks(h, torch, graph):
+    """Split operands capped at 5 blocks of the corpus's columns (with a ragged
+    last one): the same result, own points excluded in every block."""
+    n, d, k = 20011, 96, 12
+    P = torch.from_numpy(points("dups", n, d, 5)).cuda()
+    Q = torch.from_numpy(points("dups", 3000, d, 6)).cuda()
+    run = (lambda: h.graph(P, k)) if graph else (lambda: h.search(Q, P, k))
+    a, b = both("KNN_SPLIT_BYTES", str(4352 * 384), run)
+    same(a, b)
+    a, b = both("KNN_GEMM_SPLIT", "0", run)
+    same(a, b)
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+@pytest.mark.parametrize("n,d,k", [(4099, 64, 5), (5003, 129, 33), (20011, 200, 256), (9000, 700, 16)])
+def test_low_precision_matches_small_tiles(h, torch, prec, n, d, k):
+    print(f"{prec} graph {n}x{d} k={k}", flush=True)
+    P = torch.from_numpy(points("gmm", n, d, 7)).cuda()
+    a, b = both("KNN_GEMM_PIPE", "0", lambda: h.graph(P, k, precision=prec))
+    same(a, b)
