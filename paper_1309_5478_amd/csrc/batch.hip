@@ -454,6 +454,13 @@ hipError_t certify_rerank(const BatchState &b, knn_handle_t h, size_t pi, const 
     }
     RerankArgs rr{js.Q + pt.i0 * js.d, pt.mb, js.C, js.n, js.d, cidx, (uint32_t)p.kk, js.k,
                   js.out_dist + pt.i0 * js.k, js.out_idx + pt.i0 * js.k, js.graph ? pt.i0 : -1, js.oscale};
+    if (p.kk < p.n_eff && p.prec == kPrecF32) {
+        rr.keys = keys;
+        rr.qnorm2 = js.qn2 + pt.i0;
+        rr.cmax2_bits = js.cmax2;
+        rr.rel = p.rel;
+        rr.gamma = p.gamma;
+    }
     return launch_rerank(rr, s);
 }
 

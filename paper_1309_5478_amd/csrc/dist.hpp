@@ -76,6 +76,14 @@ struct RerankArgs {
     int32_t *out_idx;       // m x k
     int64_t self_offset = -1;  // >= 0: row i's own corpus index self_offset + i is never returned
     float out_scale = 1.0f;    // returned distance = out_scale * the direct-form sum (a power of two)
+    // Optional (FP32 products): the candidates' ascending reduced keys (m x kk)
+    // and what bounds their error (as CertifyArgs).  Candidates whose key lies so
+    // far above the k-th that neither the keys' nor the direct form's rounding
+    // can bring them among the k smallest are not read.
+    const float *keys = nullptr;
+    const float *qnorm2 = nullptr;
+    const unsigned int *cmax2_bits = nullptr;
+    float rel = 0.f, gamma = 0.f;
 };
 
 hipError_t launch_dist_gemm(const DistArgs &a, int epi, hipStream_t stream);

@@ -159,6 +159,13 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         }
         RerankArgs rr{Qb, mb, C, n, d, cidx, (uint32_t)p.kk, k, out_dist + i0 * k, out_idx + i0 * k,
                       graph ? i0 : -1, oscale};
+        if (refix) {
+            rr.keys = keys;
+            rr.qnorm2 = qn2 + i0;
+            rr.cmax2_bits = b.cmax2;
+            rr.rel = p.rel;
+            rr.gamma = p.gamma;
+        }
         KNN_TRY(launch_rerank(rr, stream));
         if (!refix) return KNN_SUCCESS;
         KNN_TRY(hipMemcpyAsync(hcount, b.nu, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
