@@ -6,6 +6,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <vector>
 
 #include "dist.hpp"
 #include "handle.hpp"
@@ -169,8 +170,15 @@ knn_status_t knn_create(knn_handle_t *out, int device) {
         delete h;
         return hip_fail(nullptr, e, "hipMalloc(stats)");
     }
+    if ((e = hipMalloc(&h->slots_dev, (size_t)h->num_cu * kSelSlotGroups * kSelSlot * sizeof(unsigned long long))) !=
+        hipSuccess) {
+        hipFree(h->stats_dev);
+        delete h;
+        return hip_fail(nullptr, e, "hipMalloc(selection totals)");
+    }
     if ((e = hipHostMalloc(&h->pinned, sizeof(uint32_t), hipHostMallocDefault)) != hipSuccess) {
         hipFree(h->stats_dev);
+        hipFree(h->slots_dev);
         delete h;
         return hip_fail(nullptr, e, "hipHostMalloc");
     }
@@ -190,6 +198,7 @@ knn_status_t knn_destroy(knn_handle_t h) {
         if (ev) hipEventDestroy(ev);
     if (h->copy_stream) hipStreamDestroy(h->copy_stream);
     if (h->stats_dev) hipFree(h->stats_dev);
+    if (h->slots_dev) hipFree(h->slots_dev);
     if (h->pinned) hipHostFree(h->pinned);
     for (void *p : {(void *)h->net_theta, (void *)h->net_theta_r, (void *)h->net_m, (void *)h->net_v,
                     (void *)h->net_grad, (void *)h->net_bf16, (void *)h->ex_x, (void *)h->ex_y})
@@ -198,9 +207,14 @@ knn_status_t knn_destroy(knn_handle_t h) {
     return KNN_SUCCESS;
 }
 
-static knn_status_t begin_stats(knn_handle_t h, hipStream_t stream) {
-    hipError_t e = launch_zero_u64(h->stats_dev, kStatCount, stream);
-    if (e != hipSuccess) return hip_fail(h, e, "stats reset");
+// `slots`: workgroups of a selection, whose totals take the place of the device
+// counters (nothing to clear: each workgroup writes its own); 0 for other calls.
+static knn_status_t begin_stats(knn_handle_t h, hipStream_t stream, int slots = 0) {
+    if (slots == 0) {
+        hipError_t e = launch_zero_u64(h->stats_dev, kStatCount, stream);
+        if (e != hipSuccess) return hip_fail(h, e, "stats reset");
+    }
+    h->last_slots = slots;
     h->last_stream = stream;
     h->stats_pending = true;
     h->host_rows = 0;
@@ -246,14 +260,13 @@ knn_status_t knn_select_k(knn_handle_t h, const float *dist, int64_t rows, int64
     int cap = select_cap_for_k((uint32_t)k);
     SplitPlan sp{1, 1, (uint32_t)cols, 0};
     if (!(flags & KNN_FLAG_NO_SPLIT))
-        sp = select_split_plan(rows, (uint32_t)cols, (uint32_t)k, h->num_cu, (flags & KNN_FLAG_FORCE_SPLIT) != 0);
+        sp = select_split_plan(rows, (uint32_t)cols, (uint32_t)k, h->num_cu, (flags & KNN_FLAG_FORCE_SPLIT) != 0,
+                               mode == kPivotSample);
     int grid = sp.parts > 1 ? sp.grid : select_grid(cap, rows, h->num_cu);
     void *ws = nullptr;
     size_t need = sp.parts > 1 ? select_split_ws_bytes(sp, rows, (uint32_t)k) : select_ws_bytes(cap, (uint32_t)cols, grid);
     knn_status_t st = ensure_ws(h, need < 256 ? 256 : need, stream, &ws);
     if (st != KNN_SUCCESS) return st;
-    if ((st = begin_stats(h, stream)) != KNN_SUCCESS) return st;
-    h->last_split_parts = sp.parts;
     SelectArgs a{};
     a.dist = dist;
     a.rows = rows;
@@ -264,7 +277,10 @@ knn_status_t knn_select_k(knn_handle_t h, const float *dist, int64_t rows, int64
     a.out_idx = out_idx;
     a.net = mode == kPivotLearned ? h->net_bf16 : nullptr;
     a.mode = mode;
-    a.stats = h->stats_dev;
+    a.slots = h->slots_dev;
+    const int groups = sp.parts > 1 ? select_split_grid(a, sp, h->num_cu) : select_launch_grid(a, grid, h->num_cu);
+    if ((st = begin_stats(h, stream, groups)) != KNN_SUCCESS) return st;
+    h->last_split_parts = sp.parts;
     hipError_t e = sp.parts > 1 ? launch_select_split(a, sp, ws, h->num_cu, stream) : launch_select(a, cap, grid, ws, stream);
     if (e != hipSuccess) return hip_fail(h, e, "select kernel launch");
     return KNN_SUCCESS;
@@ -293,8 +309,6 @@ knn_status_t knn_select_k_noalloc(knn_handle_t h, const float *dist, int64_t row
         const int64_t fit = (int64_t)((kScratchBytes - hdr) / (one - hdr));
         if (grid > fit) grid = (int)fit;
     }
-    knn_status_t st = begin_stats(h, stream);
-    if (st != KNN_SUCCESS) return st;
     int mode = opt ? opt->pivot : kPivotSample;
     if (mode == kPivotLearned && !h->has_net) mode = kPivotSample;
     SelectArgs a{};
@@ -307,7 +321,9 @@ knn_status_t knn_select_k_noalloc(knn_handle_t h, const float *dist, int64_t row
     a.out_idx = out_idx;
     a.net = mode == kPivotLearned ? h->net_bf16 : nullptr;
     a.mode = mode;
-    a.stats = h->stats_dev;
+    a.slots = h->slots_dev;
+    knn_status_t st = begin_stats(h, stream, select_launch_grid(a, grid, h->num_cu));
+    if (st != KNN_SUCCESS) return st;
     hipError_t e = launch_select(a, cap, grid, h->scratch, stream);
     if (e != hipSuccess) return hip_fail(h, e, "select kernel launch");
     return KNN_SUCCESS;
@@ -491,7 +507,25 @@ knn_status_t knn_get_stats(knn_handle_t h, knn_stats_t *out) {
         unsigned long long s[kStatCount];
         hipError_t e = hipStreamSynchronize(h->last_stream);
         if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-        e = hipMemcpy(s, h->stats_dev, sizeof(s), hipMemcpyDeviceToHost);
+        if (h->last_slots > 0) {
+            // a selection: the sums (largest, for passes_max) of its workgroups' totals
+            std::vector<unsigned long long> v((size_t)h->last_slots * kSelSlot);
+            e = hipMemcpy(v.data(), h->slots_dev, v.size() * sizeof(v[0]), hipMemcpyDeviceToHost);
+            std::memset(s, 0, sizeof(s));
+            for (int g = 0; g < h->last_slots; ++g) {
+                const unsigned long long *w = &v[(size_t)g * kSelSlot];
+                s[kStatRows] += w[kSlotRows];
+                s[kStatPasses] += w[kSlotPasses];
+                if (w[kSlotPassesMax] > s[kStatPassesMax]) s[kStatPassesMax] = w[kSlotPassesMax];
+                s[kStatStreamPasses] += w[kSlotStreamPasses];
+                s[kStatSpillRows] += w[kSlotSpillRows];
+                s[kStatFirstSurvivors] += w[kSlotFirstSurvivors];
+                for (int c = 0; c < 4; ++c) s[kStatCycSample + c] += w[kSlotCycles + c];
+                s[kStatErrors] += w[kSlotErrors];
+            }
+        } else {
+            e = hipMemcpy(s, h->stats_dev, sizeof(s), hipMemcpyDeviceToHost);
+        }
         if (e != hipSuccess) return hip_fail(h, e, "hipMemcpy(stats)");
         if (s[kStatErrors] != 0)
             return fail(h, KNN_ERROR_DEVICE, "a kernel reported an internal error on " + std::to_string(s[kStatErrors]) + " rows");

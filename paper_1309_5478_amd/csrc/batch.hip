@@ -236,12 +236,14 @@ void plan_selects(BatchState &b) {
     b.sample_sel.clear();
     // a sample row that fits the on-chip capacity is selected there directly
     // (no pivot sample, no streaming), so short rows go to the class that holds them
-    auto sample_cap = [](const Plan &p) {
+    // (class 0: rows selected in registers)
+    auto sample_cap = [&b](const Plan &p) {
+        if (b.smode == kPivotSample && select_short_shape((uint32_t)p.S, (uint32_t)(p.r + 1))) return 0;
         int c = select_cap_for_k((uint32_t)(p.r + 1));
         if (p.S > c && p.S <= kSelectKeysCap) c = p.S <= 2048 ? 2048 : 4096;
         return c;
     };
-    for (int cap : {1024, 2048, 4096}) {
+    for (int cap : {0, 1024, 2048, 4096}) {
         SegLaunch L;
         L.cap = cap;
         for (const BatchPart &pt : b.parts) {
@@ -354,7 +356,7 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
     }
     plan_selects(b);
     for (SegLaunch &L : b.sample_sel) {
-        selws = std::max(selws, select_ws_bytes(L.cap, L.cols, select_grid(L.cap, L.rows, num_cu)));
+        if (L.cap) selws = std::max(selws, select_ws_bytes(L.cap, L.cols, select_grid(L.cap, L.rows, num_cu)));
         L.dsegs = c.take<SelectSeg>(L.segs.size());
         L.drow_seg = c.take<uint32_t>((size_t)L.rows);
     }
@@ -501,7 +503,8 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
     // all threshold selections, one launch per capacity class
     for (const SegLaunch &L : b.sample_sel) {
         SelectArgs sa = seg_select_args(b, L);
-        BTRY(launch_select(sa, L.cap, select_grid(L.cap, L.rows, num_cu), sh.selws, s));
+        if (L.cap == 0) BTRY(launch_select_short(sa, num_cu, s));
+        else BTRY(launch_select(sa, L.cap, select_grid(L.cap, L.rows, num_cu), sh.selws, s));
     }
     // parts whose sample is the whole corpus: certificate and re-rank now
     for (size_t pi = 0; pi < b.parts.size(); ++pi)
@@ -548,7 +551,7 @@ hipError_t enqueue_final(const BatchState &b, knn_handle_t h, int num_cu, hipStr
     // the kk smallest candidate keys of every filtered row, one launch
     if (b.keys_sel.rows) {
         SelectArgs ka = seg_select_args(b, b.keys_sel);
-        BTRY(launch_select_keys(ka, b.sh.selws, ka.rows, num_cu, s));
+        BTRY(launch_select_keys(ka, num_cu, s));
     }
     for (size_t pi = 0; pi < b.parts.size(); ++pi)
         if (!b.parts[pi].direct) BTRY(certify_rerank(b, h, pi, b.parts[pi].sv, b.parts[pi].si, s));
@@ -575,7 +578,7 @@ hipError_t refinal_part(const BatchState &b, knn_handle_t h, int num_cu, size_t 
     ka.out_idx = pt.si;
     ka.mode = b.smode;
     ka.net = b.smode == kPivotLearned ? b.net : nullptr;
-    BTRY(launch_select_keys(ka, b.sh.selws, pt.mb, num_cu, s));
+    BTRY(launch_select_keys(ka, num_cu, s));
     BTRY(certify_rerank(b, h, pi, pt.sv, pt.si, s));
     return hipMemcpyAsync(b.nflag_host + b.parts.size() + pi, b.sh.nu + pi, sizeof(uint32_t), hipMemcpyDeviceToHost,
                           s);

@@ -24,6 +24,8 @@ struct knn_handle_s {
     void *scratch = nullptr;   // device address of this device's static scratch array
     size_t ws_bytes = 0;
     unsigned long long *stats_dev = nullptr;  // kStatCount counters
+    unsigned long long *slots_dev = nullptr;  // per-workgroup totals of a selection (SelectArgs::slots)
+    int last_slots = 0;                       // workgroups of the last knn_select_k (0: another call)
     hipStream_t last_stream = nullptr;
     knn_stats_t last{};
     bool stats_pending = false;

@@ -26,6 +26,21 @@ enum StatSlot : int {
     kStatCount = 14
 };
 
+// Row statistics of one selection workgroup (see SelectArgs::slots).
+enum SelSlot : int {
+    kSlotRows = 0,
+    kSlotPasses = 1,
+    kSlotPassesMax = 2,
+    kSlotStreamPasses = 3,
+    kSlotSpillRows = 4,
+    kSlotFirstSurvivors = 5,
+    kSlotCycles = 6,  // sample, stream, select, final
+    kSlotErrors = 10,
+    kSelSlot = 16     // 128 bytes
+};
+// Workgroups a selection launch may have (what the slots are allocated for).
+constexpr int kSelSlotGroups = 8;  // per CU
+
 // ---- selection over a given FP32 matrix ------------------------------------
 // One matrix of a multi-matrix selection: its rows are rows row0 .. of the
 // launch.  Either dense rows (dist, row stride ld) or key-list rows (keys,
@@ -55,7 +70,11 @@ struct SelectArgs {
     const uint64_t *keys;
     const uint32_t *key_cnt;
     int mode;              // PivotMode
-    unsigned long long *stats;  // kStatCount counters, or null
+    // per-workgroup totals: workgroup b writes kSelSlot counters (SelSlot) at
+    // slots + b * kSelSlot, or null.  (One line each, plain stores: a few
+    // counters of all workgroups in one line serialised their atomics at 11 ns,
+    // 17 us of a 27 us call with 512 workgroups.)
+    unsigned long long *slots;
     // several matrices in one launch: row r belongs to segs[row_seg[r]]; then
     // rows is the total, cols and k the largest of the segments (they size the
     // workspace and the capacity class), and dist / keys / outputs come from
@@ -92,14 +111,28 @@ int select_cap_for_k(uint32_t k);
 int select_grid(int cap, int64_t rows, int num_cu);
 // Global workspace bytes for a launch with `grid` workgroups over rows of `cols`.
 size_t select_ws_bytes(int cap, uint32_t cols, int grid);
+// Workgroups of a short selection, and of the launch that launch_select makes of
+// (a, grid).
+int select_short_grid(const SelectArgs &a, int num_cu);
+int select_launch_grid(const SelectArgs &a, int grid, int num_cu);
 // Launch; `ws` must hold select_ws_bytes(...) bytes.
 hipError_t launch_select(const SelectArgs &a, int cap, int grid, void *ws, hipStream_t stream);
+// Rows of 1025 to 16384 columns held on chip whole (select_short.hip): the
+// shapes it is for (k above 128 needs more groups with values of several
+// columns each, or a row short enough to sort), whether it serves `a`
+// (launch_select uses it then; a launch over several matrices only when asked
+// for here, every segment of such a shape), and its launch.  No workspace.
+constexpr uint32_t kShortMinCols = 1025, kShortMaxCols = 16384, kShortMaxK = 512;
+constexpr uint32_t kShortSortCols = 2016;
+inline bool select_short_shape(uint32_t cols, uint32_t k) {
+    return cols >= kShortMinCols && cols <= kShortMaxCols && k <= kShortMaxK &&
+           (k <= 128 || cols <= kShortSortCols || cols >= 4096);
+}
+bool select_short_applies(const SelectArgs &a);
+hipError_t launch_select_short(const SelectArgs &a, int num_cu, hipStream_t stream);
 // Selection over key-list rows (a.keys / a.key_cnt set, a.cols <= kSelectKeysCap).
 constexpr int kSelectKeysCap = 4096;
-// `counter` (8 bytes of device memory, or null for strided rows) holds the
-// launch's row counter.
-hipError_t launch_select_keys(const SelectArgs &a, void *counter, int64_t rows_grid_limit, int num_cu,
-                              hipStream_t stream);
+hipError_t launch_select_keys(const SelectArgs &a, int num_cu, hipStream_t stream);
 
 // ---- rows split across workgroups -----------------------------------------------
 // Few long rows leave most of the device idle with one workgroup per row.  Each
@@ -113,8 +146,11 @@ struct SplitPlan {
     int grid;                      // workgroups of the part selection
 };
 // parts = 1 when splitting is not worth it; `force` splits whenever the row is
-// at least two minimal parts long.
-SplitPlan select_split_plan(int64_t rows, uint32_t cols, uint32_t k, int num_cu, bool force);
+// at least two minimal parts long.  `sample`: the sample pivot rule, whose parts
+// may be short enough for registers.
+SplitPlan select_split_plan(int64_t rows, uint32_t cols, uint32_t k, int num_cu, bool force, bool sample);
+// Workgroups of the part selection that launch_select_split makes.
+int select_split_grid(const SelectArgs &a, const SplitPlan &sp, int num_cu);
 size_t select_split_ws_bytes(const SplitPlan &sp, int64_t rows, uint32_t k);
 // a: the whole call as for launch_select (dist, rows, cols, ld, k, outputs,
 // mode, net, stats; out_idx may be null).

@@ -4,6 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace knn {
 
 constexpr int kWave = 64;
@@ -87,10 +90,19 @@ __device__ __forceinline__ bool key_below(float v, uint32_t j, const Pivot &p) {
     return lt || (eq && j < p.pidx);
 }
 
+// Lanes whose bit b (1, 2, .. 32) is clear.
+constexpr uint64_t lanes_clear(uint32_t b) {
+    return b == 1 ? 0x5555555555555555ull : b == 2 ? 0x3333333333333333ull : b == 4 ? 0x0F0F0F0F0F0F0F0Full
+         : b == 8 ? 0x00FF00FF00FF00FFull : b == 16 ? 0x0000FFFF0000FFFFull : 0x00000000FFFFFFFFull;
+}
+// This lane's bit of a mask that is the same in every lane.
+__device__ __forceinline__ bool mine(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // The value of lane (lane ^ mask), every lane of the wave active.  Masks 1, 2
 // and 8 are single DPP moves (quad permutations, a rotation by 8 within rows
-// of 16), mask 4 two DPP moves (half-row mirror, quad reversal), mask 16 a
-// swizzle within halves of 32; only mask 32 and others go through the LDS
+// of 16), mask 4 two DPP moves (half-row mirror, quad reversal), masks 16 and 32
+// a swap of odd with even rows of 16 or of halves of 32 between two copies (each
+// lane's partner is then in one copy or the other); others go through the LDS
 // crossbar.
 __device__ __forceinline__ uint32_t xor_lanes32(uint32_t v, int mask) {
     const int x = (int)v;
@@ -104,7 +116,14 @@ __device__ __forceinline__ uint32_t xor_lanes32(uint32_t v, int mask) {
             return (uint32_t)__builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, false);  // quad_perm 3,2,1,0
         }
         case 8: return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, false);  // row_ror:8
-        case 16: return (uint32_t)__builtin_amdgcn_ds_swizzle(x, 0x401F);                    // xor 16 in 32
+        case 16: {
+            const auto w = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+            return mine(lanes_clear(16)) ? w[1] : w[0];
+        }
+        case 32: {
+            const auto w = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            return mine(lanes_clear(32)) ? w[1] : w[0];
+        }
         default: return (uint32_t)__shfl_xor(x, mask);
     }
 }
@@ -115,6 +134,9 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
     const uint32_t hi = xor_lanes32((uint32_t)(v >> 32), mask);
     return ((uint64_t)hi << 32) | lo;
 }
+
+__device__ __forceinline__ uint64_t shfl_xor_any(uint64_t v, int mask) { return shfl_xor_u64(v, mask); }
+__device__ __forceinline__ uint32_t shfl_xor_any(uint32_t v, int mask) { return xor_lanes32(v, mask); }
 
 // For masks only known at run time: one LDS-crossbar permute per half.
 __device__ __forceinline__ uint64_t shfl_xor_u64_rt(uint64_t v, int mask) {
@@ -136,25 +158,97 @@ __device__ __forceinline__ T uniform_load(const T *p) {
     return v;
 }
 
-// Ascending bitonic sort of one key per lane across the 64 lanes of a wave.
-__device__ __forceinline__ uint64_t wave_sort64(uint64_t key) {
-    const uint32_t lane = lane_id();
+// A lane mask (the same in every lane) with the constant C's bits flipped, by
+// literal operands of scalar instructions: the constants of a network's steps
+// are then part of its code, where the compiler would keep them in scalar
+// registers across a loop over rows (some two hundred, spilled).
+template <uint64_t C>
+__device__ __forceinline__ uint64_t flip(uint64_t m) {
+    uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+    if constexpr ((uint32_t)C != 0) asm("s_xor_b32 %0, %1, %2" : "=s"(lo) : "s"(lo), "i"((uint32_t)C) : "scc");
+    if constexpr ((uint32_t)(C >> 32) != 0)
+        asm("s_xor_b32 %0, %1, %2" : "=s"(hi) : "s"(hi), "i"((uint32_t)(C >> 32)) : "scc");
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// f(integral_constant 0), f(integral_constant 1), ..
+template <class F, int... I>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// Steps of a bitonic sort of n keys, and the (size, stride) of step i.
+constexpr int bitonic_steps(uint32_t n) {
+    int c = 0;
+    for (uint32_t size = 2; size <= n; size <<= 1)
+        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) ++c;
+    return c;
+}
+constexpr uint32_t bitonic_at(int i, bool want_size) {
+    for (uint32_t size = 2;; size <<= 1)
+        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1)
+            if (i-- == 0) return want_size ? size : stride;
+}
+
+// One step of a bitonic network between lanes: every lane keeps its key or takes
+// its partner's, the smaller where A ^ B ^ dyn has a clear bit.  The
+// comparison's mask is combined with the direction in scalar registers.
+template <uint64_t C, class K>
+__device__ __forceinline__ K lane_step(K key, K other, uint64_t dyn = 0) {
+    return mine(flip<C>(__ballot(key < other)) ^ dyn) ? key : other;
+}
+
+// Ascending bitonic sort of 64 J keys across a wave (key l J + j in lane l).
+template <int J, class K>
+__device__ __forceinline__ void wave_sort_regs(K (&k)[J]) {
+    constexpr uint32_t N = (uint32_t)kWave * J, UJ = J;
+    static_for(std::make_integer_sequence<int, bitonic_steps(N)>{}, [&](auto i) {
+        constexpr uint32_t size = bitonic_at(decltype(i)::value, true), stride = bitonic_at(decltype(i)::value, false);
+        // kept where (key < other) == take_min, take_min = (bit stride clear) == (bit size clear)
+        constexpr uint64_t D = size == N ? ~0ull : (size >= UJ ? lanes_clear(size / UJ > 0 ? size / UJ : 1) : 0ull);
+        if constexpr (stride < UJ) {
 #pragma unroll
-    for (int size = 2; size <= kWave; size <<= 1) {
+            for (int j = 0; j < J; ++j)
+                if ((j & stride) == 0) {
+                    const K a = k[j], b = k[j + stride];
+                    bool swap;
+                    if constexpr (size < UJ) swap = (a > b) == ((j & size) == 0);
+                    else swap = mine(flip<~D>(__ballot(a > b)));
+                    k[j] = swap ? b : a;
+                    k[j + stride] = swap ? a : b;
+                }
+        } else {
 #pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const uint64_t other = shfl_xor_u64(key, stride);
-            const bool take_min = ((lane & stride) == 0) == ((lane & size) == 0);
-            key = ((key < other) == take_min) ? key : other;
+            for (int j = 0; j < J; ++j)
+                k[j] = lane_step<lanes_clear(stride / UJ) ^ D>(k[j], shfl_xor_any(k[j], (int)(stride / UJ)));
         }
-    }
-    return key;
+    });
+}
+__device__ __forceinline__ uint64_t wave_sort64(uint64_t key) {
+    uint64_t k[1] = {key};
+    wave_sort_regs<1>(k);
+    return k[0];
 }
 
 __device__ __forceinline__ uint64_t wave_readlane_u64(uint64_t v, int lane) {
     uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane);
     uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
     return ((uint64_t)hi << 32) | lo;
+}
+
+__device__ __forceinline__ uint32_t wave_readlane_any(uint32_t v, int lane) {
+    return __builtin_amdgcn_readlane(v, lane);
+}
+__device__ __forceinline__ uint64_t wave_readlane_any(uint64_t v, int lane) { return wave_readlane_u64(v, lane); }
+// Key p (the same in every lane) of a sorted run of 64 J keys across a wave.
+template <int J, class K>
+__device__ __forceinline__ K wave_key(const K (&k)[J], uint32_t p) {
+    K v = wave_readlane_any(k[0], (int)(p / J));
+#pragma unroll
+    for (int j = 1; j < J; ++j) {
+        const K o = wave_readlane_any(k[j], (int)(p / J));
+        v = p % J == (uint32_t)j ? o : v;
+    }
+    return v;
 }
 
 // Ascending bitonic sort of NT * J keys of buf (J = 1, 2, 4 or 8), with the keys
@@ -166,56 +260,69 @@ __device__ __forceinline__ uint64_t wave_readlane_u64(uint64_t v, int lane) {
 // The keys come from load(i) for i in [0, NT * J); buf is the exchange area and
 // receives the sorted keys.  With SYNC the threads wait for each other after
 // loading (needed when load reads LDS that other threads overwrite).
-template <int NT, int J, bool SYNC, class Load>
-__device__ __forceinline__ void block_sort_regs_from(uint64_t *buf, Load load) {
-    constexpr uint32_t N = (uint32_t)NT * J;
-    const uint32_t t = threadIdx.x;
-    uint64_t k[J];
+//
+// The direction of a step depends on bits of t: below 64 lanes it is a constant
+// lane mask, above it is the same for a whole wave.
+template <int NT, int J, bool SYNC, class K, class Load>
+__device__ __forceinline__ void block_sort_any(K *buf, Load load) {
+    constexpr uint32_t N = (uint32_t)NT * J, UJ = J, W = kWave;
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // (opaque: nothing below is formed ahead of a caller's loop and kept)
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    K k[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) k[j] = load(t * J + j);
     if (SYNC) __syncthreads();
-    auto cas = [](uint64_t &lo, uint64_t &hi, bool up) {
-        const uint64_t a = lo, b = hi;
-        const bool swap = (a > b) == up;
-        lo = swap ? b : a;
-        hi = swap ? a : b;
-    };
+    static_for(std::make_integer_sequence<int, bitonic_steps(N)>{}, [&](auto i) {
+        constexpr uint32_t size = bitonic_at(decltype(i)::value, true), stride = bitonic_at(decltype(i)::value, false);
+        // ascending lanes of this size: all (the last), by a lane's bit (D), or
+        // by the wave's (dyn)
+        constexpr uint32_t sb = size / UJ;
+        constexpr uint64_t D = size == N ? ~0ull : (size >= UJ && sb < W ? lanes_clear(sb > 0 ? sb : 1) : 0ull);
+        uint64_t dyn = 0;
+        if constexpr (size < N && sb >= W) dyn = (wave & (sb / W)) ? 0ull : ~0ull;
+        if constexpr (stride < UJ) {
 #pragma unroll
-    for (uint32_t size = 2; size <= N; size <<= 1) {
-#pragma unroll
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride < (uint32_t)J) {
-#pragma unroll
-                for (int j = 0; j < J; ++j)
-                    if ((j & stride) == 0) cas(k[j], k[j + stride], ((t * J + j) & size) == 0);
-            } else {
-                // partners in other threads: the direction is the same for all J
-                // keys of a thread (stride and size are multiples of J), and a
-                // key stays where it is exactly when it is already on the side
-                // its direction asks for (one compare and one select per key)
-                const uint32_t i0 = t * J;
-                const bool take_min = ((i0 & stride) == 0) == ((i0 & size) == 0);
-                uint64_t o[J];
-                if (stride < (uint32_t)J * kWave) {
-                    const int ls = (int)(stride / J);
-#pragma unroll
-                    for (int j = 0; j < J; ++j) o[j] = shfl_xor_u64(k[j], ls);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < J; ++j) buf[i0 + j] = k[j];
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < J; ++j) o[j] = buf[(i0 + j) ^ stride];
-                    __syncthreads();
+            for (int j = 0; j < J; ++j)
+                if ((j & stride) == 0) {
+                    const K a = k[j], b = k[j + stride];
+                    bool swap;
+                    if constexpr (size < UJ) swap = (a > b) == ((j & size) == 0);
+                    else swap = mine(flip<~D>(__ballot(a > b)) ^ dyn);
+                    k[j] = swap ? b : a;
+                    k[j + stride] = swap ? a : b;
                 }
+        } else {
+            // partners in other threads: the direction is the same for all J keys
+            // of a thread (stride and size are multiples of J)
+            constexpr uint32_t ls = stride / UJ;
+            K o[J];
+            if constexpr (ls < W) {
 #pragma unroll
-                for (int j = 0; j < J; ++j) k[j] = ((k[j] < o[j]) == take_min) ? k[j] : o[j];
+                for (int j = 0; j < J; ++j) o[j] = shfl_xor_any(k[j], (int)ls);
+#pragma unroll
+                for (int j = 0; j < J; ++j) k[j] = lane_step<lanes_clear(ls) ^ D>(k[j], o[j], dyn);
+            } else {
+                const uint32_t i0 = t * J;
+#pragma unroll
+                for (int j = 0; j < J; ++j) buf[i0 + j] = k[j];
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < J; ++j) o[j] = buf[(i0 + j) ^ stride];
+                __syncthreads();
+                dyn ^= (wave & (ls / W)) ? 0ull : ~0ull;
+#pragma unroll
+                for (int j = 0; j < J; ++j) k[j] = lane_step<D>(k[j], o[j], dyn);
             }
         }
-    }
+    });
 #pragma unroll
     for (int j = 0; j < J; ++j) buf[t * J + j] = k[j];
     __syncthreads();
+}
+template <int NT, int J, bool SYNC, class Load>
+__device__ __forceinline__ void block_sort_regs_from(uint64_t *buf, Load load) {
+    block_sort_any<NT, J, SYNC, uint64_t>(buf, load);
 }
 
 // In place: every thread loads exactly the positions it later writes.

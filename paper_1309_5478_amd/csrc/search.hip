@@ -410,7 +410,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         ka.out_val = b.sv;
         ka.out_idx = b.si;
         ka.mode = smode;
-        KNN_TRY(launch_select_keys(ka, b.selws, mb, num_cu, stream));
+        KNN_TRY(launch_select_keys(ka, num_cu, stream));
         knn_status_t fs = finish(b.sv, b.si, i0, mb, nullptr, 0);
         if (fs != KNN_SUCCESS) return fs;
     }

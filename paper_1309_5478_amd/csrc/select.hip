@@ -33,6 +33,7 @@
 // makes progress and equal values resolve to the lower index.  The on-chip
 // buffers hold CAP keys each; positions beyond them live in a per-workgroup
 // global workspace, so overflowing rows stay exact.
+#include "dist.hpp"
 #include "internal.hpp"
 #include "keys.hpp"
 #include "pivot_net.hpp"
@@ -45,7 +46,7 @@ constexpr int kSortN = 1024;        // sample size; also the largest k
 constexpr int kSampleBlocks = kSortN / kWave;
 constexpr int kStackDepth = 64;
 constexpr int kMaxPasses = 4096;    // hard bound; unreachable with distinct keys
-constexpr int kAccSlots = 10;       // per-workgroup statistics totals
+constexpr int kAccSlots = kSelSlot;  // per-workgroup statistics totals
 
 template <int CAP>
 struct SelSmem {
@@ -364,11 +365,10 @@ __device__ __forceinline__ uint64_t lowest64_of_blocks(SelSmem<CAP> &sm) {
             const uint32_t a0 = 2 * q * w * kWave, b0 = a0 + w * kWave;
             const uint64_t x = sm.sortbuf[a0 + lane], y = sm.sortbuf[b0 + (kWave - 1 - lane)];
             m = x < y ? x : y;
-#pragma unroll
-            for (int st = 32; st > 0; st >>= 1) {
-                const uint64_t o = shfl_xor_u64(m, st);
-                m = ((m < o) == ((lane & st) == 0)) ? m : o;
-            }
+            static_for(std::make_integer_sequence<int, 6>{}, [&](auto i) {
+                constexpr int st = 32 >> decltype(i)::value;
+                m = lane_step<~lanes_clear(st)>(m, shfl_xor_u64(m, st));
+            });
             if (2 * w < (uint32_t)kSampleBlocks) sm.sortbuf[a0 + lane] = m;
         }
         __syncthreads();
@@ -424,8 +424,8 @@ __device__ __forceinline__ bool direct_sort_fits(uint32_t nstack, uint32_t ss, u
 // per-row register reloads and for the longer rows that overflow to the
 // workspace.  The larger instances serve rows that fit them whole, as many per
 // CU as their LDS allows.
-template <int CAP, bool KEYS>
-__global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (CAP == 2048 ? 3 : 2))) void select_rows_kernel(
+template <int CAP>
+__global__ __launch_bounds__(kSelThreads, CAP == kSelectCap ? 5 : (CAP == 2048 ? 3 : 2)) void select_rows_kernel(
     SelectArgs a, uint64_t *ws, uint64_t ws_slot) {
     __shared__ SelSmem<CAP> sm;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
@@ -440,13 +440,11 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
     for (int64_t r = blockIdx.x; r < a.rows;) {
         // this row's matrix: the launch's own, or one segment of several
         const float *dist = a.dist;
-        const uint64_t *keys = a.keys;
-        const uint32_t *key_cnt = a.key_cnt;
         int64_t ld = a.ld, lr = r, orow = r;
         uint32_t N = a.cols, k = a.k, kout = a.k, col_off = 0;
         float *out_val = a.out_val;
         int32_t *out_idx = a.out_idx;
-        if (!KEYS && a.split > 1) {
+        if (a.split > 1) {
             // part p of matrix row r / split
             lr = r / a.split;
             col_off = (uint32_t)(r - lr * a.split) * a.cols;
@@ -457,8 +455,6 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
         if (a.segs) {
             const SelectSeg sg = uniform_load(a.segs + __builtin_amdgcn_readfirstlane(a.row_seg[r]));
             dist = sg.dist;
-            keys = sg.keys;
-            key_cnt = sg.key_cnt;
             ld = sg.ld;
             lr = r - sg.row0;
             orow = lr;
@@ -475,18 +471,7 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
         long long cyc_sample = 0, cyc_stream = 0;
         uint32_t sb, ss, se, Kp;  // active segment (buffer, start, end) and keys still needed
 
-        if (KEYS) {
-            // key-list row (at most CAP keys); a list shorter than k (a row
-            // whose candidates are re-done later) is padded with the largest
-            // key up to k, so that it is exactly the answer
-            const uint32_t c = key_cnt ? key_cnt[lr] : N;
-            const uint32_t n = c < N ? c : N;
-            const uint32_t len = n < k ? k : n;
-            const uint64_t *src = keys + lr * ld;
-            for (uint32_t p = tid; p < len; p += kSelThreads) sm.buf[0][p] = p < n ? src[p] : kKeyMax;
-            __syncthreads();
-            sb = 0; ss = 0; se = len; Kp = k;
-        } else if (N <= (uint32_t)CAP) {
+        if (N <= (uint32_t)CAP) {
             for (uint32_t p = tid; p < N; p += kSelThreads) sm.buf[0][p] = make_key(row[p], p);
             __syncthreads();
             sb = 0; ss = 0; se = N; Kp = k;
@@ -640,7 +625,7 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
             }
             if (passes >= (uint32_t)kMaxPasses) {
                 // unreachable (each pass shrinks the segment); reported, never hangs
-                if (tid == 0 && a.stats) atomicAdd(&a.stats[kStatErrors], 1ull);
+                if (tid == 0) sm.acc[kSlotErrors] += 1;
                 nfinal = 0;
                 break;
             }
@@ -704,7 +689,7 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
                 idx = 0xFFFFFFFFu;
             } else if (o == kOrdZero || o == kOrdNaN) {
                 // the key holds the class, the input its bits
-                v = !KEYS ? row[idx] : (a.src ? a.src[lr * a.src_ld + idx] : ord_to_float(o));
+                v = row[idx];
             } else {
                 v = ord_to_float(o);
             }
@@ -712,7 +697,7 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
             if (out_idx) out_idx[o_at] = (int32_t)(idx + col_off);
         };
         // a part shorter than k: its missing slots hold the largest key
-        if (!KEYS && a.out_keys)
+        if (a.out_keys)
             for (uint32_t t = k + tid; t < kout; t += kSelThreads) a.out_keys[orow * (int64_t)kout + t] = kKeyMax;
         if (direct) {
             // no kept segments: the active segment [0, se) of buffer sb (its
@@ -748,8 +733,7 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
             for (uint32_t t = tid; t < k; t += kSelThreads) emit(t, sm.sortbuf[t]);
         }
         long long t4 = clock64();
-        // per-workgroup totals, published once after the last row (all rows'
-        // counters share one cache line: per-row atomics would serialise there)
+        // per-workgroup totals, published once after the last row
         if (tid == 0) {
             sm.acc[0] += 1;
             sm.acc[1] += passes;
@@ -766,18 +750,7 @@ __global__ __launch_bounds__(kSelThreads, KEYS ? 1 : (CAP == kSelectCap ? 5 : (C
         __syncthreads();
         r = sm.next_row;
     }
-    if (tid == 0 && a.stats && sm.acc[0]) {
-        atomicAdd(&a.stats[kStatRows], sm.acc[0]);
-        atomicAdd(&a.stats[kStatPasses], sm.acc[1]);
-        atomicMax(&a.stats[kStatPassesMax], sm.acc[2]);
-        atomicAdd(&a.stats[kStatStreamPasses], sm.acc[3]);
-        atomicAdd(&a.stats[kStatSpillRows], sm.acc[4]);
-        atomicAdd(&a.stats[kStatFirstSurvivors], sm.acc[5]);
-        atomicAdd(&a.stats[kStatCycSample], sm.acc[6]);
-        atomicAdd(&a.stats[kStatCycStream], sm.acc[7]);
-        atomicAdd(&a.stats[kStatCycSelect], sm.acc[8]);
-        atomicAdd(&a.stats[kStatCycFinal], sm.acc[9]);
-    }
+    if (a.slots && tid < kAccSlots) a.slots[(size_t)blockIdx.x * kSelSlot + tid] = sm.acc[tid];
 }
 
 // ---- one partition pass per row, one wave per row (Figures 1-3) -------------
@@ -855,12 +828,16 @@ static int blocks_per_cu() {
     static int cached = 0;  // the library targets one architecture, so one value per kernel
     if (cached == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, select_rows_kernel<CAP, false>, kSelThreads, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, select_rows_kernel<CAP>, kSelThreads, 0) != hipSuccess ||
             n < 1)
             n = 1;
         cached = n;
     }
     return cached;
+}
+
+int select_launch_grid(const SelectArgs &a, int grid, int num_cu) {
+    return !a.segs && select_short_applies(a) ? select_short_grid(a, num_cu) : grid;
 }
 
 int select_grid(int cap, int64_t rows, int num_cu) {
@@ -880,6 +857,8 @@ size_t select_ws_bytes(int cap, uint32_t cols, int grid) {
 }
 
 hipError_t launch_select(const SelectArgs &args, int cap, int grid, void *ws, hipStream_t stream) {
+    // rows that fit the registers, where the pivot is the library's choice
+    if (!args.segs && select_short_applies(args)) return launch_select_short(args, device_cus(), stream);
     if (!ws) return hipErrorInvalidValue;
     uint64_t slot = args.cols > (uint32_t)cap ? (uint64_t)args.cols - cap : 0;
     SelectArgs a = args;
@@ -896,67 +875,53 @@ hipError_t launch_select(const SelectArgs &args, int cap, int grid, void *ws, hi
     }
     switch (cap) {
         case kSelectCap:
-            hipLaunchKernelGGL((select_rows_kernel<kSelectCap, false>), dim3(grid), dim3(kSelThreads), 0, stream, a, w,
+            hipLaunchKernelGGL((select_rows_kernel<kSelectCap>), dim3(grid), dim3(kSelThreads), 0, stream, a, w,
                                slot);
             break;
-        case 2048: hipLaunchKernelGGL((select_rows_kernel<2048, false>), dim3(grid), dim3(kSelThreads), 0, stream, a, w, slot); break;
-        case 4096: hipLaunchKernelGGL((select_rows_kernel<4096, false>), dim3(grid), dim3(kSelThreads), 0, stream, a, w, slot); break;
+        case 2048: hipLaunchKernelGGL((select_rows_kernel<2048>), dim3(grid), dim3(kSelThreads), 0, stream, a, w, slot); break;
+        case 4096: hipLaunchKernelGGL((select_rows_kernel<4096>), dim3(grid), dim3(kSelThreads), 0, stream, a, w, slot); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_select_keys(const SelectArgs &args, void *counter, int64_t rows_grid_limit, int num_cu,
-                              hipStream_t stream) {
-    if (args.cols > (uint32_t)kSelectKeysCap || args.k > (uint32_t)kSelectMaxK) return hipErrorInvalidValue;
-    SelectArgs a = args;
-    a.next_row = static_cast<unsigned long long *>(counter);
-    if (a.next_row) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, stream, a.next_row, 1);
-    static int per = 0;
-    if (per == 0) {
-        int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, select_rows_kernel<kSelectKeysCap, true>, kSelThreads, 0) !=
-                hipSuccess ||
-            n < 1)
-            n = 1;
-        per = n;
-    }
-    int64_t g = (int64_t)per * num_cu;
-    if (g > a.rows) g = a.rows;
-    if (g > rows_grid_limit) g = rows_grid_limit;
-    if (g < 1) g = 1;
-    hipLaunchKernelGGL((select_rows_kernel<kSelectKeysCap, true>), dim3((unsigned)g), dim3(kSelThreads), 0, stream, a,
-                       (uint64_t *)nullptr, (uint64_t)0);
-    return hipGetLastError();
-}
-
 // ---- rows split across workgroups -------------------------------------------
 // A part is worth its own workgroup once it is long against the work that does
-// not scale with its length (the pivot sample, the final sort of about k keys
-// and the merge of its k keys).  Smallest part: 32 k columns (a part's k keys stay a small fraction of it) and
-// at least 64 Ki columns when the split is chosen here: every part pays a fixed
-// cost (sample, sort, its list in the merge) that 16 KiB parts do not amortise
-// (8 rows of 2^20, k = 32: 181 us with 4 Ki-column parts, 56 us with 64 Ki).
-// A forced split goes down to 4 Ki columns.
+// not scale with its length.  Parts held in registers (select_short.hip) cost
+// little beyond their one read: rows are cut into parts of at most 16384 columns,
+// and of 8192 or 4096 while that leaves CUs without a part and the lists still
+// merge in one level (8 rows of 2^20, k = 32: 55 us with 64 Ki-column parts of
+// the streamed kernel, 19 us with 16 Ki).  For k beyond that kernel's, or a
+// named pivot rule, a part pays for its pivot sample, its final sort and its
+// list in the merge: at least 32 k and 65536 columns then (181 us with 4 Ki,
+// 54 us with 64 Ki).  A forced split goes down to 4 Ki columns.
 static uint64_t split_min_chunk(uint32_t k, bool force) {
     const uint64_t floor = force ? 4096ull : 65536ull;
     return k * 32ull > floor ? k * 32ull : floor;
 }
 
-SplitPlan select_split_plan(int64_t rows, uint32_t cols, uint32_t k, int num_cu, bool force) {
+SplitPlan select_split_plan(int64_t rows, uint32_t cols, uint32_t k, int num_cu, bool force, bool sample) {
     SplitPlan sp{1, 1, cols, 0};
     const int64_t resident = (int64_t)blocks_per_cu<kSelectCap>() * num_cu;
     // enough rows to keep every resident workgroup busy: nothing to gain
     if (rows < 1 || (!force && rows * 2 > resident)) return sp;
     uint32_t group = 2;
     while (2ull * group * k <= (uint64_t)kSelectKeysCap) group *= 2;
-    const uint64_t min_chunk = split_min_chunk(k, force);
-    // parts for half the resident workgroups: fewer, longer parts measured
-    // faster than filling every slot (their streams are latency-bound, and each
-    // part's fixed cost grows the merge)
-    const int64_t want = force ? INT64_MAX : resident / 2;
     uint32_t parts = 1;
-    while (parts < 4096u && rows * (int64_t)parts < want && (uint64_t)cols >= 2ull * parts * min_chunk) parts *= 2;
+    const bool in_registers = !force && sample && k <= kShortMaxK && cols > kShortMaxCols;  // (chunks of 4 Ki and up)
+    if (in_registers) {
+        while (parts < (1u << 20) && ((uint64_t)cols + parts - 1) / parts > kShortMaxCols) parts *= 2;
+        while (rows * (int64_t)parts < num_cu && 2 * parts <= group && cols / parts >= 8192u &&
+               cols / parts >= 32ull * k)
+            parts *= 2;
+    } else {
+        const uint64_t min_chunk = split_min_chunk(k, force);
+        // parts for half the resident workgroups: fewer, longer parts measured
+        // faster than filling every slot (their streams are latency-bound, and each
+        // part's fixed cost grows the merge)
+        const int64_t want = force ? INT64_MAX : resident / 2;
+        while (parts < 4096u && rows * (int64_t)parts < want && (uint64_t)cols >= 2ull * parts * min_chunk) parts *= 2;
+    }
     for (; parts > 1; parts /= 2) {
         // every part keeps at least one column (the last one may be short)
         const uint64_t chunk = (((uint64_t)cols + parts - 1) / parts + 3) / 4 * 4;
@@ -968,13 +933,14 @@ SplitPlan select_split_plan(int64_t rows, uint32_t cols, uint32_t k, int num_cu,
     if (parts < 2) return sp;
     sp.parts = parts;
     sp.group = group;
-    sp.grid = select_grid(kSelectCap, rows * parts, num_cu);
+    // (parts in registers need no overflow buffers)
+    sp.grid = in_registers ? 0 : select_grid(kSelectCap, rows * parts, num_cu);
     return sp;
 }
 
 // Workspace of a split call: the part selection's (header with its row counter,
-// overflow buffers), a 256-byte block with the merges' row counter, then two
-// key arrays: the parts' lists and the first merge level's.
+// overflow buffers), then two key arrays: the parts' lists and the first merge
+// level's.
 static size_t split_keys_a(const SplitPlan &sp, int64_t rows, uint32_t k) { return (size_t)rows * sp.parts * k; }
 static size_t split_keys_b(const SplitPlan &sp, int64_t rows, uint32_t k) {
     const uint32_t g = sp.group < sp.parts ? sp.group : sp.parts;
@@ -983,7 +949,24 @@ static size_t split_keys_b(const SplitPlan &sp, int64_t rows, uint32_t k) {
 
 size_t select_split_ws_bytes(const SplitPlan &sp, int64_t rows, uint32_t k) {
     const size_t sel = (select_ws_bytes(kSelectCap, sp.chunk, sp.grid) + 255) / 256 * 256;
-    return sel + 256 + (split_keys_a(sp, rows, k) + split_keys_b(sp, rows, k)) * sizeof(uint64_t);
+    return sel + (split_keys_a(sp, rows, k) + split_keys_b(sp, rows, k)) * sizeof(uint64_t);
+}
+
+// The part selection's arguments (every part's k smallest keys go to `keys`).
+static SelectArgs part_args(const SelectArgs &a, const SplitPlan &sp, uint64_t *keys) {
+    SelectArgs pa = a;
+    pa.rows = a.rows * sp.parts;
+    pa.cols = sp.chunk;
+    pa.row_cols = a.cols;
+    pa.split = sp.parts;
+    pa.out_keys = keys;
+    pa.out_val = nullptr;
+    pa.out_idx = nullptr;
+    return pa;
+}
+
+int select_split_grid(const SelectArgs &a, const SplitPlan &sp, int num_cu) {
+    return select_launch_grid(part_args(a, sp, nullptr), sp.grid, num_cu);
 }
 
 hipError_t launch_select_split(const SelectArgs &a, const SplitPlan &sp, void *ws, int num_cu, hipStream_t stream) {
@@ -991,19 +974,10 @@ hipError_t launch_select_split(const SelectArgs &a, const SplitPlan &sp, void *w
         return hipErrorInvalidValue;
     char *w = static_cast<char *>(ws);
     const size_t sel = (select_ws_bytes(kSelectCap, sp.chunk, sp.grid) + 255) / 256 * 256;
-    void *counter = w + sel;
-    uint64_t *ka = reinterpret_cast<uint64_t *>(w + sel + 256);
+    uint64_t *ka = reinterpret_cast<uint64_t *>(w + sel);
     uint64_t *kb = ka + split_keys_a(sp, a.rows, a.k);
     // 1. every part's k smallest keys, global column indices
-    SelectArgs pa = a;
-    pa.rows = a.rows * sp.parts;
-    pa.cols = sp.chunk;
-    pa.row_cols = a.cols;
-    pa.split = sp.parts;
-    pa.out_keys = ka;
-    pa.out_val = nullptr;
-    pa.out_idx = nullptr;
-    hipError_t e = launch_select(pa, kSelectCap, sp.grid, ws, stream);
+    hipError_t e = launch_select(part_args(a, sp, ka), kSelectCap, sp.grid, ws, stream);
     if (e != hipSuccess) return e;
     // 2. merge levels: `group` lists of k keys per merged row
     uint64_t *in = ka, *out = kb;
@@ -1024,7 +998,7 @@ hipError_t launch_select_split(const SelectArgs &a, const SplitPlan &sp, void *w
         } else {
             m.out_keys = out;
         }
-        if ((e = launch_select_keys(m, counter, m.rows, num_cu, stream)) != hipSuccess) return e;
+        if ((e = launch_select_keys(m, num_cu, stream)) != hipSuccess) return e;
         uint64_t *t = in;
         in = out;
         out = t;
