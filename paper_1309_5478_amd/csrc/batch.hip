@@ -76,8 +76,9 @@ struct BatchPart {
     int job;
     int64_t i0, mb;
     bool direct;    // the threshold sample is the whole corpus: its selection is the candidate list
-    bool grouped;   // FILTER product in the grouped launch (else its own: FP32 with d % 4 != 0)
-    bool sgrouped;  // sample product in the grouped launch (same condition)
+    bool pipe;      // both products on two-half operands, in the grouped pipelined launches
+    bool grouped;   // else FILTER product in the grouped launch (or its own: FP32 with d % 4 != 0)
+    bool sgrouped;  // and sample product in the grouped launch (same condition)
     float *Ds = nullptr;   // mb x S sample distances
     float *tv = nullptr;   // mb x (r + 1) selected sample keys (values, indices)
     int32_t *ti = nullptr;
@@ -111,7 +112,9 @@ struct BatchShared {
     uint32_t *cnt_all = nullptr;  // the candidate counts of all parts, contiguous
     int64_t cnt_rows = 0;
     DistArgs *table = nullptr, *probe = nullptr, *stable = nullptr;
-    GemmItem *items = nullptr, *sitems = nullptr;
+    GemmItem *items = nullptr, *sitems = nullptr;    // 128 x 128 .. tiles of gemm.hip
+    GemmItem *pitems = nullptr, *psitems = nullptr;  // tiles of the pipelined product
+    unsigned int *cmax2 = nullptr;                   // per job, the largest squared corpus norm
     uint32_t *nflag = nullptr;
     uint32_t *nu = nullptr;  // uncertified-row counts, one per part
     uint32_t *queues = nullptr;  // the eight per-XCD item queues of the persistent product
@@ -134,7 +137,7 @@ struct BatchState {
     BatchShared sh;
     int tile = kTileWide;
     bool queue = false;  // the product as a resident grid over per-XCD item queues
-    size_t nitems = 0, nsitems = 0;
+    size_t nitems = 0, nsitems = 0, npitems = 0, npsitems = 0;
     std::vector<SegLaunch> sample_sel;  // threshold selections, one launch per capacity class
     SegLaunch keys_sel;                 // candidate selections
     int smode = kPivotSample;
@@ -170,16 +173,18 @@ namespace {
 // Autotune candidates: a tile shape, plus this for the queue form.
 constexpr int kQueueChoice = 16;
 
+constexpr int kPipeForm = -2;  // tile argument: the pipelined product's tiles and parts
+
 void build_items(const BatchState &b, int tile, std::vector<GemmItem> &items) {
     constexpr int kQueues = 8;
-    int bm, bn;
-    gemm_tile_dims(tile, &bm, &bn);
+    int bm = kPipeTileDim, bn = kPipeTileDim;
+    if (tile != kPipeForm) gemm_tile_dims(tile, &bm, &bn);
     std::vector<std::vector<GemmItem>> q(kQueues);
     for (int j : b.order) {
         const BatchJob &js = b.jobs[j];
         for (int pi = js.first_part; pi < js.first_part + js.nparts; ++pi) {
             const BatchPart &pt = b.parts[pi];
-            if (!pt.grouped) continue;
+            if (tile == kPipeForm ? !pt.pipe : !pt.grouped) continue;
             const uint32_t tm_n = (uint32_t)((pt.mb + bm - 1) / bm);
             const uint32_t tn_n = (uint32_t)((js.n + bn - 1) / bn);
             for (int qi = 0; qi < kQueues; ++qi) {
@@ -217,13 +222,15 @@ size_t max_items(const BatchState &b) {
     return n;
 }
 
-// Items of the grouped sample products (128 x 128 tiles), part after part.
-void build_sample_items(const BatchState &b, std::vector<GemmItem> &items) {
+// Items of the grouped sample products (128 x 128 tiles, or the pipelined
+// product's), part after part.
+void build_sample_items(const BatchState &b, bool pipe, std::vector<GemmItem> &items) {
     items.clear();
+    const int t = pipe ? kPipeTileDim : 128;
     for (size_t pi = 0; pi < b.parts.size(); ++pi) {
         const BatchPart &pt = b.parts[pi];
-        if (!pt.sgrouped) continue;
-        const uint32_t tm_n = (uint32_t)((pt.mb + 127) / 128), tn_n = (uint32_t)((b.jobs[pt.job].p.S + 127) / 128);
+        if (pipe ? !pt.pipe : !pt.sgrouped) continue;
+        const uint32_t tm_n = (uint32_t)((pt.mb + t - 1) / t), tn_n = (uint32_t)((b.jobs[pt.job].p.S + t - 1) / t);
         for (uint32_t tm = 0; tm < tm_n; ++tm)
             for (uint32_t tn = 0; tn < tn_n; ++tn) items.push_back(GemmItem{(uint32_t)pi, tm, tn});
     }
@@ -293,13 +300,14 @@ void plan_selects(BatchState &b) {
 // each phase can run as one launch over all parts.
 size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
     BatchShared &s = b.sh;
+    s.cmax2 = c.take<unsigned int>(b.jobs.size());
+    for (size_t j = 0; j < b.jobs.size(); ++j) b.jobs[j].cmax2 = s.cmax2 ? s.cmax2 + j : nullptr;
     size_t qf = 0, df = 0, fv = 0, qfq = 0, fb = 0, selws = 0;
     for (BatchJob &js : b.jobs) {
         const Plan &p = js.p;
         js.cnorm = c.take<float>(js.n);
-        js.qn2 = c.take<float>(js.m);
-        js.cmax2 = c.take<unsigned int>(1);
-        if (p.prec != kPrecF32) {
+        js.qn2 = js.graph ? js.cnorm : c.take<float>(js.m);  // (a graph's queries are its corpus)
+        if (p.prec != kPrecF32 || p.split) {
             js.Cq = c.take<char>((size_t)js.n * p.ldq);
             js.cs = c.take<float>(js.n);
             if (!js.graph) {
@@ -317,7 +325,7 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
         if (p.gathered && js.nparts) {
             js.Cs = c.take<float>((size_t)p.S * p.d);
             js.csn = c.take<float>(p.S);
-            if (p.prec != kPrecF32) {
+            if (p.prec != kPrecF32 || p.split) {
                 js.Csq = c.take<char>((size_t)p.S * p.ldq);
                 js.css = c.take<float>(p.S);
             }
@@ -325,7 +333,7 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
         qf = std::max(qf, (size_t)p.Fb * p.d);
         df = std::max(df, (size_t)p.Fb * js.n);
         fv = std::max(fv, (size_t)p.Fb * p.kk);
-        qfq = std::max(qfq, (size_t)p.Fb * p.ldq);
+        if (!p.split) qfq = std::max(qfq, (size_t)p.Fb * p.ldq);
         fb = std::max(fb, (size_t)p.Fb);
         const int cap2 = select_cap_for_k(p.kk);
         selws = std::max(selws, select_ws_bytes(cap2, (uint32_t)js.n, select_grid(cap2, p.Fb, num_cu)));
@@ -375,9 +383,18 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
     s.probe = probe ? c.take<DistArgs>(b.parts.size()) : nullptr;
     s.items = c.take<GemmItem>(std::max<size_t>(max_items(b), 1));
     std::vector<GemmItem> si;
-    build_sample_items(b, si);
+    build_sample_items(b, false, si);
     s.sitems = c.take<GemmItem>(std::max<size_t>(si.size(), 1));
     b.nsitems = si.size();
+    build_sample_items(b, true, si);
+    s.psitems = c.take<GemmItem>(std::max<size_t>(si.size(), 1));
+    b.npsitems = si.size();
+    b.npitems = 0;
+    for (const BatchPart &pt : b.parts)
+        if (pt.pipe)
+            b.npitems += (size_t)((pt.mb + kPipeTileDim - 1) / kPipeTileDim) *
+                         (size_t)((b.jobs[pt.job].n + kPipeTileDim - 1) / kPipeTileDim);
+    s.pitems = c.take<GemmItem>(std::max<size_t>(b.npitems, 1));
     s.nflag = c.take<uint32_t>(b.parts.size());
     s.nu = c.take<uint32_t>(b.parts.size());
     s.queues = c.take<uint32_t>(8);
@@ -400,7 +417,7 @@ DistArgs part_args(const BatchState &b, const BatchPart &pt) {
     a.cnt = pt.cnt;
     a.cand = pt.cand;
     a.cap = p.cap;
-    a.prec = p.prec;
+    a.prec = p.split ? kPrecSplit : p.prec;
     a.Qq = js.Qq ? static_cast<const char *>(js.Qq) + pt.i0 * p.ldq : nullptr;
     a.Cq = js.Cq;
     a.ldq = p.ldq;
@@ -475,14 +492,19 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
         if ((e = (call)) != hipSuccess) return e;  \
     } while (0)
     BTRY(launch_fill_u32(sh.nu, (int64_t)b.parts.size(), 0u, s));
+    BTRY(launch_fill_u32(sh.cmax2, (int64_t)b.jobs.size(), 0u, s));
     // per job: norms, quantised copies, the gathered threshold sample
     for (int j : b.order) {
         const BatchJob &js = b.jobs[j];
         const Plan &p = js.p;
         if (js.nparts == 0) continue;
-        BTRY(launch_fill_u32(js.cmax2, 1, 0u, s));
-        BTRY(launch_sqnorm(js.C, js.n, js.d, js.cnorm, js.cmax2, s));
-        BTRY(launch_sqnorm(js.Q, js.m, js.d, js.qn2, nullptr, s));
+        if (p.split) {
+            BTRY(launch_split(js.C, js.n, js.d, js.Cq, js.cs, js.cnorm, js.cmax2, s));
+            if (!js.graph) BTRY(launch_split(js.Q, js.m, js.d, js.Qq, js.qs, js.qn2, nullptr, s));
+        } else {
+            BTRY(launch_sqnorm(js.C, js.n, js.d, js.cnorm, js.cmax2, s));
+            if (!js.graph) BTRY(launch_sqnorm(js.Q, js.m, js.d, js.qn2, nullptr, s));
+        }
         if (p.prec != kPrecF32) {
             BTRY(launch_quantize(js.C, js.n, js.d, p.prec, js.Cq, js.cs, s));
             if (!js.graph) BTRY(launch_quantize(js.Q, js.m, js.d, p.prec, js.Qq, js.qs, s));
@@ -493,13 +515,17 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
             if (p.prec != kPrecF32)
                 BTRY(launch_quantize(Cs, p.S, js.d, p.prec, const_cast<void *>(js.Csq), const_cast<float *>(js.css),
                                      s));
+            else if (p.split)
+                BTRY(launch_split(Cs, p.S, js.d, const_cast<void *>(js.Csq), const_cast<float *>(js.css), nullptr,
+                                  nullptr, s));
         }
     }
-    // all sample products in one launch (FP32 parts with d % 4 != 0 on their own)
+    // all sample products in one launch per form (FP32 parts with d % 4 != 0 on their own)
+    BTRY(launch_dist_gemm_pipe_grouped(sh.stable, sh.psitems, (int64_t)b.npsitems, kPrecSplit, s, kEpiDense));
     BTRY(launch_dist_gemm_grouped(sh.stable, sh.sitems, (int64_t)b.nsitems, b.jobs[0].p.prec, kTileSmall, s,
                                   kEpiDense));
     for (const BatchPart &pt : b.parts)
-        if (!pt.sgrouped) BTRY(launch_dist_gemm(sample_args(b, pt), kEpiDense, s));
+        if (!pt.sgrouped && !pt.pipe) BTRY(launch_dist_gemm(sample_args(b, pt), kEpiDense, s));
     // all threshold selections, one launch per capacity class
     for (const SegLaunch &L : b.sample_sel) {
         SelectArgs sa = seg_select_args(b, L);
@@ -516,13 +542,14 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
 hipError_t enqueue_product(const BatchState &b, const DistArgs *table, int tile, bool queue, int num_cu,
                            hipStream_t s) {
     hipError_t e = hipSuccess;
+    BTRY(launch_dist_gemm_pipe_grouped(table, b.sh.pitems, (int64_t)b.npitems, kPrecSplit, s));
     if (queue)
         BTRY(launch_dist_gemm_queue(table, b.sh.items, (int64_t)b.nitems, b.jobs[0].p.prec, tile, b.sh.queues, num_cu,
                                     s));
     else
         BTRY(launch_dist_gemm_grouped(table, b.sh.items, (int64_t)b.nitems, b.jobs[0].p.prec, tile, s));
     for (const BatchPart &pt : b.parts) {
-        if (pt.grouped || pt.direct) continue;
+        if (pt.grouped || pt.pipe || pt.direct) continue;
         DistArgs fa = part_args(b, pt);
         if (table == b.sh.probe) {
             fa.tau = b.sh.ninf;
@@ -798,6 +825,16 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         b.net = net;
         b.force = (o.flags & KNN_FLAG_FORCE_FALLBACK) ? 1 : 0;
         b.timed = timed;
+        const bool tune = autotune_enabled(&o);
+        // two-half operands (as large as the points themselves) for the longest
+        // jobs first, up to a third of the memory that is free: the rest is the
+        // workspace's and the program's
+        size_t split_left = 0;
+        if (!tune && !std::getenv("KNN_BATCH_QUEUE")) {
+            size_t free_bytes = 0, total_bytes = 0;
+            KTRY(hipMemGetInfo(&free_bytes, &total_bytes));
+            split_left = (free_bytes + b.ws_bytes) / 3;
+        }
         for (int32_t j = 0; j < njobs; ++j) {
             const knn_job_t &jb = jobs[j];
             BatchJob js{};
@@ -813,42 +850,68 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
             js.p = make_plan(jb.m > 0 ? jb.m : 1, jb.n, jb.d, jb.k, js.graph, &o, kRowBlock);
             js.cost = 2.0 * (double)jb.m * (double)jb.n * jb.d;
             js.oscale = o.metric != KNN_METRIC_SQEUCLIDEAN ? 0.5f : 1.0f;
-            js.first_part = (int)b.parts.size();
-            for (int64_t i0 = 0; i0 < jb.m; i0 += js.p.Mb) {
-                BatchPart pt{};
-                pt.job = j;
-                pt.i0 = i0;
-                pt.mb = jb.m - i0 < js.p.Mb ? jb.m - i0 : js.p.Mb;
-                pt.direct = !js.p.gathered;
-                pt.sgrouped = !(js.p.prec == kPrecF32 && js.d % 4 != 0);
-                pt.grouped = !pt.direct && pt.sgrouped;
-                b.parts.push_back(pt);
-            }
-            js.nparts = (int)b.parts.size() - js.first_part;
             b.jobs.push_back(js);
         }
         b.order.resize(b.jobs.size());
         for (size_t j = 0; j < b.jobs.size(); ++j) b.order[j] = (int)j;
         std::stable_sort(b.order.begin(), b.order.end(),
                          [&](int x, int y) { return b.jobs[x].cost > b.jobs[y].cost; });
+        std::vector<Plan> plain;  // the plans before split operands
+        for (const BatchJob &js : b.jobs) plain.push_back(js.p);
+        bool any_split = false;
+        auto plan_parts = [&]() {
+            b.parts.clear();
+            any_split = false;
+            for (int j : b.order) {
+                BatchJob &js = b.jobs[j];
+                js.p = plain[j];
+                if (js.m == 0 || !split_serves(js.p)) continue;
+                const size_t need = (size_t)(js.n + (js.graph ? 0 : js.m) + js.p.S) * (size_t)split_row_bytes(js.d);
+                if (need > split_left) continue;
+                split_left -= need;
+                use_split(js.p);
+                any_split = true;
+            }
+            for (int32_t j = 0; j < njobs; ++j) {
+                BatchJob &js = b.jobs[j];
+                js.first_part = (int)b.parts.size();
+                for (int64_t i0 = 0; i0 < js.m; i0 += js.p.Mb) {
+                    BatchPart pt{};
+                    pt.job = j;
+                    pt.i0 = i0;
+                    pt.mb = js.m - i0 < js.p.Mb ? js.m - i0 : js.p.Mb;
+                    pt.direct = !js.p.gathered;
+                    pt.pipe = js.p.split;
+                    pt.sgrouped = !pt.pipe && !(js.p.prec == kPrecF32 && js.d % 4 != 0);
+                    pt.grouped = !pt.direct && pt.sgrouped;
+                    b.parts.push_back(pt);
+                }
+                js.nparts = (int)b.parts.size() - js.first_part;
+            }
+        };
+        plan_parts();
         if (b.parts.empty()) return KNN_SUCCESS;
 
-        const bool tune = autotune_enabled(&o);
-        Carve sizing{nullptr};
-        const size_t bytes = carve_batch(sizing, b, num_cu, tune);
-        if (bytes > b.ws_bytes) {
+        for (;;) {
+            Carve sizing{nullptr};
+            const size_t bytes = carve_batch(sizing, b, num_cu, tune);
+            if (bytes <= b.ws_bytes) break;
             if (b.ws) {
                 hipFree(b.ws);
                 b.ws = nullptr;
                 b.ws_bytes = 0;
             }
-            if (hipMalloc(&b.ws, bytes) != hipSuccess) {
-                b.ws = nullptr;
-                (void)hipGetLastError();
+            if (hipMalloc(&b.ws, bytes) == hipSuccess) {
+                b.ws_bytes = bytes;
+                break;
+            }
+            b.ws = nullptr;
+            (void)hipGetLastError();
+            if (!any_split)
                 return fail_msg(h, KNN_ERROR_OUT_OF_MEMORY,
                                 "knn_batch_search: workspace of " + std::to_string(bytes) + " bytes");
-            }
-            b.ws_bytes = bytes;
+            split_left = 0;  // again without split operands
+            plan_parts();
         }
         Carve real{static_cast<char *>(b.ws)};
         carve_batch(real, b, num_cu, tune);
@@ -874,11 +937,17 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         for (size_t pi = 0; pi < b.parts.size(); ++pi) stable[pi] = sample_args(b, b.parts[pi]);
         KTRY(hipMemcpyAsync(b.sh.stable, stable.data(), stable.size() * sizeof(DistArgs), hipMemcpyHostToDevice,
                             stream));
-        std::vector<GemmItem> sitems;
-        build_sample_items(b, sitems);
-        if (!sitems.empty())
-            KTRY(hipMemcpyAsync(b.sh.sitems, sitems.data(), sitems.size() * sizeof(GemmItem), hipMemcpyHostToDevice,
-                                stream));
+        std::vector<GemmItem> sitems, psitems, pitems;
+        build_sample_items(b, false, sitems);
+        build_sample_items(b, true, psitems);
+        build_items(b, kPipeForm, pitems);
+        auto upload_items = [&](GemmItem *to, const std::vector<GemmItem> &v) -> hipError_t {
+            if (v.empty()) return hipSuccess;
+            return hipMemcpyAsync(to, v.data(), v.size() * sizeof(GemmItem), hipMemcpyHostToDevice, stream);
+        };
+        KTRY(upload_items(b.sh.sitems, sitems));
+        KTRY(upload_items(b.sh.psitems, psitems));
+        KTRY(upload_items(b.sh.pitems, pitems));
         std::vector<SegLaunch *> launches;
         for (SegLaunch &L : b.sample_sel) launches.push_back(&L);
         launches.push_back(&b.keys_sel);

@@ -105,6 +105,11 @@ hipError_t launch_dist_gemm_grouped(const DistArgs *jobs, const GemmItem *items,
 // device memory (cleared by the launch).
 hipError_t launch_dist_gemm_queue(const DistArgs *jobs, const GemmItem *items, int64_t nitems, int prec, int tile,
                                   uint32_t *queues, int num_cu, hipStream_t stream);
+// The pipelined product over a list of 256 x 256 tiles of many products (split
+// operands): as launch_dist_gemm_grouped, ldq at most 2^22 and no qnorm / row_ids.
+constexpr int kPipeTileDim = 256;
+hipError_t launch_dist_gemm_pipe_grouped(const DistArgs *jobs, const GemmItem *items, int64_t nitems, int prec,
+                                         hipStream_t stream, int epi = kEpiFilter);
 // The resident-corpus product for short BF16 / FP8 rows with the FILTER
 // epilogue (gemm_sk.hip): whether it serves `a` (KNN_GEMM_SK=0 turns it off),
 // and its launch.  launch_dist_gemm uses it where it applies.

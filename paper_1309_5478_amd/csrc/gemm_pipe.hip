@@ -62,8 +62,8 @@ constexpr int kPipeWM = 2, kPipeWN = 4;                // waves: rows x columns
 constexpr int kPipeBI = 4, kPipeBJ = 2;                // 32 x 32 blocks per wave
 constexpr int kPipeWaves = kPipeWM * kPipeWN;
 constexpr int kPipeThreads = 64 * kPipeWaves;
-constexpr int kPipeTile = 32 * kPipeBI * kPipeWM;      // 256 rows, 256 columns
-static_assert(kPipeTile == 32 * kPipeBJ * kPipeWN, "square tile");
+constexpr int kPipeTile = kPipeTileDim;               // rows and columns
+static_assert(kPipeTile == 32 * kPipeBI * kPipeWM && kPipeTile == 32 * kPipeBJ * kPipeWN, "256 x 256");
 constexpr int kPipeChunk = 128;                        // bytes of a row per stage
 constexpr int kPipeStage = 2 * kPipeTile * kPipeChunk;
 constexpr int kPipeLoads = 2 * kPipeTile / 8 / kPipeWaves;  // load instructions per wave and stage (8 rows each)
@@ -100,12 +100,22 @@ constexpr int chunk_elems() {
 
 }  // namespace
 
-// One product (a) per launch.  The tiles are cut into eight contiguous ranges,
-// one per XCD (workgroup b runs on XCD b % 8), each walked in groups of
-// kPipeGroup row tiles across the column tiles, so that the workgroups of an XCD
-// share operands in its L2.
-template <int PREC, int EPI>
-__global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs a) {
+// One tile: the product it belongs to (scalar registers) and its origin.
+struct PipeTile {
+    const DistArgs *a;
+    uint32_t row0, col0;
+};
+
+// The tiles of a workgroup.  One product (GROUPED false): its tiles are cut into
+// eight contiguous ranges, one per XCD (workgroup b runs on XCD b % 8), each
+// walked in groups of kPipeGroup row tiles across the column tiles, so that the
+// workgroups of an XCD share operands in its L2.  Many products (GROUPED): items
+// in dispatch order, workgroup b taking b, b + grid, .. (the grid is a multiple
+// of eight, so an item stays on the XCD the order gives it).
+template <int PREC, int EPI, bool GROUPED>
+__global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one, const DistArgs *__restrict__ jobs,
+                                                                    const GemmItem *__restrict__ items,
+                                                                    uint32_t nitems) {
     constexpr int BI = kPipeBI, BJ = kPipeBJ;
     constexpr bool SC = PREC != kPrecBF16;  // per-point scales
     __shared__ __align__(1024) unsigned char stage[2 * kPipeStage];
@@ -114,35 +124,45 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs a) 
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint32_t wm = wave % kPipeWM, wn = wave / kPipeWM, h = lane / 32, l32 = lane % 32;
 
-    const uint32_t T = a.tiles_m * a.tiles_n, per = (T + 7) / 8;
-    const uint32_t first = (blockIdx.x % 8) * per + blockIdx.x / 8, step = gridDim.x / 8;
-    const uint32_t end = (blockIdx.x % 8) * per + per < T ? (blockIdx.x % 8) * per + per : T;
+    uint32_t first, end, step;
+    if (GROUPED) {
+        first = blockIdx.x;
+        end = nitems;
+        step = gridDim.x;
+    } else {
+        const uint32_t T = one.tiles_m * one.tiles_n, per = (T + 7) / 8, x0 = (blockIdx.x % 8) * per;
+        first = x0 + blockIdx.x / 8;
+        end = x0 + per < T ? x0 + per : T;
+        step = gridDim.x / 8;
+    }
     if (first >= end) return;  // the whole workgroup leaves together
-    auto origin = [&](uint32_t t, uint32_t &row0, uint32_t &col0) {
-        const uint32_t group = t / (kPipeGroup * a.tiles_n), r0 = group * kPipeGroup;
-        const uint32_t gs = a.tiles_m - r0 < kPipeGroup ? a.tiles_m - r0 : kPipeGroup;
-        const uint32_t in = t - r0 * a.tiles_n;
-        row0 = (r0 + in % gs) * kPipeTile;
-        col0 = (in / gs) * kPipeTile;
+    auto tile_at = [&](uint32_t t) -> PipeTile {
+        if (GROUPED) {
+            const GemmItem w = items[t];
+            return PipeTile{jobs + w.job, w.tm * kPipeTile, w.tn * kPipeTile};
+        }
+        const uint32_t group = t / (kPipeGroup * one.tiles_n), r0 = group * kPipeGroup;
+        const uint32_t gs = one.tiles_m - r0 < kPipeGroup ? one.tiles_m - r0 : kPipeGroup;
+        const uint32_t in = t - r0 * one.tiles_n;
+        return PipeTile{&one, (r0 + in % gs) * kPipeTile, (in / gs) * kPipeTile};
     };
-    const int nk = (a.d + chunk_elems<PREC>() - 1) / chunk_elems<PREC>();
 
     // the load stream: instruction x of this wave fills rows 8 (wave kPipeLoads
     // + x) .. + 7 of the stage (256 query rows, then 256 corpus rows); rows
     // beyond the matrices read the last one (their results are never kept)
     uint32_t off[kPipeLoads];
     const unsigned char *Ab, *Bb;
-    auto load_tile = [&](uint32_t t) {
-        uint32_t row0, col0;
-        origin(t, row0, col0);
-        Ab = static_cast<const unsigned char *>(a.Qq) + (int64_t)row0 * a.ldq;
-        Bb = static_cast<const unsigned char *>(a.Cq) + (int64_t)col0 * a.ldq;
-        const uint32_t alim = (uint32_t)a.m - row0 - 1, blim = (uint32_t)a.n - col0 - 1;
+    auto load_tile = [&](const PipeTile &pt) {
+        const DistArgs &a = *pt.a;
+        const uint32_t ldq = (uint32_t)a.ldq;
+        Ab = static_cast<const unsigned char *>(a.Qq) + (int64_t)pt.row0 * ldq;
+        Bb = static_cast<const unsigned char *>(a.Cq) + (int64_t)pt.col0 * ldq;
+        const uint32_t alim = (uint32_t)a.m - pt.row0 - 1, blim = (uint32_t)a.n - pt.col0 - 1;
 #pragma unroll
         for (int x = 0; x < kPipeLoads; ++x) {
             const uint32_t r8 = (wave * kPipeLoads + x) * 8;
             const uint32_t r = (r8 < kPipeTile ? r8 : r8 - kPipeTile) + lane / 8, lim = r8 < kPipeTile ? alim : blim;
-            off[x] = (r < lim ? r : lim) * (uint32_t)a.ldq + ((lane % 8) ^ (((r8 + lane / 8) >> 1) & 7)) * 16;
+            off[x] = (r < lim ? r : lim) * ldq + ((lane % 8) ^ (((r8 + lane / 8) >> 1) & 7)) * 16;
         }
     };
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)stage;
@@ -215,13 +235,17 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs a) 
         }
     };
 
-    load_tile(first);
+    PipeTile next = tile_at(first);
+    load_tile(next);
     load_chunk(0, 0);
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     uint32_t buf = 0, par = 0;
     for (uint32_t t = first; t < end; t += step, par ^= 1) {
-        uint32_t row0, col0;
-        origin(t, row0, col0);
+        const uint32_t row0 = next.row0, col0 = next.col0;
+        const DistArgs &a = *next.a;
+        const int nk = (a.d + chunk_elems<PREC>() - 1) / chunk_elems<PREC>();
+        const bool more = t + step < end;
+        if (more) next = tile_at(t + step);
         // this tile's thresholds and scales are requested now, and stored to LDS
         // (the copy of this tile's parity: another wave may still be in the
         // previous tile's epilogue) ahead of its first barrier.  A NaN
@@ -248,8 +272,8 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs a) 
             // every wave has left the other buffer (the barrier below)
             if (kc + 1 < nk) {
                 load_chunk(kc + 1, buf ^ 1);
-            } else if (t + step < end) {
-                load_tile(t + step);
+            } else if (more) {
+                load_tile(next);
                 load_chunk(0, buf ^ 1);
             }
             mma_chunk(buf);
@@ -399,11 +423,11 @@ static hipError_t launch_pipe_t(const DistArgs &a0, int epi, hipStream_t stream)
     const dim3 g((unsigned)(fit < cus ? fit : cus)), b(kPipeThreads);
     if (epi == kEpiDense) {
         if constexpr (PREC == kPrecSplit)
-            hipLaunchKernelGGL((dist_pipe_kernel<PREC, kEpiDense>), g, b, 0, stream, a);
+            hipLaunchKernelGGL((dist_pipe_kernel<PREC, kEpiDense, false>), g, b, 0, stream, a, nullptr, nullptr, 0u);
         else
             return hipErrorInvalidValue;
     } else {
-        hipLaunchKernelGGL((dist_pipe_kernel<PREC, kEpiFilter>), g, b, 0, stream, a);
+        hipLaunchKernelGGL((dist_pipe_kernel<PREC, kEpiFilter, false>), g, b, 0, stream, a, nullptr, nullptr, 0u);
     }
     return hipGetLastError();
 }
@@ -416,6 +440,23 @@ hipError_t launch_dist_gemm_pipe(const DistArgs &a, int epi, hipStream_t stream)
         case kPrecFP8: return launch_pipe_t<kPrecFP8>(a, epi, stream);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_dist_gemm_pipe_grouped(const DistArgs *jobs, const GemmItem *items, int64_t nitems, int prec,
+                                         hipStream_t stream, int epi) {
+    if (nitems == 0) return hipSuccess;
+    if (nitems > 0x7fffffff) return hipErrorInvalidValue;
+    const int64_t fit = (nitems + 7) / 8 * 8, cus = (int64_t)device_cus() / 8 * 8;
+    const dim3 g((unsigned)(fit < cus ? fit : cus)), b(kPipeThreads);
+    const DistArgs none{};
+    const uint32_t n = (uint32_t)nitems;
+    if (prec == kPrecSplit && epi == kEpiDense)
+        hipLaunchKernelGGL((dist_pipe_kernel<kPrecSplit, kEpiDense, true>), g, b, 0, stream, none, jobs, items, n);
+    else if (prec == kPrecSplit)
+        hipLaunchKernelGGL((dist_pipe_kernel<kPrecSplit, kEpiFilter, true>), g, b, 0, stream, none, jobs, items, n);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 }  // namespace knn

@@ -216,22 +216,34 @@ inline hipError_t select_dense(const float *D, int64_t rows, int64_t cols, int64
     return launch_select(a, cap, select_grid(cap, rows, num_cu), ws, stream);
 }
 
-// Puts an FP32 plan's products on two-half operands (gemm_pipe.hip) where they
-// are at least as exact as the FP32 matrix instruction (d >= 64, measured there)
-// and pay: from 128 rows on (making the operands moves 8 bytes per corpus
-// element, about what 150 rows of the FP32 product take) and once the filter has
-// about a 256 x 256 tile per CU (16 x 16 tiles at n = m = 4096; fewer leave CUs
-// idle that smaller FP32 tiles use).  Only the filtered path: a corpus no larger
-// than its sample is too small.
-// KNN_GEMM_SPLIT=0 turns it off, KNN_SPLIT_BYTES caps the operands held (tests).
+// Whether two-half operands (gemm_pipe.hip) serve an FP32 plan's products: where
+// they are at least as exact as the FP32 matrix instruction (d >= 64, measured
+// there) and pay, from 128 rows on (making the operands moves 8 bytes per corpus
+// element, about what 150 rows of the FP32 product take).  Only the filtered
+// path: a corpus no larger than its sample is too small.  KNN_GEMM_SPLIT=0 turns
+// it off, and so does a tile of the FP32 product asked for by KNN_GEMM_TILE.
+inline bool split_serves(const Plan &p) {
+    if (p.prec != kPrecF32 || p.unfused || !p.gathered || p.d < 64 || p.m < 128) return false;
+    if (split_row_bytes(p.d) > (1 << 22)) return false;
+    if (const char *e = std::getenv("KNN_GEMM_SPLIT"))
+        if (e[0] == '0') return false;
+    return std::getenv("KNN_GEMM_TILE") == nullptr;
+}
+inline void use_split(Plan &p) {
+    p.split = true;
+    p.ldq = split_row_bytes(p.d);
+    // three times the terms, each with a rounding (one accumulation of 3 d
+    // products); both operands within 2^-23 of themselves; low x low left out
+    p.rel = (float)(std::ldexp(1.0, -21) + 3.0 * p.gamma);
+}
+
+// The single call's choice: also once the filter has about a 256 x 256 tile per
+// CU (16 x 16 tiles at n = m = 4096; fewer leave CUs idle that smaller FP32 tiles
+// use).  KNN_SPLIT_BYTES caps the operands held (tests).
 inline void plan_split(Plan &p) {
-    if (p.prec != kPrecF32 || p.unfused || !p.gathered || p.d < 64 || p.m < 128) return;
     const int64_t bytes = split_row_bytes(p.d);
     const int64_t rows = p.m < p.Mb ? p.m : p.Mb;
-    if (bytes > (1 << 22) || ((rows + 255) / 256) * ((p.n + 255) / 256) < 192) return;
-    if (const char *e = std::getenv("KNN_GEMM_SPLIT"))
-        if (e[0] == '0') return;
-    if (std::getenv("KNN_GEMM_TILE")) return;  // a tile of the FP32 product is asked for
+    if (!split_serves(p) || ((rows + 255) / 256) * ((p.n + 255) / 256) < 192) return;
     size_t budget = kSplitBytes;
     if (const char *e = std::getenv("KNN_SPLIT_BYTES")) {
         const long long v = std::atoll(e);
@@ -240,11 +252,7 @@ inline void plan_split(Plan &p) {
     int64_t nb = (int64_t)(budget / (size_t)bytes) / 256 * 256;
     if (nb < 256) nb = 256;
     p.Nb = nb < p.n ? nb : p.n;
-    p.ldq = bytes;
-    p.split = true;
-    // three times the terms, each with a rounding (one accumulation of 3 d
-    // products); both operands within 2^-23 of themselves; low x low left out
-    p.rel = (float)(std::ldexp(1.0, -21) + 3.0 * p.gamma);
+    use_split(p);
 }
 
 // The plan of one search / graph call: candidate oversampling, threshold sample,

@@ -108,3 +108,38 @@ def test_low_precision_matches_small_tiles(h, torch, prec, n, d, k):
     P = torch.from_numpy(points("gmm", n, d, 7)).cuda()
     a, b = both("KNN_GEMM_PIPE", "0", lambda: h.graph(P, k, precision=prec))
     same(a, b)
+
+
+def test_batch_split_matches_fp32(torch):
+    """Uneven FP32 jobs (graphs, odd d, few rows, tiny corpora among them) in one
+    batch: the pipelined grouped products and the FP32 ones give the same bits,
+    on the first call and on a replay with new values in the same buffers."""
+    import paper_1309_5478_amd as knn
+    shapes = [(300, 9000, 64, 7), (128, 30011, 96, 300), (1024, 5003, 65, 1), (50, 20000, 128, 10),
+              (None, 4111, 72, 12), (257, 1500, 64, 16), (200, 700, 33, 900), (0, 5000, 64, 3)]
+
+    def run(split):
+        h = knn.Handle(0)
+        jobs, res = [], []
+        for s, (m, n, d, k) in enumerate(shapes):
+            q = None if m is None else torch.from_numpy(points("gmm", m, d, 50 + s)).cuda()
+            jobs.append((q, torch.from_numpy(points("gmm", n, d, 80 + s)).cuda(), k))
+        out = [(torch.empty(((n if m is None else m), k), device="cuda"),
+                torch.empty(((n if m is None else m), k), dtype=torch.int32, device="cuda"))
+               for m, n, d, k in shapes]
+        if not split:
+            os.environ["KNN_GEMM_SPLIT"] = "0"
+        try:
+            for call in range(3):
+                if call == 2:
+                    for s, (q, c, k) in enumerate(jobs):
+                        c.copy_(torch.from_numpy(points("gmm", c.shape[0], c.shape[1], 180 + s)))
+                h.batch_search(jobs, out=out)
+                res.append([(a.clone(), b.clone()) for a, b in out])
+        finally:
+            os.environ.pop("KNN_GEMM_SPLIT", None)
+        return res
+
+    for x, y in zip(run(True), run(False)):
+        for a, b in zip(x, y):
+            same(a, b)
