@@ -76,9 +76,10 @@ struct BatchPart {
     int job;
     int64_t i0, mb;
     bool direct;    // the threshold sample is the whole corpus: its selection is the candidate list
-    bool pipe;      // both products on two-half operands, in the grouped pipelined launches
-    bool grouped;   // else FILTER product in the grouped launch (or its own: FP32 with d % 4 != 0)
-    bool sgrouped;  // and sample product in the grouped launch (same condition)
+    bool pipe;      // FILTER product in the grouped pipelined launch
+    bool grouped;   // else in the grouped launch (or its own: FP32 with d % 4 != 0)
+    bool spipe;     // sample product in the grouped pipelined launch (two-half operands)
+    bool sgrouped;  // else in the grouped launch (or its own)
     float *Ds = nullptr;   // mb x S sample distances
     float *tv = nullptr;   // mb x (r + 1) selected sample keys (values, indices)
     int32_t *ti = nullptr;
@@ -229,7 +230,7 @@ void build_sample_items(const BatchState &b, bool pipe, std::vector<GemmItem> &i
     const int t = pipe ? kPipeTileDim : 128;
     for (size_t pi = 0; pi < b.parts.size(); ++pi) {
         const BatchPart &pt = b.parts[pi];
-        if (pipe ? !pt.pipe : !pt.sgrouped) continue;
+        if (pipe ? !pt.spipe : !pt.sgrouped) continue;
         const uint32_t tm_n = (uint32_t)((pt.mb + t - 1) / t), tn_n = (uint32_t)((b.jobs[pt.job].p.S + t - 1) / t);
         for (uint32_t tm = 0; tm < tm_n; ++tm)
             for (uint32_t tn = 0; tn < tn_n; ++tn) items.push_back(GemmItem{(uint32_t)pi, tm, tn});
@@ -525,7 +526,7 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
     BTRY(launch_dist_gemm_grouped(sh.stable, sh.sitems, (int64_t)b.nsitems, b.jobs[0].p.prec, kTileSmall, s,
                                   kEpiDense));
     for (const BatchPart &pt : b.parts)
-        if (!pt.sgrouped && !pt.pipe) BTRY(launch_dist_gemm(sample_args(b, pt), kEpiDense, s));
+        if (!pt.sgrouped && !pt.spipe) BTRY(launch_dist_gemm(sample_args(b, pt), kEpiDense, s));
     // all threshold selections, one launch per capacity class
     for (const SegLaunch &L : b.sample_sel) {
         SelectArgs sa = seg_select_args(b, L);
@@ -542,7 +543,10 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
 hipError_t enqueue_product(const BatchState &b, const DistArgs *table, int tile, bool queue, int num_cu,
                            hipStream_t s) {
     hipError_t e = hipSuccess;
-    BTRY(launch_dist_gemm_pipe_grouped(table, b.sh.pitems, (int64_t)b.npitems, kPrecSplit, s));
+    if (table != b.sh.probe) {  // (the timed forms differ in the other parts alone)
+        const int prec = b.jobs[0].p.prec == kPrecF32 ? kPrecSplit : b.jobs[0].p.prec;
+        BTRY(launch_dist_gemm_pipe_grouped(table, b.sh.pitems, (int64_t)b.npitems, prec, s));
+    }
     if (queue)
         BTRY(launch_dist_gemm_queue(table, b.sh.items, (int64_t)b.nitems, b.jobs[0].p.prec, tile, b.sh.queues, num_cu,
                                     s));
@@ -830,7 +834,7 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         // jobs first, up to a third of the memory that is free: the rest is the
         // workspace's and the program's
         size_t split_left = 0;
-        if (!tune && !std::getenv("KNN_BATCH_QUEUE")) {
+        if (!std::getenv("KNN_BATCH_QUEUE")) {
             size_t free_bytes = 0, total_bytes = 0;
             KTRY(hipMemGetInfo(&free_bytes, &total_bytes));
             split_left = (free_bytes + b.ws_bytes) / 3;
@@ -856,6 +860,7 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         for (size_t j = 0; j < b.jobs.size(); ++j) b.order[j] = (int)j;
         std::stable_sort(b.order.begin(), b.order.end(),
                          [&](int x, int y) { return b.jobs[x].cost > b.jobs[y].cost; });
+        const bool lowprec_pipe = o.precision != KNN_PREC_FP32 && lowprec_pipe_on() && !std::getenv("KNN_BATCH_QUEUE");
         std::vector<Plan> plain;  // the plans before split operands
         for (const BatchJob &js : b.jobs) plain.push_back(js.p);
         bool any_split = false;
@@ -881,9 +886,11 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
                     pt.i0 = i0;
                     pt.mb = js.m - i0 < js.p.Mb ? js.m - i0 : js.p.Mb;
                     pt.direct = !js.p.gathered;
-                    pt.pipe = js.p.split;
-                    pt.sgrouped = !pt.pipe && !(js.p.prec == kPrecF32 && js.d % 4 != 0);
-                    pt.grouped = !pt.direct && pt.sgrouped;
+                    const bool group = !(js.p.prec == kPrecF32 && js.d % 4 != 0);
+                    pt.spipe = js.p.split;
+                    pt.sgrouped = !pt.spipe && group;
+                    pt.pipe = !pt.direct && (js.p.split || (lowprec_pipe && pt.mb > 64 && js.p.ldq <= (1 << 22)));
+                    pt.grouped = !pt.direct && !pt.pipe && group;
                     b.parts.push_back(pt);
                 }
                 js.nparts = (int)b.parts.size() - js.first_part;

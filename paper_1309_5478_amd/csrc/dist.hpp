@@ -9,7 +9,7 @@ enum : int { kEpiDense = 0, kEpiFilter = 1 };
 // (kPrecSplit: FP32 operands as two FP16 halves, see gemm_pipe.hip; a form of the
 // operands inside the library, not a caller's precision)
 enum : int { kPrecF32 = 0, kPrecBF16 = 1, kPrecFP8 = 2, kPrecSplit = 3 };
-enum : int { kTileSmall = 0, kTileWide = 1, kTileBig = 2, kTileSmall1 = 3 };
+enum : int { kTileSmall = 0, kTileWide = 1, kTileBig = 2, kTileSmall1 = 3, kTilePipe = 4 };
 
 // Quantised operands (BF16 / FP8): rows padded with zeros to a multiple of
 // kQuantPad elements, so every 128-byte k-chunk load is in bounds.
@@ -48,14 +48,9 @@ struct DistArgs {
     int64_t ldq;
     const float *qscale;
     const float *cscale;
-    // tile shape (kTile*), or -1 for the default choice of gemm_tile_choice
+    // tile shape (kTile*; kTilePipe: the pipelined product where it serves), or -1
+    // for the default choice
     int tile = -1;
-    // FILTER with the resident-corpus product only (optional): stage_bytes of
-    // device memory where each wave appends its kept keys without atomics; a
-    // second pass then appends them to the rows (cnt / cand as above).  Null:
-    // every kept key is appended to its row in the product itself.
-    void *stage = nullptr;
-    int64_t stage_bytes = 0;
     // FILTER on the pipelined product only: corpus index of column 0 (the corpus
     // passes in blocks of columns)
     int64_t col_base = 0;
@@ -106,19 +101,26 @@ hipError_t launch_dist_gemm_grouped(const DistArgs *jobs, const GemmItem *items,
 hipError_t launch_dist_gemm_queue(const DistArgs *jobs, const GemmItem *items, int64_t nitems, int prec, int tile,
                                   uint32_t *queues, int num_cu, hipStream_t stream);
 // The pipelined product over a list of 256 x 256 tiles of many products (split
-// operands): as launch_dist_gemm_grouped, ldq at most 2^22 and no qnorm / row_ids.
+// operands; BF16 and FP8 with the FILTER epilogue): as launch_dist_gemm_grouped,
+// ldq at most 2^22 and no qnorm / row_ids.
 constexpr int kPipeTileDim = 256;
 hipError_t launch_dist_gemm_pipe_grouped(const DistArgs *jobs, const GemmItem *items, int64_t nitems, int prec,
                                          hipStream_t stream, int epi = kEpiFilter);
-// The resident-corpus product for short BF16 / FP8 rows with the FILTER
-// epilogue (gemm_sk.hip): whether it serves `a` (KNN_GEMM_SK=0 turns it off),
-// and its launch.  launch_dist_gemm uses it where it applies.
-bool gemm_sk_applies(const DistArgs &a, int epi);
-hipError_t launch_dist_gemm_sk(const DistArgs &a, hipStream_t stream);
+// The 256 x 256 tiles pay from about 24 of them on, for more than 64 rows
+// (whole searches, 128 x 128 tiles / these; d = 256: BF16 256 x 3000 118 / 123 us,
+// 128 x 6000 131 / 120, 100 x 40000 218 / 170, 1000 x 10000 170 / 153; FP8 256 x
+// 3000 125 / 127, 256 x 6000 143 / 132, 1000 x 40000 273 / 210; halves, from 128
+// rows on, 1000 x 10000 213 / 194, d = 1024 418 / 290; 128 x 40000, d = 256, 246 /
+// 249).  Of at most 64 rows the 256-row tile wastes more than it gains once the
+// corpus is long: 64 x 10^6, d = 1024, BF16 2753 / 2910.
+inline bool pipe_fills(int64_t m, int64_t n) {
+    return m > 64 && ((m + kPipeTileDim - 1) / kPipeTileDim) * ((n + kPipeTileDim - 1) / kPipeTileDim) >= 24;
+}
 // The pipelined product on 256 x 256 tiles (gemm_pipe.hip): whether it serves `a`
 // (KNN_GEMM_PIPE=0 turns it off for BF16 and FP8), and its launch.
 // launch_dist_gemm uses it where it applies.
 bool gemm_pipe_applies(const DistArgs &a, int epi);
+bool lowprec_pipe_on();  // (not turned off, and no tile of gemm.hip asked for by KNN_GEMM_TILE)
 hipError_t launch_dist_gemm_pipe(const DistArgs &a, int epi, hipStream_t stream);
 // Compute units of the current device.
 int device_cus();

@@ -428,8 +428,6 @@ hipError_t launch_dist_gemm(const DistArgs &a, int epi, hipStream_t stream) {
     if (a.m == 0 || a.n == 0) return hipSuccess;
     // enough work for 256 x 256 tiles: the pipelined product (gemm_pipe.hip)
     if (gemm_pipe_applies(a, epi)) return launch_dist_gemm_pipe(a, epi, stream);
-    // short reduced-precision rows: the resident-corpus product (gemm_sk.hip)
-    if (gemm_sk_applies(a, epi)) return launch_dist_gemm_sk(a, stream);
     switch (gemm_tile_choice(a)) {
         case kTileBig:
             return epi == kEpiDense ? launch_gemm_t<2, 4, 4, 2, kEpiDense>(a, stream)

@@ -30,18 +30,27 @@
 // wave the fragments alone take the LDS bandwidth (BF16: 128 B per cycle and CU
 // at full rate, 96 here, 48 for the halves, which use each fragment twice).
 //
-// The epilogue forms d' = ||c||^2 - 2 q.c for four rows by two blocks at a time,
+// The epilogue forms d' = ||c||^2 - 2 q.c for two rows by two blocks at a time,
 // votes per accumulator register and appends the kept keys to the wave's list
-// in LDS (position from the ballot, nothing waited for), then appends the list
-// to the rows, a lane per key, so that its slot reservations (global atomics)
-// are in flight together.
+// in LDS (position from the ballot, nothing waited for).  The list is emptied
+// to the rows, a lane per key so that the slot reservations (global atomics) are
+// in flight together, when it is half full or the wave's rows change: a
+// workgroup's tiles follow each other along a row tile, so most tiles pass
+// without touching memory.  For short rows this path is the bound: the overflow
+// branch, 128 times inline as first written, took 1.3 of 4.1 ms (FP8, 32768 x
+// 262144, d = 256, 554 keys kept per row) in instruction fetch alone; with the
+// test once per four registers, marked unlikely, 3.6 ms (2.6 with no key kept).
+// Nothing in front of a tile's first products waits for its thresholds, norms
+// and scales (2.70 -> 2.55 ms with no key kept).
 //
 // Measured (32768 x 131072, d = 1024, about 450 keys kept per row): halves
 // 19.3 ms = 451 TFLOP/s of FP32 work, 1352 on the matrix cores (FP32 instruction
 // 69.0 ms, 128); the cores are 73 % busy at the 1.8 GHz that the power limit
 // leaves.  BF16 7.5 ms = 1133 TFLOP/s (128 x 128 tiles 12.0 ms, 731), FP8 3.7 ms
-// = 2315 (871 at 128 x 128).  32768 x 262144, d = 256: FP8 2.95 ms = 1438 TFLOP/s
-// (resident-corpus product 4.1 + 0.5 ms).
+// = 2315 (871 at 128 x 128).  Whole k-NN graphs against a product that kept the
+// corpus in registers and streamed the queries past it, which it replaced (k =
+// 32; BF16 262144 x 256 56.9 -> 54.7 ms, 2^20 x 256 681 -> 660, 262144 x 64 38.5 ->
+// 29.9; FP8 262144 x 256 48.1 -> 42.3).
 #include <cstdlib>
 #include <type_traits>
 
@@ -67,7 +76,8 @@ static_assert(kPipeTile == 32 * kPipeBI * kPipeWM && kPipeTile == 32 * kPipeBJ *
 constexpr int kPipeChunk = 128;                        // bytes of a row per stage
 constexpr int kPipeStage = 2 * kPipeTile * kPipeChunk;
 constexpr int kPipeLoads = 2 * kPipeTile / 8 / kPipeWaves;  // load instructions per wave and stage (8 rows each)
-constexpr uint32_t kPipeList = 256;                    // listed keys per wave
+constexpr uint32_t kPipeList = 448;                    // listed keys per wave
+constexpr uint32_t kListColBits = 25;
 constexpr uint32_t kPipeGroup = 4;                     // row tiles walked together across the columns
 
 // 64 lanes x 16 bytes from base + off (per lane) to LDS bytes lds .. + 1023.
@@ -119,7 +129,7 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
     constexpr int BI = kPipeBI, BJ = kPipeBJ;
     constexpr bool SC = PREC != kPrecBF16;  // per-point scales
     __shared__ __align__(1024) unsigned char stage[2 * kPipeStage];
-    __shared__ uint64_t list[EPI == kEpiFilter ? kPipeWaves : 1][EPI == kEpiFilter ? kPipeList : 1];
+    __shared__ uint2 list[EPI == kEpiFilter ? kPipeWaves : 1][EPI == kEpiFilter ? kPipeList : 1];
     __shared__ __align__(16) float stau[2][EPI == kEpiFilter ? kPipeTile : 4], sqs[2][SC ? kPipeTile : 4];
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint32_t wm = wave % kPipeWM, wn = wave / kPipeWM, h = lane / 32, l32 = lane % 32;
@@ -240,29 +250,30 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
     load_chunk(0, 0);
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     uint32_t buf = 0, par = 0;
+    uint32_t kept = 0, list_col0 = 0;  // listed keys of this wave (the same in every lane), origin of their columns
     for (uint32_t t = first; t < end; t += step, par ^= 1) {
         const uint32_t row0 = next.row0, col0 = next.col0;
         const DistArgs &a = *next.a;
         const int nk = (a.d + chunk_elems<PREC>() - 1) / chunk_elems<PREC>();
         const bool more = t + step < end;
         if (more) next = tile_at(t + step);
-        // this tile's thresholds and scales are requested now, and stored to LDS
-        // (the copy of this tile's parity: another wave may still be in the
-        // previous tile's epilogue) ahead of its first barrier.  A NaN
-        // threshold keeps nothing (rows beyond the matrix), nor does a NaN norm
-        // (columns beyond it).
+        // This tile's thresholds, scales and norms are requested now (rows and
+        // columns beyond the matrices: the last one's) and not touched before
+        // the first chunk's products are done, so that nothing waits for them.
         float tv = 0.f, qv = 1.f;
+        const uint32_t grow = row0 + tid;
         if (tid < (uint32_t)kPipeTile) {
-            const uint32_t gi = row0 + tid;
-            if (EPI == kEpiFilter) tv = gi < a.m ? a.tau[(int64_t)gi * a.tau_stride] : __uint_as_float(0x7fc00000u);
-            if (SC && gi < a.m) qv = a.qscale[gi];
+            const int64_t gi = grow < a.m ? grow : a.m - 1;
+            if (EPI == kEpiFilter) tv = a.tau[gi * a.tau_stride];
+            if (SC) qv = a.qscale[gi];
         }
         float cn[BJ], cs[BJ];
 #pragma unroll
         for (int j = 0; j < BJ; ++j) {
             const uint32_t gj = col0 + wn * 32 * BJ + j * 32 + l32;
-            cn[j] = gj < a.n ? a.cnorm[gj] : __uint_as_float(0x7fc00000u);
-            cs[j] = SC && gj < a.n ? -2.0f * a.cscale[gj] : -2.0f;
+            const int64_t cj = gj < a.n ? gj : a.n - 1;
+            cn[j] = a.cnorm[cj];
+            cs[j] = SC ? a.cscale[cj] : 1.0f;
         }
 #pragma unroll
         for (int i = 0; i < BI; ++i)
@@ -277,13 +288,18 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
                 load_chunk(0, buf ^ 1);
             }
             mma_chunk(buf);
+            // this wave's loads have landed; with the first chunk the thresholds
+            // and scales go to LDS (the copy of this tile's parity: another wave
+            // may still be in the previous tile's epilogue).  A NaN threshold
+            // keeps nothing (rows beyond the matrix), nor does a NaN norm
+            // (columns beyond it).
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (kc == 0 && tid < (uint32_t)kPipeTile) {
-                if (EPI == kEpiFilter) stau[par][tid] = tv;
+                if (EPI == kEpiFilter) stau[par][tid] = grow < a.m ? tv : __uint_as_float(0x7fc00000u);
                 if (SC) sqs[par][tid] = qv;
             }
-            // this wave's loads have landed and its LDS reads are done, and
-            // after the barrier every wave's
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            // and its LDS accesses are done, and after the barrier every wave's
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             buf ^= 1;
         }
 
@@ -293,6 +309,12 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
         // place, not kept in registers through the K loop)
         uint32_t hv = h, lv = l32;
         asm volatile("" : "+v"(hv), "+v"(lv));
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) {
+            asm volatile("" : "+v"(cn[j]), "+v"(cs[j]));
+            if (col0 + wn * 32 * BJ + j * 32 + lv >= a.n) cn[j] = __uint_as_float(0x7fc00000u);
+            cs[j] *= -2.0f;
+        }
         const float *qp = &sqs[par][SC ? wm * 32 * BI + 4 * hv : 0];
         if constexpr (EPI == kEpiDense) {
 #pragma unroll
@@ -317,21 +339,25 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
                     __builtin_amdgcn_sched_barrier(0);
                 }
         } else {
-            uint64_t *const mine = list[wave];
-            uint32_t kept = 0;  // (the same in every lane)
+            // listed: the distance's bits, and the row in the wave's block (7
+            // bits) over the column from list_col0 on (25 bits)
+            if (kept == 0) list_col0 = gc0;
+            uint2 *const mine = list[wave];
             auto drain = [&]() {
                 __builtin_amdgcn_wave_barrier();
                 for (uint32_t p = lane; p < kept; p += kWave) {
-                    const uint64_t e = mine[p];
-                    const uint32_t row = gr0 + ((uint32_t)e >> 16);
-                    const uint32_t col = (uint32_t)a.col_base + gc0 + ((uint32_t)e & 0xffffu);
+                    const uint2 e = mine[p];
+                    const uint32_t row = gr0 + (e.y >> kListColBits);
+                    const uint32_t col = (uint32_t)a.col_base + list_col0 + (e.y & ((1u << kListColBits) - 1));
                     if (a.self_offset >= 0 && (int64_t)col == a.self_offset + row) continue;  // own point
                     const uint32_t slot = atomicAdd(&a.cnt[row], 1u);
-                    if (slot < (uint32_t)a.cap) a.cand[(size_t)row * a.cap + slot] = key_of(key_ord(e), col);
+                    if (slot < (uint32_t)a.cap)
+                        a.cand[(size_t)row * a.cap + slot] = key_of(ord32_not_nan(__uint_as_float(e.x)), col);
                 }
                 __builtin_amdgcn_wave_barrier();
                 kept = 0;
             };
+            const uint32_t rc0 = (4 * hv << kListColBits) + (gc0 - list_col0 + lv);
             const float *tp = &stau[par][wm * 32 * BI + 4 * hv];
 #pragma unroll
             for (int i = 0; i < BI; ++i) {
@@ -342,38 +368,47 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
                     if (SC) q4[q] = *reinterpret_cast<const f32x4 *>(qp + i * 32 + 8 * q);
                 }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    uint64_t m[4][BJ], any = 0;
-                    float dp[4][BJ];
+                for (int g = 0; g < 8; ++g) {  // two rows by BJ blocks at a time
+                    const int q = g / 2;
+                    uint64_t m[2][BJ], any = 0;
+                    float dp[2][BJ];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                    for (int u = 0; u < 2; ++u)
 #pragma unroll
                         for (int j = 0; j < BJ; ++j) {
+                            const int e = 2 * (g % 2) + u;
                             const float dot = SC ? acc[i][j][4 * q + e] * q4[q][e] : acc[i][j][4 * q + e];
-                            dp[e][j] = fmaf(cs[j], dot, cn[j]);
-                            m[e][j] = __ballot(dp[e][j] <= t4[q][e]);
-                            any |= m[e][j];
+                            dp[u][j] = fmaf(cs[j], dot, cn[j]);
+                            m[u][j] = __ballot(dp[u][j] <= t4[q][e]);
+                            any |= m[u][j];
                         }
                     if (any) {
+                        if (__builtin_expect(kept > kPipeList - 2 * BJ * kWave, 0)) {
+                            drain();
+                            // (the list's origin stays: rc0 counts from it)
+                        }
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
+                        for (int u = 0; u < 2; ++u)
 #pragma unroll
                             for (int j = 0; j < BJ; ++j)
-                                if (m[e][j]) {
-                                    const uint32_t k = (uint32_t)__popcll(m[e][j]);
-                                    if (kept + k > kPipeList) drain();
-                                    if ((m[e][j] >> lane) & 1ull)
-                                        mine[kept + lanes_below(m[e][j])] = key_of(
-                                            ord32_not_nan(dp[e][j]), (i * 32 + 8 * q + e + 4 * hv) << 16 | (j * 32 + lv));
-                                    kept += k;
+                                if (m[u][j]) {
+                                    if (__builtin_amdgcn_inverse_ballot_w64(m[u][j]))
+                                        mine[kept + lanes_below(m[u][j])] =
+                                            uint2{__float_as_uint(dp[u][j]),
+                                                  rc0 + ((uint32_t)(i * 32 + 8 * q + 2 * (g % 2) + u) << kListColBits) +
+                                                      j * 32};
+                                    kept += (uint32_t)__popcll(m[u][j]);
                                 }
                     }
-                    // four rows at a time (hoisting the others' work would hold
-                    // them all in registers)
+                    // (hoisting the other groups' work would hold them all in
+                    // registers)
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            drain();
+            // the list stays open while the tiles stay in these rows
+            if (!more || next.row0 != row0 || next.a != &a || next.col0 < col0 ||
+                next.col0 - list_col0 >= (1u << kListColBits) - kPipeTile || kept > kPipeList / 2)
+                drain();
         }
     }
 }
@@ -391,11 +426,9 @@ int device_cus() {
     return cus;
 }
 
-// The 256 x 256 tiles pay once there is about one per CU: below that the
-// 128 x 128 tiles of gemm.hip spread the work over more CUs.
-static bool pipe_fills(const DistArgs &a) {
-    const int64_t tm = (a.m + kPipeTile - 1) / kPipeTile, tn = (a.n + kPipeTile - 1) / kPipeTile;
-    return a.m >= 128 && tm * tn >= 192;
+bool lowprec_pipe_on() {
+    const char *e = std::getenv("KNN_GEMM_PIPE");
+    return !(e && e[0] == '0') && !std::getenv("KNN_GEMM_TILE");
 }
 
 bool gemm_pipe_applies(const DistArgs &a, int epi) {
@@ -404,11 +437,8 @@ bool gemm_pipe_applies(const DistArgs &a, int epi) {
     // written, and the 128 x 128 tiles, several to a CU, overlap that: 32768 x
     // 8192, d = 1024, BF16: 697 us here, 496 there)
     if (epi != kEpiFilter || (a.prec != kPrecBF16 && a.prec != kPrecFP8)) return false;
-    if (a.qnorm || a.row_ids || a.tile >= 0 || a.ldq > (1 << 22)) return false;
-    if (std::getenv("KNN_GEMM_TILE")) return false;  // a tile of gemm.hip is asked for
-    if (const char *e = std::getenv("KNN_GEMM_PIPE"))
-        if (e[0] == '0') return false;
-    return pipe_fills(a);
+    if (a.qnorm || a.row_ids || (a.tile >= 0 && a.tile != kTilePipe) || a.ldq > (1 << 22)) return false;
+    return lowprec_pipe_on() && pipe_fills(a.m, a.n);
 }
 
 template <int PREC>
@@ -450,12 +480,20 @@ hipError_t launch_dist_gemm_pipe_grouped(const DistArgs *jobs, const GemmItem *i
     const dim3 g((unsigned)(fit < cus ? fit : cus)), b(kPipeThreads);
     const DistArgs none{};
     const uint32_t n = (uint32_t)nitems;
-    if (prec == kPrecSplit && epi == kEpiDense)
-        hipLaunchKernelGGL((dist_pipe_kernel<kPrecSplit, kEpiDense, true>), g, b, 0, stream, none, jobs, items, n);
-    else if (prec == kPrecSplit)
-        hipLaunchKernelGGL((dist_pipe_kernel<kPrecSplit, kEpiFilter, true>), g, b, 0, stream, none, jobs, items, n);
-    else
-        return hipErrorInvalidValue;
+#define KNN_PIPE_GROUPED(PREC, EPI) \
+    hipLaunchKernelGGL((dist_pipe_kernel<PREC, EPI, true>), g, b, 0, stream, none, jobs, items, n)
+    if (epi == kEpiDense) {
+        if (prec != kPrecSplit) return hipErrorInvalidValue;
+        KNN_PIPE_GROUPED(kPrecSplit, kEpiDense);
+    } else {
+        switch (prec) {
+            case kPrecSplit: KNN_PIPE_GROUPED(kPrecSplit, kEpiFilter); break;
+            case kPrecBF16: KNN_PIPE_GROUPED(kPrecBF16, kEpiFilter); break;
+            case kPrecFP8: KNN_PIPE_GROUPED(kPrecFP8, kEpiFilter); break;
+            default: return hipErrorInvalidValue;
+        }
+    }
+#undef KNN_PIPE_GROUPED
     return hipGetLastError();
 }
 

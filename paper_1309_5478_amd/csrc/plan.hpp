@@ -83,8 +83,6 @@ struct Bufs {
     float *tfix = nullptr;
     void *selws = nullptr;
     float *ninf = nullptr;  // one -inf: threshold of the tile-timing launches
-    void *stage = nullptr;  // kept-key staging of the resident-corpus product
-    size_t stage_bytes = 0;
 };
 
 inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
@@ -138,14 +136,6 @@ inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
         b.ti = c.take<int32_t>((size_t)p.Mb * (p.r + 1));
         b.cnt = c.take<uint32_t>(p.Mb);
         b.cand = c.take<uint64_t>((size_t)p.Mb * p.cap);
-        if (p.prec != kPrecF32 && p.ldq <= 512) {
-            // room for every row's full candidate list (key and row), plus one
-            // count per wave of the resident-corpus grid (at most 8 waves per
-            // 256 columns per 512 rows)
-            const size_t waves = (size_t)((p.n + 255) / 256) * (size_t)(p.Mb / 512 + 2) * 8;
-            b.stage_bytes = (size_t)p.Mb * p.cap * 12 + waves * 4 + 256;
-            b.stage = c.take<char>(b.stage_bytes);
-        }
         b.flags = c.take<int32_t>(p.Mb);
         b.nflag = c.take<uint32_t>(1);
         b.sv = c.take<float>((size_t)p.Mb * p.kk);
@@ -237,13 +227,11 @@ inline void use_split(Plan &p) {
     p.rel = (float)(std::ldexp(1.0, -21) + 3.0 * p.gamma);
 }
 
-// The single call's choice: also once the filter has about a 256 x 256 tile per
-// CU (16 x 16 tiles at n = m = 4096; fewer leave CUs idle that smaller FP32 tiles
-// use).  KNN_SPLIT_BYTES caps the operands held (tests).
+// The single call's choice: also once there is work for the large tiles
+// (pipe_fills in gemm_pipe.hip).  KNN_SPLIT_BYTES caps the operands held (tests).
 inline void plan_split(Plan &p) {
     const int64_t bytes = split_row_bytes(p.d);
-    const int64_t rows = p.m < p.Mb ? p.m : p.Mb;
-    if (!split_serves(p) || ((rows + 255) / 256) * ((p.n + 255) / 256) < 192) return;
+    if (!split_serves(p) || !pipe_fills(p.m < p.Mb ? p.m : p.Mb, p.n)) return;
     size_t budget = kSplitBytes;
     if (const char *e = std::getenv("KNN_SPLIT_BYTES")) {
         const long long v = std::atoll(e);

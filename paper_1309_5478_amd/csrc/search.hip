@@ -268,26 +268,37 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     // autotuning is on (the timing launches keep nothing: threshold -inf)
     int ftile = -1;
     if (autotune_enabled(opt)) {
+        KNN_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(b.ninf), 1, 0xFF800000u, stream));
+        DistArgs pa{};
+        pa.Q = Q;
+        pa.m = p.Mb < 8192 ? p.Mb : 8192;
+        pa.C = C;
+        pa.n = n < p.Nb ? n : p.Nb;
+        pa.d = d;
+        pa.cnorm = b.cnorm;
+        pa.self_offset = graph ? 0 : -1;
+        pa.tau = b.ninf;
+        pa.tau_stride = 0;
+        pa.cnt = b.cnt;
+        pa.cand = b.cand;
+        pa.cap = p.cap;
+        set_prec(pa, qrow(0), qsrow(0), Cq, csc);
+        const bool pipe = gemm_pipe_applies(pa, kEpiFilter);
         const std::string key = "fused|" + h->arch + "|cu" + std::to_string(num_cu) + "|p" + std::to_string(p.prec) +
                                 "|d" + std::to_string(d) + "|m" + std::to_string(size_bucket(p.Mb)) + "|n" +
-                                std::to_string(size_bucket(n));
+                                std::to_string(size_bucket(n)) + (pipe ? "|pipe" : "");
         ftile = autotune_lookup(key);
         if (ftile < 0) {
-            KNN_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(b.ninf), 1, 0xFF800000u, stream));
-            DistArgs pa{};
-            pa.Q = Q;
-            pa.m = p.Mb < 8192 ? p.Mb : 8192;
-            pa.C = C;
-            pa.n = n;
-            pa.d = d;
-            pa.cnorm = b.cnorm;
-            pa.self_offset = graph ? 0 : -1;
-            pa.tau = b.ninf;
-            pa.tau_stride = 0;
-            pa.cnt = b.cnt;
-            pa.cand = b.cand;
-            pa.cap = p.cap;
-            set_prec(pa, qrow(0), qsrow(0), Cq, csc);
+            if (p.split) {  // the timed block's operands (remade below where a block's are)
+                if (!whole) KNN_TRY(launch_split(C, pa.n, d, b.Cq, b.cs, nullptr, nullptr, stream));
+                if (!pa.Qq) {
+                    KNN_TRY(launch_split(Q, pa.m, d, b.Qq, b.qs, nullptr, nullptr, stream));
+                    pa.Qq = b.Qq;
+                    pa.qscale = b.qs;
+                }
+                pa.Cq = b.Cq;
+                pa.cscale = b.cs;
+            }
             // the default first, kept unless another shape is more than 3 %
             // faster: these probes keep nothing (threshold -inf), and the
             // candidate writes they leave out favour the default's more
@@ -295,11 +306,18 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             // calls 4 % faster on the default)
             std::vector<int> cands = {kTileSmall1, kTileSmall, kTileWide};
             if (p.prec != kPrecFP8) cands.push_back(kTileBig);
+            if (pipe) cands.insert(cands.begin(), kTilePipe);
             auto run = [&](int t) -> hipError_t {
                 pa.tile = t;
+                pa.prec = p.split && t == kTilePipe ? kPrecSplit : p.prec;
                 return launch_dist_gemm(pa, kEpiFilter, stream);
             };
             KNN_TRY(autotune_pick(key, cands, run, stream, 2, &ftile, 0.03f));
+        }
+        if (p.split && ftile != kTilePipe) {  // an FP32 tile is faster here
+            p.split = false;
+            p.rel = p.gamma;
+            if (!graph) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
         }
     }
     for (int64_t i0 = 0; i0 < m; i0 += p.Mb) {
@@ -357,12 +375,11 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         fa.cand = b.cand;
         fa.cap = p.cap;
         fa.tile = ftile;
-        fa.stage = b.stage;
-        fa.stage_bytes = (int64_t)b.stage_bytes;
         set_prec(fa, Qbq, qbs, p.split ? b.Cq : Cq, p.split ? b.cs : csc);
         KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
-        for (int64_t c0 = 0; c0 < n; c0 += p.Nb) {  // (one block unless split operands are capped)
-            fa.n = n - c0 < p.Nb ? n - c0 : p.Nb;
+        const int64_t nb = p.split ? p.Nb : n;  // (one block unless split operands are capped)
+        for (int64_t c0 = 0; c0 < n; c0 += nb) {
+            fa.n = n - c0 < nb ? n - c0 : nb;
             fa.cnorm = b.cnorm + c0;
             fa.col_base = c0;
             if (p.split && !whole)

@@ -143,3 +143,30 @@ def test_batch_split_matches_fp32(torch):
     for x, y in zip(run(True), run(False)):
         for a, b in zip(x, y):
             same(a, b)
+
+
+# few tiles (24 and just above), more kept keys than a wave's list holds in one
+# tile (kk = 1024 of 6145: a sixth or more of all), lists that stay open over many
+# column tiles, and a last row tile of one row
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("m,n,d,k", [(130, 6145, 256, 256), (513, 2100, 64, 200), (140, 70001, 64, 3)])
+def test_few_tiles_and_key_lists(h, torch, prec, m, n, d, k):
+    import paper_1309_5478_amd as knn
+    print(f"{prec} {m}x{n}x{d} k={k}", flush=True)
+    Q = torch.from_numpy(points("gmm", m, d, 11)).cuda()
+    C = torch.from_numpy(points("gmm", n, d, 12)).cuda()
+    env = "KNN_GEMM_SPLIT" if prec == "fp32" else "KNN_GEMM_PIPE"
+    a, b = both(env, "0", lambda: h.search(Q, C, k, precision=prec))
+    same(a, b)
+    same(h.search(Q, C, k, precision=prec, flags=knn.FLAG_AUTOTUNE), b)
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+def test_batch_low_precision_matches_small_tiles(torch, prec):
+    import paper_1309_5478_amd as knn
+    shapes = [(300, 9000, 64, 7), (65, 30011, 96, 256), (64, 5003, 65, 1), (None, 4111, 200, 12), (200, 700, 33, 90)]
+    jobs = [(None if m is None else torch.from_numpy(points("gmm", m, d, 21 + s)).cuda(),
+             torch.from_numpy(points("gmm", n, d, 31 + s)).cuda(), k) for s, (m, n, d, k) in enumerate(shapes)]
+    a, b = both("KNN_GEMM_PIPE", "0", lambda: knn.Handle(0).batch_search(jobs, precision=prec))
+    for x, y in zip(a, b):
+        same(x, y)
