@@ -109,6 +109,7 @@ struct BatchShared {
     void *Qfq = nullptr;
     int32_t *fi = nullptr;
     void *selws = nullptr;
+    size_t selws_bytes = 0;
     float *ninf = nullptr;
     uint32_t *cnt_all = nullptr;  // the candidate counts of all parts, contiguous
     int64_t cnt_rows = 0;
@@ -377,7 +378,8 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
     s.fi = c.take<int32_t>(fv);
     s.Qfq = c.take<char>(qfq);
     s.qfs = c.take<float>(fb);
-    s.selws = c.take<char>(selws < 256 ? 256 : selws);
+    s.selws_bytes = selws < 256 ? 256 : selws;
+    s.selws = c.take<char>(s.selws_bytes);
     s.ninf = c.take<float>(1);
     s.table = c.take<DistArgs>(b.parts.size());
     s.stable = c.take<DistArgs>(b.parts.size());
@@ -650,7 +652,7 @@ hipError_t run_fallback(const BatchState &b, int num_cu, hipStream_t s, int64_t 
             da.qscale = sh.qfs;
             da.cscale = js.cs;
             BTRY(launch_dist_gemm(da, kEpiDense, s));
-            BTRY(select_dense(sh.Df, fb, js.n, js.n, p.kk, sh.fv, sh.fi, sh.selws, num_cu, b.smode, b.net, s));
+            BTRY(select_dense(sh.Df, fb, js.n, js.n, p.kk, sh.fv, sh.fi, sh.selws, sh.selws_bytes, num_cu, b.smode, b.net, s));
             BTRY(launch_scatter_fallback(pt.flags + f0, fb, sh.fv, sh.fi, p.kk, pt.cand, pt.cnt, p.cap, s));
         }
     }

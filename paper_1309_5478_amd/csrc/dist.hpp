@@ -122,6 +122,32 @@ inline bool pipe_fills(int64_t m, int64_t n) {
 bool gemm_pipe_applies(const DistArgs &a, int epi);
 bool lowprec_pipe_on();  // (not turned off, and no tile of gemm.hip asked for by KNN_GEMM_TILE)
 hipError_t launch_dist_gemm_pipe(const DistArgs &a, int epi, hipStream_t stream);
+// The distance rows of a few FP32 queries (few.hip): out (m x n) = the reduced
+// keys, with the queries' squared norms and, folded into max_bits (zero or a
+// smaller value at launch), the largest corpus norm.  few_passes(m, d) must not
+// be 0.
+constexpr int kFewRows = 127;
+constexpr int kFewPasses = 3;
+constexpr size_t kFewLds = 156u << 10;
+inline size_t few_lds_bytes(int tiles, int d) {  // of 16 queries each
+    return (size_t)tiles * 16 * (((size_t)d + 15) / 16 * 16 + 4) * sizeof(float);
+}
+// Query tiles per pass over the corpus: as many as LDS holds.
+inline int few_tiles(int64_t m, int d) {
+    int tiles = m <= 16 ? 1 : (m <= 32 ? 2 : (m <= 64 ? 4 : 8));
+    while (tiles > 1 && few_lds_bytes(tiles, d) > kFewLds) tiles /= 2;
+    return tiles;
+}
+// Passes over the corpus, 0 where another path serves better (the fused path /
+// this one, 200000 x 768: m = 33 in two passes 653 / 385 us, m = 64 663 / 410, m =
+// 100 in four 664 / 749).
+inline int few_passes(int64_t m, int d) {
+    if (m < 1 || m > kFewRows || d > 8192 || few_lds_bytes(1, d) > kFewLds) return 0;
+    const int rows = 16 * few_tiles(m, d), passes = ((int)m + rows - 1) / rows;
+    return passes <= kFewPasses ? passes : 0;
+}
+hipError_t launch_dist_few(const float *Q, int64_t m, const float *C, int64_t n, int d, float *out, float *qnorm2,
+                           unsigned int *max_bits, int num_cu, hipStream_t stream);
 // Compute units of the current device.
 int device_cus();
 // Tile shape launch_dist_gemm uses for `a` (kTile*).

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstdint>
@@ -47,6 +48,7 @@ struct Plan {
     bool graph, unfused;
     int force;
     int force_rerun;
+    bool few;          // a few queries: their distance rows stored in one pass over the corpus (with unfused)
     bool split;        // FP32 product on two-half operands (ldq: bytes per split row)
     int64_t Nb;        // corpus points whose operands are held at a time
     // fused
@@ -82,8 +84,19 @@ struct Bufs {
     uint32_t *nu = nullptr;
     float *tfix = nullptr;
     void *selws = nullptr;
+    size_t selws_bytes = 0;
     float *ninf = nullptr;  // one -inf: threshold of the tile-timing launches
 };
+
+// Workspace of a dense selection that splits its rows (0: none of them does).
+inline size_t dense_split_bytes(int64_t rows, int64_t cols, int k, int num_cu) {
+    size_t need = 0;
+    for (const bool sample : {false, true}) {
+        const SplitPlan sp = select_split_plan(rows, (uint32_t)cols, (uint32_t)k, num_cu, false, sample);
+        if (sp.parts > 1) need = std::max(need, select_split_ws_bytes(sp, rows, (uint32_t)k));
+    }
+    return need;
+}
 
 inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
     b.cnorm = c.take<float>(p.n);
@@ -126,6 +139,7 @@ inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
         b.si = c.take<int32_t>((size_t)p.Mu * p.kk);
         int cap = select_cap_for_k(p.kk);
         selws = select_ws_bytes(cap, (uint32_t)p.n, select_grid(cap, p.Mu, num_cu));
+        selws = std::max(selws, dense_split_bytes(p.Mu, p.n, p.kk, num_cu));
     } else {
         if (p.gathered) {
             b.Cs = c.take<float>((size_t)p.S * p.d);
@@ -148,9 +162,11 @@ inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
         size_t w1 = select_ws_bytes(cap1, (uint32_t)p.S, select_grid(cap1, p.Mb, num_cu));
         int cap2 = select_cap_for_k(p.kk);
         size_t w2 = select_ws_bytes(cap2, (uint32_t)p.n, select_grid(cap2, p.Fb, num_cu));
-        selws = w1 > w2 ? w1 : w2;
+        // (fallback rows are few as a rule)
+        selws = std::max(std::max(w1, w2), dense_split_bytes(p.Fb < 8 ? p.Fb : 8, p.n, p.kk, num_cu));
     }
-    b.selws = c.take<char>(selws < 256 ? 256 : selws);
+    b.selws_bytes = selws < 256 ? 256 : selws;
+    b.selws = c.take<char>(b.selws_bytes);
     b.ninf = c.take<float>(1);
     return c.off;
 }
@@ -190,8 +206,10 @@ struct ProductTimer {
     }
 };
 
+// The k smallest of every row, too few long rows for one workgroup each in
+// parts where the workspace has room for them.
 inline hipError_t select_dense(const float *D, int64_t rows, int64_t cols, int64_t ld, int k, float *ov, int32_t *oi,
-                               void *ws, int num_cu, int mode, const uint16_t *net, hipStream_t stream) {
+                               void *ws, size_t ws_bytes, int num_cu, int mode, const uint16_t *net, hipStream_t stream) {
     SelectArgs a{};
     a.dist = D;
     a.rows = rows;
@@ -202,6 +220,9 @@ inline hipError_t select_dense(const float *D, int64_t rows, int64_t cols, int64
     a.out_idx = oi;
     a.mode = mode;
     a.net = mode == kPivotLearned ? net : nullptr;
+    const SplitPlan sp = select_split_plan(rows, (uint32_t)cols, (uint32_t)k, num_cu, false, mode == kPivotSample);
+    if (sp.parts > 1 && select_split_ws_bytes(sp, rows, (uint32_t)k) <= ws_bytes)
+        return launch_select_split(a, sp, ws, num_cu, stream);
     int cap = select_cap_for_k((uint32_t)k);
     return launch_select(a, cap, select_grid(cap, rows, num_cu), ws, stream);
 }
@@ -241,6 +262,21 @@ inline void plan_split(Plan &p) {
     if (nb < 256) nb = 256;
     p.Nb = nb < p.n ? nb : p.n;
     use_split(p);
+}
+
+// A few FP32 queries: their distance rows in one pass over the corpus (few.hip),
+// selected as on the unfused path.  Up to 3 d rows, or 2^25 keys: more of them
+// cost more than the corpus (the fused path / this one, n = 10^6, k = 10: d = 32,
+// m = 96 356 / 327 us, m = 127 359 / 392; d = 24, m = 72 337 / 280; small corpora
+// gain with any m).
+inline void plan_few(Plan &p) {
+    if (p.prec != kPrecF32 || p.graph || p.unfused || !p.gathered || p.force || std::getenv("KNN_GEMM_TILE")) return;
+    if (const char *e = std::getenv("KNN_FEW"))
+        if (e[0] == '0') return;
+    if (few_passes(p.m, p.d) == 0 || (p.m > 3 * (int64_t)p.d && p.m * p.n > (1 << 25))) return;
+    if ((size_t)p.m * (size_t)p.n * sizeof(float) > kDenseBytes) return;
+    p.few = p.unfused = true;
+    p.Mu = p.m;
 }
 
 // The plan of one search / graph call: candidate oversampling, threshold sample,

@@ -74,7 +74,8 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     int smode = opt ? opt->pivot : kPivotSample;
     if (smode == kPivotLearned && !net) smode = kPivotSample;
     Plan p = make_plan(m, n, d, k, graph, opt, m);
-    if (!autotune_enabled(opt)) plan_split(p);  // (autotuning times the FP32 tiles)
+    plan_few(p);
+    plan_split(p);
     Bufs b;
     auto need = [&]() {
         Carve sizing{nullptr};
@@ -82,7 +83,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     };
     void *ws = nullptr;
     knn_status_t st = ensure_ws(h, need(), stream, &ws);
-    if (st == KNN_ERROR_OUT_OF_MEMORY && p.split) {  // no room for the split operands
+    if (st == KNN_ERROR_OUT_OF_MEMORY && (p.split || p.few)) {  // no room for the split operands or the rows
         p = make_plan(m, n, d, k, graph, opt, m);
         st = ensure_ws(h, need(), stream, &ws);
     }
@@ -101,10 +102,10 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     // split operands of the whole corpus: made once, with the norms
     const bool whole = p.split && p.Nb >= n;
     if (whole) KNN_TRY(launch_split(C, n, d, b.Cq, b.cs, b.cnorm, b.cmax2, stream));
-    else KNN_TRY(launch_sqnorm(C, n, d, b.cnorm, b.cmax2, stream));
+    else if (!p.few) KNN_TRY(launch_sqnorm(C, n, d, b.cnorm, b.cmax2, stream));
     const float *qn2 = b.qn2;  // a graph's queries are its corpus
     if (graph) qn2 = b.cnorm;
-    else if (!p.split) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
+    else if (!p.split && !p.few) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
     const void *Qq = nullptr, *Cq = nullptr;
     const float *qsc = nullptr, *csc = nullptr;
     if (p.prec != kPrecF32) {
@@ -232,9 +233,10 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             a.ldo = n;
             set_prec(a, qrow(i0), qsrow(i0), Cq, csc);
             KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
-            KNN_TRY(launch_dist_gemm(a, kEpiDense, stream));
+            if (p.few) KNN_TRY(launch_dist_few(a.Q, mb, C, n, d, b.Dm, b.qn2, b.cmax2, num_cu, stream));
+            else KNN_TRY(launch_dist_gemm(a, kEpiDense, stream));
             KNN_TRY(timer.end(stream));
-            KNN_TRY(select_dense(b.Dm, mb, n, n, p.kk, b.sv, b.si, b.selws, num_cu, smode, net, stream));
+            KNN_TRY(select_dense(b.Dm, mb, n, n, p.kk, b.sv, b.si, b.selws, b.selws_bytes, num_cu, smode, net, stream));
             knn_status_t fs = finish(b.sv, b.si, i0, mb, b.Dm, n);
             if (fs != KNN_SUCCESS) return fs;
             if (timer.on) {
@@ -346,7 +348,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         if (!p.gathered) KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
         KNN_TRY(launch_dist_gemm(sa, kEpiDense, stream));
         if (!p.gathered) KNN_TRY(timer.end(stream));
-        KNN_TRY(select_dense(b.Ds, mb, p.S, p.S, p.r + 1, b.tv, b.ti, b.selws, num_cu, smode, net, stream));
+        KNN_TRY(select_dense(b.Ds, mb, p.S, p.S, p.r + 1, b.tv, b.ti, b.selws, b.selws_bytes, num_cu, smode, net, stream));
         if (!p.gathered) {
             // the sample is the whole corpus: its selection already holds each
             // row's kk smallest keys, in order, so the filtered product, the
@@ -413,7 +415,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             da.ldo = n;
             if (!p.split) set_prec(da, b.Qfq, b.qfs, Cq, csc);
             KNN_TRY(launch_dist_gemm(da, kEpiDense, stream));
-            KNN_TRY(select_dense(b.Df, fb, n, n, p.kk, b.fv, b.fi, b.selws, num_cu, smode, net, stream));
+            KNN_TRY(select_dense(b.Df, fb, n, n, p.kk, b.fv, b.fi, b.selws, b.selws_bytes, num_cu, smode, net, stream));
             KNN_TRY(launch_scatter_fallback(b.flags + f0, fb, b.fv, b.fi, p.kk, b.cand, b.cnt, p.cap, stream));
         }
         // 4. kk smallest candidates, exact re-rank, final k
