@@ -449,6 +449,7 @@ static hipError_t launch_pipe_t(const DistArgs &a0, int epi, hipStream_t stream)
     const uint64_t tiles = (uint64_t)a.tiles_m * a.tiles_n;
     // tile numbers up to the end of the last XCD's range, plus one step, in 32 bits
     if (tiles > 0x7fffffffull || a.ldq > (1 << 22) || a.qnorm || a.row_ids) return hipErrorInvalidValue;
+    if (!a.Qq || !a.Cq || (PREC != kPrecBF16 && (!a.qscale || !a.cscale))) return hipErrorInvalidValue;
     const uint64_t fit = (tiles + 7) / 8 * 8, cus = (uint64_t)device_cus() / 8 * 8;
     const dim3 g((unsigned)(fit < cus ? fit : cus)), b(kPipeThreads);
     if (epi == kEpiDense) {

@@ -233,13 +233,13 @@ inline hipError_t select_dense(const float *D, int64_t rows, int64_t cols, int64
 // element, about what 150 rows of the FP32 product take).  Only the filtered
 // path: a corpus no larger than its sample is too small.  KNN_GEMM_SPLIT=0 turns
 // it off, and so does a tile of the FP32 product asked for by KNN_GEMM_TILE.
-inline bool split_serves(const Plan &p) {
-    if (p.prec != kPrecF32 || p.unfused || !p.gathered || p.d < 64 || p.m < 128) return false;
-    if (split_row_bytes(p.d) > (1 << 22)) return false;
+inline bool split_pays(const Plan &p) {
+    if (p.prec != kPrecF32 || p.d < 64 || p.m < 128 || split_row_bytes(p.d) > (1 << 22)) return false;
     if (const char *e = std::getenv("KNN_GEMM_SPLIT"))
         if (e[0] == '0') return false;
     return std::getenv("KNN_GEMM_TILE") == nullptr;
 }
+inline bool split_serves(const Plan &p) { return p.gathered && !p.unfused && split_pays(p); }
 inline void use_split(Plan &p) {
     p.split = true;
     p.ldq = split_row_bytes(p.d);
@@ -270,13 +270,50 @@ inline void plan_split(Plan &p) {
 // m = 96 356 / 327 us, m = 127 359 / 392; d = 24, m = 72 337 / 280; small corpora
 // gain with any m).
 inline void plan_few(Plan &p) {
-    if (p.prec != kPrecF32 || p.graph || p.unfused || !p.gathered || p.force || std::getenv("KNN_GEMM_TILE")) return;
+    if (p.prec != kPrecF32 || p.graph || p.unfused || p.force || std::getenv("KNN_GEMM_TILE")) return;
     if (const char *e = std::getenv("KNN_FEW"))
         if (e[0] == '0') return;
+    if (!p.gathered && p.m > 16) return;  // (2000 x 512: m = 16 94 / 58 us, m = 100 96 / 115)
     if (few_passes(p.m, p.d) == 0 || (p.m > 3 * (int64_t)p.d && p.m * p.n > (1 << 25))) return;
     if ((size_t)p.m * (size_t)p.n * sizeof(float) > kDenseBytes) return;
     p.few = p.unfused = true;
     p.Mu = p.m;
+}
+
+// Corpora short enough that storing the distance rows and selecting from them
+// costs less than the threshold sample, its selection, the candidate lists and a
+// second product; as on the unfused path, the FP32 product on two-half operands.
+// A stored key is written and read once, about 1.8 ps; what it replaces grows
+// with the lists: up to 8192 + 40 kk points, and 20000 + 150 kk for FP32 rows too
+// short for two-half operands, whose filter pass costs more (fused / this, us.
+// 16384 queries, FP32 d = 128: kk = 128 n = 12000 684 / 644, 24000 833 / 1137; kk = 512
+// 24000 1441 / 1358, 40000 1847 / 2032; kk = 1000 40000 2839 / 2357, 64000 2902 / 3263;
+// BF16 d = 512: kk = 128 12000 1028 / 977, kk = 256 12000 1655 / 1419, 24000 1904 / 2084;
+// FP32 d = 32: kk = 128 40000 1606 / 1439, 64000 2031 / 2285.  Graphs, FP32 d = 128:
+// kk = 16 n = 4096 163 / 106, 8192 251 / 215, 16000 505 / 603; kk = 64 201 / 114, 290 /
+// 233, 582 / 676; kk = 1024, n = 3000 1181 / 250).  The plain pivot rule reads long
+// rows many times: 4096 points (kk = 32, n = 3000 223 / 170, 8192 378 / 448).  A
+// corpus that is its own sample is stored anyway; it gains only the two-half
+// product, from about 128 tiles on (20000 x 2000, d = 512 576 / 349; 2000 x 2000,
+// d = 128 82 / 85).
+inline void plan_dense(Plan &p, int smode) {
+    if (p.unfused || p.force || std::getenv("KNN_GEMM_TILE")) return;
+    if (const char *e = std::getenv("KNN_DENSE"))
+        if (e[0] == '0') return;
+    const bool split = split_pays(p) && pipe_fills(p.m, p.n);
+    if (p.gathered) {
+        const int64_t most = smode == kPivotPlain                    ? 4096
+                             : p.prec == kPrecF32 && p.d < 64 ? std::min(20000 + 150 * p.kk, 65536)
+                                                                     : 8192 + 40 * p.kk;
+        if (p.n > most) return;
+    } else if (!split || ((p.m + 255) / 256) * ((p.n + 255) / 256) < 128) {
+        return;
+    }
+    if (split) use_split(p);  // (the operands of the whole corpus: Nb = n)
+    const int64_t mu = (int64_t)(kDenseBytes / sizeof(float) / (size_t)p.n);
+    p.Mu = mu < p.m ? mu : p.m;
+    p.Mb = p.Mu;
+    p.unfused = true;
 }
 
 // The plan of one search / graph call: candidate oversampling, threshold sample,

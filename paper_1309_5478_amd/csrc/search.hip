@@ -74,7 +74,9 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     int smode = opt ? opt->pivot : kPivotSample;
     if (smode == kPivotLearned && !net) smode = kPivotSample;
     Plan p = make_plan(m, n, d, k, graph, opt, m);
+    const bool asked = p.unfused;
     plan_few(p);
+    if (!autotune_enabled(opt)) plan_dense(p, smode);  // (autotuning times the fused product)
     plan_split(p);
     Bufs b;
     auto need = [&]() {
@@ -83,7 +85,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     };
     void *ws = nullptr;
     knn_status_t st = ensure_ws(h, need(), stream, &ws);
-    if (st == KNN_ERROR_OUT_OF_MEMORY && (p.split || p.few)) {  // no room for the split operands or the rows
+    if (st == KNN_ERROR_OUT_OF_MEMORY && (p.split || p.unfused != asked)) {  // no room for split operands or the rows
         p = make_plan(m, n, d, k, graph, opt, m);
         st = ensure_ws(h, need(), stream, &ws);
     }
@@ -231,7 +233,12 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             a.self_offset = graph ? i0 : -1;
             a.out = b.Dm;
             a.ldo = n;
-            set_prec(a, qrow(i0), qsrow(i0), Cq, csc);
+            if (p.split) {
+                if (!Qq) KNN_TRY(launch_split(a.Q, mb, d, b.Qq, b.qs, b.qn2 + i0, nullptr, stream));
+                set_prec(a, Qq ? qrow(i0) : b.Qq, Qq ? qsrow(i0) : b.qs, b.Cq, b.cs);
+            } else {
+                set_prec(a, qrow(i0), qsrow(i0), Cq, csc);
+            }
             KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
             if (p.few) KNN_TRY(launch_dist_few(a.Q, mb, C, n, d, b.Dm, b.qn2, b.cmax2, num_cu, stream));
             else KNN_TRY(launch_dist_gemm(a, kEpiDense, stream));

@@ -13,6 +13,15 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def filtered():
+    """Short corpora too on the filtered path (their distance rows are stored
+    otherwise: test_gpu_dense.py)."""
+    os.environ["KNN_DENSE"] = "0"
+    yield
+    del os.environ["KNN_DENSE"]
+
+
 @pytest.fixture(scope="module")
 def torch():
     import torch as t
