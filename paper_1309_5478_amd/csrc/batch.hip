@@ -835,11 +835,13 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         // two-half operands (as large as the points themselves) for the longest
         // jobs first, up to a third of the memory that is free: the rest is the
         // workspace's and the program's
-        size_t split_left = 0;
+        // and, up to a sixth, whole distance rows of the jobs with short corpora
+        size_t split_left = 0, direct_left = 0;
         if (!std::getenv("KNN_BATCH_QUEUE")) {
             size_t free_bytes = 0, total_bytes = 0;
             KTRY(hipMemGetInfo(&free_bytes, &total_bytes));
             split_left = (free_bytes + b.ws_bytes) / 3;
+            direct_left = split_left / 2;
         }
         for (int32_t j = 0; j < njobs; ++j) {
             const knn_job_t &jb = jobs[j];
@@ -865,14 +867,21 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         const bool lowprec_pipe = o.precision != KNN_PREC_FP32 && lowprec_pipe_on() && !std::getenv("KNN_BATCH_QUEUE");
         std::vector<Plan> plain;  // the plans before split operands
         for (const BatchJob &js : b.jobs) plain.push_back(js.p);
-        bool any_split = false;
+        bool any_split = false, any_direct = false;
         auto plan_parts = [&]() {
             b.parts.clear();
-            any_split = false;
+            any_split = any_direct = false;
             for (int j : b.order) {
                 BatchJob &js = b.jobs[j];
                 js.p = plain[j];
-                if (js.m == 0 || !split_serves(js.p)) continue;
+                if (js.m == 0) continue;
+                const size_t rows = (size_t)js.m * (size_t)js.n * sizeof(float);
+                if (js.p.gathered && js.n <= kSampleColsMax && rows <= direct_left && dense_serves(js.p, smode)) {
+                    direct_left -= rows;
+                    plan_direct(js.p);
+                    any_direct = true;
+                }
+                if (!split_pays(js.p)) continue;
                 const size_t need = (size_t)(js.n + (js.graph ? 0 : js.m) + js.p.S) * (size_t)split_row_bytes(js.d);
                 if (need > split_left) continue;
                 split_left -= need;
@@ -916,10 +925,10 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
             }
             b.ws = nullptr;
             (void)hipGetLastError();
-            if (!any_split)
+            if (!any_split && !any_direct)
                 return fail_msg(h, KNN_ERROR_OUT_OF_MEMORY,
                                 "knn_batch_search: workspace of " + std::to_string(bytes) + " bytes");
-            split_left = 0;  // again without split operands
+            split_left = direct_left = 0;  // again without them
             plan_parts();
         }
         Carve real{static_cast<char *>(b.ws)};

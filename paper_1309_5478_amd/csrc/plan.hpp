@@ -296,24 +296,32 @@ inline void plan_few(Plan &p) {
 // corpus that is its own sample is stored anyway; it gains only the two-half
 // product, from about 128 tiles on (20000 x 2000, d = 512 576 / 349; 2000 x 2000,
 // d = 128 82 / 85).
-inline void plan_dense(Plan &p, int smode) {
-    if (p.unfused || p.force || std::getenv("KNN_GEMM_TILE")) return;
+inline bool dense_serves(const Plan &p, int smode) {
+    if (p.unfused || p.force || std::getenv("KNN_GEMM_TILE")) return false;
     if (const char *e = std::getenv("KNN_DENSE"))
-        if (e[0] == '0') return;
+        if (e[0] == '0') return false;
+    const int64_t most = smode == kPivotPlain             ? 4096
+                         : p.prec == kPrecF32 && p.d < 64 ? std::min(20000 + 150 * p.kk, 65536)
+                                                          : 8192 + 40 * p.kk;
+    return p.n <= most;
+}
+inline void plan_dense(Plan &p, int smode) {
+    if (!dense_serves(p, smode)) return;
     const bool split = split_pays(p) && pipe_fills(p.m, p.n);
-    if (p.gathered) {
-        const int64_t most = smode == kPivotPlain                    ? 4096
-                             : p.prec == kPrecF32 && p.d < 64 ? std::min(20000 + 150 * p.kk, 65536)
-                                                                     : 8192 + 40 * p.kk;
-        if (p.n > most) return;
-    } else if (!split || ((p.m + 255) / 256) * ((p.n + 255) / 256) < 128) {
-        return;
-    }
+    if (!p.gathered && (!split || ((p.m + 255) / 256) * ((p.n + 255) / 256) < 128)) return;
     if (split) use_split(p);  // (the operands of the whole corpus: Nb = n)
     const int64_t mu = (int64_t)(kDenseBytes / sizeof(float) / (size_t)p.n);
     p.Mu = mu < p.m ? mu : p.m;
     p.Mb = p.Mu;
     p.unfused = true;
+}
+
+// The same in a batch, whose jobs keep their sample distances: the sample is the
+// whole corpus.
+inline void plan_direct(Plan &p) {
+    p.S = (int)p.n;
+    p.gathered = false;
+    p.r = p.kk - 1;
 }
 
 // The plan of one search / graph call: candidate oversampling, threshold sample,
