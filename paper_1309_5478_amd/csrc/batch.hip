@@ -11,11 +11,17 @@
 //    each corpus tile is read by one XCD, where the part's row tiles reuse it
 //    from L2.  The items run one per workgroup, or (queue form) a resident
 //    grid takes them from eight per-XCD atomic queues in the same order;
-//  * every step of a call (norms, sample product, threshold selection, the
-//    product, list flagging, candidate selection, certificate, re-rank) is
-//    captured into one HIP graph on the first call and replayed by later calls
-//    with the same job table; one synchronisation then brings the counts of
-//    rows needing the exact fallback or re-run (rare) to the host;
+//  * FP32 jobs that two-half operands serve, and BF16 / FP8 jobs, take the
+//    pipelined 256 x 256 form of that launch (gemm_pipe.hip);
+//  * jobs with short corpora take the whole corpus as their sample (plan.hpp);
+//  * the steps around the products (norms, operands, samples, list flags,
+//    certificates, re-rank) run as one launch per kernel instance over all jobs:
+//    96 uneven jobs 23.0 -> 16.1 ms, 57 jobs of 41 queries and up to 6987 points
+//    3.28 -> 1.05 ms against a launch per job and step;
+//  * every step of a call is captured into one HIP graph on the first call and
+//    replayed by later calls with the same job table; one synchronisation then
+//    brings the counts of rows needing the exact fallback or re-run (rare) to the
+//    host;
 //  * with autotuning on, the tile shape and form of the grouped launch are
 //    the fastest of the candidates, timed on the batch itself with a threshold
 //    of -inf (nothing is kept, so the timing run has no effect on the results).
@@ -119,6 +125,12 @@ struct BatchShared {
     unsigned int *cmax2 = nullptr;                   // per job, the largest squared corpus norm
     uint32_t *nflag = nullptr;
     uint32_t *nu = nullptr;  // uncertified-row counts, one per part
+    // the preparation, flag, certificate and re-rank steps of all jobs or parts
+    PrepSeg *preps = nullptr;
+    FlagSeg *flags = nullptr;
+    CertifyArgs *certs = nullptr;
+    RerankArgs *reranks = nullptr;
+    uint32_t *preps_first = nullptr, *flags_first = nullptr, *certs_first = nullptr, *reranks_first = nullptr;
     uint32_t *queues = nullptr;  // the eight per-XCD item queues of the persistent product
 };
 
@@ -140,6 +152,7 @@ struct BatchState {
     int tile = kTileWide;
     bool queue = false;  // the product as a resident grid over per-XCD item queues
     size_t nitems = 0, nsitems = 0, npitems = 0, npsitems = 0;
+    std::vector<SegClass> preps, flags, certs, reranks;  // their launches
     std::vector<SegLaunch> sample_sel;  // threshold selections, one launch per capacity class
     SegLaunch keys_sel;                 // candidate selections
     int smode = kPivotSample;
@@ -297,6 +310,8 @@ void plan_selects(BatchState &b) {
     b.keys_sel = std::move(K);
 }
 
+constexpr size_t kPrepSegs = 7;  // preparation segments of a job, at most
+
 // Lays out the batch workspace (sizing pass with base == nullptr).  Every
 // part keeps its own sample distances, selections and candidate lists, so
 // each phase can run as one launch over all parts.
@@ -325,11 +340,12 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
         js.Csq = js.Cq;
         js.css = js.cs;
         if (p.gathered && js.nparts) {
-            js.Cs = c.take<float>((size_t)p.S * p.d);
             js.csn = c.take<float>(p.S);
             if (p.prec != kPrecF32 || p.split) {
                 js.Csq = c.take<char>((size_t)p.S * p.ldq);
                 js.css = c.take<float>(p.S);
+            } else {
+                js.Cs = c.take<float>((size_t)p.S * p.d);
             }
         }
         qf = std::max(qf, (size_t)p.Fb * p.d);
@@ -401,6 +417,15 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
     s.nflag = c.take<uint32_t>(b.parts.size());
     s.nu = c.take<uint32_t>(b.parts.size());
     s.queues = c.take<uint32_t>(8);
+    const size_t np = kPrepSegs * b.jobs.size(), parts = b.parts.size();
+    s.preps = c.take<PrepSeg>(np);
+    s.preps_first = c.take<uint32_t>(2 * np);
+    s.flags = c.take<FlagSeg>(parts);
+    s.flags_first = c.take<uint32_t>(2 * parts);
+    s.certs = c.take<CertifyArgs>(parts);
+    s.certs_first = c.take<uint32_t>(2 * parts);
+    s.reranks = c.take<RerankArgs>(parts);
+    s.reranks_first = c.take<uint32_t>(2 * parts);
     return c.off;
 }
 
@@ -461,33 +486,70 @@ SelectArgs seg_select_args(const BatchState &b, const SegLaunch &L) {
 }
 
 // Certificate of a part's kk candidates (FP32: uncertified rows are listed for
-// the exact re-run), then the exact re-rank.
-hipError_t certify_rerank(const BatchState &b, knn_handle_t h, size_t pi, const float *keys, const int32_t *cidx,
-                          hipStream_t s) {
+// the exact re-run; none is needed where they are all there are), and its exact
+// re-rank.
+const float *part_keys(const BatchPart &pt) { return pt.direct ? pt.tv : pt.sv; }
+const int32_t *part_cidx(const BatchPart &pt) { return pt.direct ? pt.ti : pt.si; }
+bool part_certified(const BatchState &b, const BatchPart &pt) {
+    const Plan &p = b.jobs[pt.job].p;
+    return p.kk < p.n_eff;
+}
+
+CertifyArgs certify_args(const BatchState &b, knn_handle_t h, size_t pi) {
     const BatchPart &pt = b.parts[pi];
     const BatchJob &js = b.jobs[pt.job];
     const Plan &p = js.p;
-    hipError_t e = hipSuccess;
-    if (p.kk < p.n_eff) {
-        CertifyArgs ca{keys, pt.mb, p.kk, js.k, js.qn2 + pt.i0, js.cmax2, p.rel, p.gamma,
+    return CertifyArgs{part_keys(pt), pt.mb, p.kk, js.k, js.qn2 + pt.i0, js.cmax2, p.rel, p.gamma,
                        stats_ptr(h) + kStatUncertified, pt.ulist, b.sh.nu + pi, pt.tfix,
                        pt.ulist != nullptr && p.force_rerun};
-        if ((e = launch_certify(ca, s)) != hipSuccess) return e;
-    }
-    RerankArgs rr{js.Q + pt.i0 * js.d, pt.mb, js.C, js.n, js.d, cidx, (uint32_t)p.kk, js.k,
+}
+
+RerankArgs rerank_args(const BatchState &b, size_t pi) {
+    const BatchPart &pt = b.parts[pi];
+    const BatchJob &js = b.jobs[pt.job];
+    const Plan &p = js.p;
+    RerankArgs rr{js.Q + pt.i0 * js.d, pt.mb, js.C, js.n, js.d, part_cidx(pt), (uint32_t)p.kk, js.k,
                   js.out_dist + pt.i0 * js.k, js.out_idx + pt.i0 * js.k, js.graph ? pt.i0 : -1, js.oscale};
-    if (p.kk < p.n_eff && p.prec == kPrecF32) {
-        rr.keys = keys;
+    if (part_certified(b, pt) && p.prec == kPrecF32) {
+        rr.keys = part_keys(pt);
         rr.qnorm2 = js.qn2 + pt.i0;
         rr.cmax2_bits = js.cmax2;
         rr.rel = p.rel;
         rr.gamma = p.gamma;
     }
-    return launch_rerank(rr, s);
+    return rr;
+}
+
+// Norms, two-half or quantised operands, and the threshold sample of every job.
+std::vector<PrepSeg> prep_segs(const BatchState &b) {
+    std::vector<PrepSeg> v;
+    for (int j : b.order) {
+        const BatchJob &js = b.jobs[j];
+        const Plan &p = js.p;
+        if (js.nparts == 0) continue;
+        const bool quant = p.prec != kPrecF32;
+        auto add = [&](const float *X, int64_t n, int64_t src_n, const void *out, const float *scale, const float *norm,
+                       unsigned int *max_bits) {
+            const int kind = p.split ? kPrepSplit : kPrepNorm;
+            v.push_back(PrepSeg{kind, X, n, src_n, js.d, p.prec, p.split ? const_cast<void *>(out) : nullptr,
+                                p.split ? const_cast<float *>(scale) : nullptr, const_cast<float *>(norm), max_bits});
+            if (quant)
+                v.push_back(PrepSeg{kPrepQuant, X, n, src_n, js.d, p.prec, const_cast<void *>(out),
+                                    const_cast<float *>(scale), nullptr, nullptr});
+        };
+        add(js.C, js.n, 0, js.Cq, js.cs, js.cnorm, js.cmax2);
+        if (!js.graph) add(js.Q, js.m, 0, js.Qq, js.qs, js.qn2, nullptr);
+        if (!p.gathered) continue;
+        add(js.C, p.S, js.n, js.Csq, js.css, js.csn, nullptr);
+        if (!quant && !p.split)
+            v.push_back(PrepSeg{kPrepGather, js.C, p.S, js.n, js.d, p.prec, const_cast<float *>(js.Cs), nullptr,
+                                nullptr, nullptr});
+    }
+    return v;
 }
 
 // ---- the phases, enqueued on a stream (captured or eager) ------------------
-hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStream_t s) {
+hipError_t enqueue_prep(const BatchState &b, int num_cu, hipStream_t s) {
     hipError_t e = hipSuccess;
     const BatchShared &sh = b.sh;
 #define BTRY(call)                                 \
@@ -496,33 +558,7 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
     } while (0)
     BTRY(launch_fill_u32(sh.nu, (int64_t)b.parts.size(), 0u, s));
     BTRY(launch_fill_u32(sh.cmax2, (int64_t)b.jobs.size(), 0u, s));
-    // per job: norms, quantised copies, the gathered threshold sample
-    for (int j : b.order) {
-        const BatchJob &js = b.jobs[j];
-        const Plan &p = js.p;
-        if (js.nparts == 0) continue;
-        if (p.split) {
-            BTRY(launch_split(js.C, js.n, js.d, js.Cq, js.cs, js.cnorm, js.cmax2, s));
-            if (!js.graph) BTRY(launch_split(js.Q, js.m, js.d, js.Qq, js.qs, js.qn2, nullptr, s));
-        } else {
-            BTRY(launch_sqnorm(js.C, js.n, js.d, js.cnorm, js.cmax2, s));
-            if (!js.graph) BTRY(launch_sqnorm(js.Q, js.m, js.d, js.qn2, nullptr, s));
-        }
-        if (p.prec != kPrecF32) {
-            BTRY(launch_quantize(js.C, js.n, js.d, p.prec, js.Cq, js.cs, s));
-            if (!js.graph) BTRY(launch_quantize(js.Q, js.m, js.d, p.prec, js.Qq, js.qs, s));
-        }
-        if (p.gathered) {
-            float *Cs = const_cast<float *>(js.Cs), *csn = const_cast<float *>(js.csn);
-            BTRY(launch_gather_rows(js.C, js.n, js.d, nullptr, p.S, Cs, js.cnorm, csn, s));
-            if (p.prec != kPrecF32)
-                BTRY(launch_quantize(Cs, p.S, js.d, p.prec, const_cast<void *>(js.Csq), const_cast<float *>(js.css),
-                                     s));
-            else if (p.split)
-                BTRY(launch_split(Cs, p.S, js.d, const_cast<void *>(js.Csq), const_cast<float *>(js.css), nullptr,
-                                  nullptr, s));
-        }
-    }
+    for (const SegClass &c : b.preps) BTRY(launch_prep_group(c, sh.preps, sh.preps_first, s));
     // all sample products in one launch per form (FP32 parts with d % 4 != 0 on their own)
     BTRY(launch_dist_gemm_pipe_grouped(sh.stable, sh.psitems, (int64_t)b.npsitems, kPrecSplit, s, kEpiDense));
     BTRY(launch_dist_gemm_grouped(sh.stable, sh.sitems, (int64_t)b.nsitems, b.jobs[0].p.prec, kTileSmall, s,
@@ -535,9 +571,6 @@ hipError_t enqueue_prep(const BatchState &b, knn_handle_t h, int num_cu, hipStre
         if (L.cap == 0) BTRY(launch_select_short(sa, num_cu, s));
         else BTRY(launch_select(sa, L.cap, select_grid(L.cap, L.rows, num_cu), sh.selws, s));
     }
-    // parts whose sample is the whole corpus: certificate and re-rank now
-    for (size_t pi = 0; pi < b.parts.size(); ++pi)
-        if (b.parts[pi].direct) BTRY(certify_rerank(b, h, pi, b.parts[pi].tv, b.parts[pi].ti, s));
     if (sh.cnt_rows) BTRY(launch_fill_u32(sh.cnt_all, sh.cnt_rows, 0u, s));
     return e;
 }
@@ -570,24 +603,19 @@ hipError_t enqueue_flags(const BatchState &b, knn_handle_t h, hipStream_t s) {
     hipError_t e = hipSuccess;
     BTRY(launch_fill_u32(b.sh.nflag, (int64_t)b.parts.size(), 0u, s));
     if (b.sh.cnt_rows) BTRY(launch_sum_u32(b.sh.cnt_all, b.sh.cnt_rows, stats_ptr(h) + kStatCandidates, s));
-    for (size_t pi = 0; pi < b.parts.size(); ++pi) {
-        const BatchPart &pt = b.parts[pi];
-        const Plan &p = b.jobs[pt.job].p;
-        if (pt.direct) continue;
-        BTRY(launch_flag_rows(pt.cnt, pt.mb, (uint32_t)p.kk, (uint32_t)p.cap, b.force, b.sh.nflag + pi, pt.flags, s));
-    }
+    for (const SegClass &c : b.flags) BTRY(launch_flag_group(c, b.sh.flags, b.sh.flags_first, s));
     return hipMemcpyAsync(b.nflag_host, b.sh.nflag, b.parts.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s);
 }
 
-hipError_t enqueue_final(const BatchState &b, knn_handle_t h, int num_cu, hipStream_t s) {
+hipError_t enqueue_final(const BatchState &b, int num_cu, hipStream_t s) {
     hipError_t e = hipSuccess;
     // the kk smallest candidate keys of every filtered row, one launch
     if (b.keys_sel.rows) {
         SelectArgs ka = seg_select_args(b, b.keys_sel);
         BTRY(launch_select_keys(ka, num_cu, s));
     }
-    for (size_t pi = 0; pi < b.parts.size(); ++pi)
-        if (!b.parts[pi].direct) BTRY(certify_rerank(b, h, pi, b.parts[pi].sv, b.parts[pi].si, s));
+    for (const SegClass &c : b.certs) BTRY(launch_certify_group(c, b.sh.certs, b.sh.certs_first, s));
+    for (const SegClass &c : b.reranks) BTRY(launch_rerank_group(c, b.sh.reranks, b.sh.reranks_first, s));
     // the uncertified-row counts, for the exact re-run that follows
     return hipMemcpyAsync(b.nflag_host + b.parts.size(), b.sh.nu, b.parts.size() * sizeof(uint32_t),
                           hipMemcpyDeviceToHost, s);
@@ -612,7 +640,8 @@ hipError_t refinal_part(const BatchState &b, knn_handle_t h, int num_cu, size_t 
     ka.mode = b.smode;
     ka.net = b.smode == kPivotLearned ? b.net : nullptr;
     BTRY(launch_select_keys(ka, num_cu, s));
-    BTRY(certify_rerank(b, h, pi, pt.sv, pt.si, s));
+    if (part_certified(b, pt)) BTRY(launch_certify(certify_args(b, h, pi), s));
+    BTRY(launch_rerank(rerank_args(b, pi), s));
     return hipMemcpyAsync(b.nflag_host + b.parts.size() + pi, b.sh.nu + pi, sizeof(uint32_t), hipMemcpyDeviceToHost,
                           s);
 }
@@ -976,6 +1005,35 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
             KTRY(hipMemcpyAsync(L->drow_seg, L->row_seg.data(), L->row_seg.size() * sizeof(uint32_t),
                                 hipMemcpyHostToDevice, stream));
         }
+        std::vector<PrepSeg> preps = prep_segs(b);
+        std::vector<FlagSeg> flags;
+        std::vector<CertifyArgs> certs;
+        std::vector<RerankArgs> reranks;
+        for (size_t pi = 0; pi < b.parts.size(); ++pi) {
+            const BatchPart &pt = b.parts[pi];
+            const Plan &p = b.jobs[pt.job].p;
+            if (!pt.direct)
+                flags.push_back(FlagSeg{pt.cnt, pt.mb, (uint32_t)p.kk, (uint32_t)p.cap, b.force, b.sh.nflag + pi,
+                                        pt.flags});
+            if (part_certified(b, pt)) certs.push_back(certify_args(b, h, pi));
+            reranks.push_back(rerank_args(b, pi));
+        }
+        std::vector<uint32_t> fpreps, fflags, fcerts, freranks;
+        b.preps = group_prep(preps, fpreps);
+        b.flags = group_flags(flags, fflags);
+        b.certs = group_certify(certs, fcerts);
+        b.reranks = group_rerank(reranks, freranks);
+        auto upload_vec = [&](void *to, const void *from, size_t bytes) -> hipError_t {
+            return bytes ? hipMemcpyAsync(to, from, bytes, hipMemcpyHostToDevice, stream) : hipSuccess;
+        };
+        KTRY(upload_vec(b.sh.preps, preps.data(), preps.size() * sizeof(PrepSeg)));
+        KTRY(upload_vec(b.sh.flags, flags.data(), flags.size() * sizeof(FlagSeg)));
+        KTRY(upload_vec(b.sh.certs, certs.data(), certs.size() * sizeof(CertifyArgs)));
+        KTRY(upload_vec(b.sh.reranks, reranks.data(), reranks.size() * sizeof(RerankArgs)));
+        KTRY(upload_vec(b.sh.preps_first, fpreps.data(), fpreps.size() * sizeof(uint32_t)));
+        KTRY(upload_vec(b.sh.flags_first, fflags.data(), fflags.size() * sizeof(uint32_t)));
+        KTRY(upload_vec(b.sh.certs_first, fcerts.data(), fcerts.size() * sizeof(uint32_t)));
+        KTRY(upload_vec(b.sh.reranks_first, freranks.data(), freranks.size() * sizeof(uint32_t)));
         KTRY(hipStreamSynchronize(stream));  // the host vectors above are released at scope end
         KTRY(launch_fill_u32(reinterpret_cast<uint32_t *>(b.sh.ninf), 1, 0xFF800000u, stream));
         const int prec = b.jobs[0].p.prec;
@@ -1062,20 +1120,20 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
             // flagged for the exact fallback come out of it with provisional
             // results, re-done eagerly afterwards
             if (timed) {
-                ok = capture(b, [&](hipStream_t s) { return enqueue_prep(b, h, num_cu, s); }, &g) == hipSuccess;
+                ok = capture(b, [&](hipStream_t s) { return enqueue_prep(b, num_cu, s); }, &g) == hipSuccess;
                 if (ok) gs.push_back(g);
                 ok = ok && capture(b, [&](hipStream_t s) {
                                hipError_t ce = enqueue_flags(b, h, s);
-                               if (ce == hipSuccess) ce = enqueue_final(b, h, num_cu, s);
+                               if (ce == hipSuccess) ce = enqueue_final(b, num_cu, s);
                                return ce;
                            }, &g) == hipSuccess;
                 if (ok) gs.push_back(g);
             } else {
                 ok = capture(b, [&](hipStream_t s) {
-                         hipError_t ce = enqueue_prep(b, h, num_cu, s);
+                         hipError_t ce = enqueue_prep(b, num_cu, s);
                          if (ce == hipSuccess) ce = enqueue_product(b, b.sh.table, b.tile, b.queue, num_cu, s);
                          if (ce == hipSuccess) ce = enqueue_flags(b, h, s);
-                         if (ce == hipSuccess) ce = enqueue_final(b, h, num_cu, s);
+                         if (ce == hipSuccess) ce = enqueue_final(b, num_cu, s);
                          return ce;
                      }, &g) == hipSuccess;
                 if (ok) gs.push_back(g);
@@ -1098,12 +1156,12 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
     double flops = 0;
     for (const BatchJob &js : b.jobs) flops += js.cost;
     if (b.eager) {
-        KTRY(enqueue_prep(b, h, num_cu, stream));
+        KTRY(enqueue_prep(b, num_cu, stream));
         KTRY(timer.begin(stream, flops));
         KTRY(enqueue_product(b, b.sh.table, b.tile, b.queue, num_cu, stream));
         KTRY(timer.end(stream));
         KTRY(enqueue_flags(b, h, stream));
-        KTRY(enqueue_final(b, h, num_cu, stream));
+        KTRY(enqueue_final(b, num_cu, stream));
     } else if (timed) {
         KTRY(hipGraphLaunch(b.graphs[0], stream));
         KTRY(timer.begin(stream, flops));

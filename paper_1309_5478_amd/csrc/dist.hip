@@ -3,6 +3,9 @@
 // distances, reduced-precision operands, candidate bookkeeping, the
 // certificate, and the exact direct-form re-rank of the surviving candidates
 // (and of uncertified rows).  The product itself is in gemm.hip.
+#include <algorithm>
+#include <vector>
+
 #include <cstdlib>
 #include <cstring>
 #include "dist.hpp"
@@ -92,23 +95,29 @@ hipError_t launch_unit_rows(const float *X, int64_t n, int d, bool centre, float
 // order, then a fixed xor-shuffle tree over the G lanes.  With max_bits, the
 // largest norm (as FP32 bits; norms are non-negative) is folded into *max_bits
 // with one atomic per workgroup.
+// (src_n: the points are the n of src_n rows that source_row gives.)
+__device__ __forceinline__ int64_t source_row(int64_t i, int64_t n, int64_t src_n) {
+    return src_n ? (i * src_n) / n : i;
+}
+
 template <int G, bool VEC>
-__global__ __launch_bounds__(256) void sqnorm_kernel(const float *__restrict__ X, int64_t n, int d,
-                                                     float *__restrict__ out, unsigned int *__restrict__ max_bits) {
+__device__ __forceinline__ void sqnorm_body(const float *__restrict__ X, int64_t n, int64_t src_n, int d,
+                                            float *__restrict__ out, unsigned int *__restrict__ max_bits,
+                                            uint32_t block, uint32_t blocks) {
     constexpr int PPW = kWave / G;
     __shared__ float wmax[256 / kWave];
     const uint32_t lane = lane_id(), sub = lane % G, grp = lane / G, wave = threadIdx.x / kWave;
-    const int64_t stride = (int64_t)gridDim.x * (256 / kWave) * PPW;
+    const int64_t stride = (int64_t)blocks * (256 / kWave) * PPW;
     float mx = 0.f;
     // two points per group per step (independent loads in flight)
-    for (int64_t base = ((int64_t)blockIdx.x * (256 / kWave) + wave) * PPW; base < n; base += 2 * stride) {
+    for (int64_t base = ((int64_t)block * (256 / kWave) + wave) * PPW; base < n; base += 2 * stride) {
         float acc[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int64_t i = base + u * stride + grp;
             float s = 0.f;
             if (i < n) {
-                const float *x = X + i * d;
+                const float *x = X + source_row(i, n, src_n) * d;
                 if (VEC) {
                     for (int t = (int)sub * 4; t < d; t += G * 4) {
                         const f32x4 v = *reinterpret_cast<const f32x4 *>(x + t);
@@ -145,6 +154,12 @@ __global__ __launch_bounds__(256) void sqnorm_kernel(const float *__restrict__ X
     }
 }
 
+template <int G, bool VEC>
+__global__ __launch_bounds__(256) void sqnorm_kernel(const float *__restrict__ X, int64_t n, int d,
+                                                     float *__restrict__ out, unsigned int *__restrict__ max_bits) {
+    sqnorm_body<G, VEC>(X, n, 0, d, out, max_bits, blockIdx.x, gridDim.x);
+}
+
 // ---- FP32 operands as two FP16 halves ----------------------------------------
 // The point scaled by 2^e, its largest finite magnitude into [2^14, 2^15) (e in
 // [-113, 100]; 0 for a zero point), each element as h = FP16(x 2^e) and l =
@@ -154,20 +169,20 @@ __global__ __launch_bounds__(256) void sqnorm_kernel(const float *__restrict__ X
 // bytes read (the second pass over a row finds it in L1) and 4 d written per
 // point, against the d^2-fold work of the product it feeds.
 template <int G, bool VEC>
-__global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict__ X, int64_t n, int d,
-                                                         unsigned char *__restrict__ out, int64_t ldo,
-                                                         float *__restrict__ scale_out, float *__restrict__ norm,
-                                                         unsigned int *__restrict__ max_bits) {
+__device__ __forceinline__ void split_body(const float *__restrict__ X, int64_t n, int64_t src_n, int d,
+                                           unsigned char *__restrict__ out, int64_t ldo, float *__restrict__ scale_out,
+                                           float *__restrict__ norm, unsigned int *__restrict__ max_bits,
+                                           uint32_t block, uint32_t blocks) {
     constexpr int PPW = kWave / G;
     __shared__ float wmax[256 / kWave];
     const uint32_t lane = lane_id(), sub = lane % G, grp = lane / G, wave = threadIdx.x / kWave;
-    const int64_t stride = (int64_t)gridDim.x * (256 / kWave) * PPW;
+    const int64_t stride = (int64_t)blocks * (256 / kWave) * PPW;
     const int dp = (d + 31) / 32 * 32;
     float mx = 0.f;
-    for (int64_t base = ((int64_t)blockIdx.x * (256 / kWave) + wave) * PPW; base < n; base += stride) {
+    for (int64_t base = ((int64_t)block * (256 / kWave) + wave) * PPW; base < n; base += stride) {
         const int64_t i = base + grp;
         const bool in = i < n;
-        const float *x = X + (in ? i : n - 1) * d;
+        const float *x = X + source_row(in ? i : n - 1, n, src_n) * d;
         float s = 0.f, am = 0.f;
         auto see = [&](float v) {
             s = fmaf(v, v, s);
@@ -252,6 +267,14 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict
     }
 }
 
+template <int G, bool VEC>
+__global__ __launch_bounds__(256) void split_rows_kernel(const float *__restrict__ X, int64_t n, int64_t src_n, int d,
+                                                         unsigned char *__restrict__ out, int64_t ldo,
+                                                         float *__restrict__ scale_out, float *__restrict__ norm,
+                                                         unsigned int *__restrict__ max_bits) {
+    split_body<G, VEC>(X, n, src_n, d, out, ldo, scale_out, norm, max_bits, blockIdx.x, gridDim.x);
+}
+
 // Lanes per point or candidate for a row length d: the power of two covering
 // its 16-byte chunks (or its elements), at most a wave.
 static int lanes_for(int d, bool vec) {
@@ -278,16 +301,16 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restric
 // ---- candidate bookkeeping ----------------------------------------------------
 // Rows whose candidate count is below `need` or above `cap` are listed for the
 // exact fallback.
-__global__ __launch_bounds__(256) void flag_rows_kernel(const uint32_t *__restrict__ cnt, int64_t m, uint32_t need,
-                                                        uint32_t cap, int force, uint32_t *__restrict__ nflag,
-                                                        int32_t *__restrict__ flags) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const uint32_t c = cnt[i];
-    if (force || c < need || c > cap) {
-        uint32_t p = atomicAdd(nflag, 1u);
-        flags[p] = (int32_t)i;
+__device__ __forceinline__ void flag_body(const FlagSeg &a, int64_t i) {
+    if (i >= a.m) return;
+    const uint32_t c = a.cnt[i];
+    if (a.force || c < a.need || c > a.cap) {
+        uint32_t p = atomicAdd(a.nflag, 1u);
+        a.flags[p] = (int32_t)i;
     }
+}
+__global__ __launch_bounds__(256) void flag_rows_kernel(FlagSeg a) {
+    flag_body(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // Replaces the candidate lists of the flagged rows by the exact selection made
@@ -350,11 +373,10 @@ __device__ __forceinline__ float rerank_dist(const float *__restrict__ q, const 
 }
 
 template <int G, bool VEC>
-__global__ __launch_bounds__(kRerankThreads) void rerank_kernel(RerankArgs a) {
+__device__ __forceinline__ void rerank_body(const RerankArgs &a, int64_t i) {
     constexpr uint32_t PPW = kWave / G;                       // candidates per wave per pass
     constexpr uint32_t STEP = (kRerankThreads / kWave) * PPW;  // per workgroup per pass
     __shared__ uint64_t keys[kRerankMax];
-    const int64_t i = blockIdx.x;
     if (i >= a.m) return;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave, sub = lane % G, grp = lane / G;
     const float *q = a.Q + i * a.d;
@@ -411,6 +433,11 @@ __global__ __launch_bounds__(kRerankThreads) void rerank_kernel(RerankArgs a) {
     }
 }
 
+template <int G, bool VEC>
+__global__ __launch_bounds__(kRerankThreads) void rerank_kernel(RerankArgs a) {
+    rerank_body<G, VEC>(a, blockIdx.x);
+}
+
 // ---- reduced-precision operands ---------------------------------------------
 // OCP e4m3 (1 sign, 4 exponent bits with bias 7, 3 mantissa bits, no infinity),
 // round to nearest even, saturating at +-448 (also for infinities); a NaN
@@ -447,12 +474,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // amax the largest finite magnitude of the point (e = 0 without a finite
 // non-zero element; e limited to [-100, 100]), elements x * 2^e rounded to
 // e4m3, scale 2^-e.
-__global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ X, int64_t n, int d, int prec, int dq,
-                                                       void *__restrict__ out, float *__restrict__ scale_out) {
-    const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave;
-    if (i >= n) return;
+__device__ __forceinline__ void quantize_row(const float *__restrict__ X, int64_t n, int64_t src_n, int d, int prec,
+                                             int dq, void *__restrict__ out, float *__restrict__ scale_out, int64_t i) {
     const uint32_t lane = lane_id();
-    const float *x = X + i * d;
+    const float *x = X + source_row(i, n, src_n) * d;
     if (prec == kPrecBF16) {
         uint16_t *o = static_cast<uint16_t *>(out) + i * dq;
         for (int t = lane; t < dq; t += kWave) o[t] = t < d ? f32_to_bf16_rne(x[t]) : (uint16_t)0;
@@ -479,9 +504,15 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__
     if (lane == 0) scale_out[i] = ldexpf(1.0f, -e);
 }
 
+__global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ X, int64_t n, int64_t src_n, int d,
+                                                       int prec, int dq, void *__restrict__ out,
+                                                       float *__restrict__ scale_out) {
+    const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave;
+    if (i < n) quantize_row(X, n, src_n, d, prec, dq, out, scale_out, i);
+}
+
 // Per-row candidate certificate (see launch_certify in dist.hpp for the bound).
-__global__ __launch_bounds__(256) void certify_kernel(CertifyArgs a) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void certify_body(const CertifyArgs &a, int64_t i) {
     bool bad = false;
     if (i < a.m) {
         const float ak = a.sorted_keys[i * a.kk + a.k - 1];
@@ -498,6 +529,10 @@ __global__ __launch_bounds__(256) void certify_kernel(CertifyArgs a) {
     }
     const uint64_t b = __ballot(bad);
     if (lane_id() == 0 && b) atomicAdd(a.count, (unsigned long long)__popcll(b));
+}
+
+__global__ __launch_bounds__(256) void certify_kernel(CertifyArgs a) {
+    certify_body(a, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // ---- exact re-run of uncertified rows ------------------------------------------
@@ -601,12 +636,20 @@ __global__ __launch_bounds__(kFixThreads) void exact_rows_kernel(FixupArgs a) {
     }
 }
 
+// Workgroups for n points of G lanes each.
+static int64_t sqnorm_blocks(int64_t n, int G) {
+    const int64_t b = (n * G + 8 * kWave - 1) / (8 * kWave);
+    return b > 4096 ? 4096 : b;
+}
+static int64_t split_blocks(int64_t n, int G) {
+    const int64_t b = (n * G + 4 * kWave - 1) / (4 * kWave);
+    return b > 8192 ? 8192 : b;
+}
+
 template <int G>
 static void launch_sqnorm_g(const float *X, int64_t n, int d, float *out, unsigned int *max_bits, bool vec,
                             hipStream_t stream) {
-    constexpr int PPW = kWave / G;
-    int64_t blocks = (n + 8 * PPW - 1) / (8 * PPW);
-    if (blocks > 4096) blocks = 4096;
+    const int64_t blocks = sqnorm_blocks(n, G);
     if (vec)
         hipLaunchKernelGGL((sqnorm_kernel<G, true>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, out,
                            max_bits);
@@ -631,30 +674,28 @@ hipError_t launch_sqnorm(const float *X, int64_t n, int d, float *out, unsigned 
 }
 
 template <int G>
-static void launch_split_g(const float *X, int64_t n, int d, void *out, float *sc, float *norm, unsigned int *max_bits,
-                           bool vec, hipStream_t stream) {
-    constexpr int PPW = kWave / G;
-    int64_t blocks = (n + 4 * PPW - 1) / (4 * PPW);
-    if (blocks > 8192) blocks = 8192;
+static void launch_split_g(const float *X, int64_t n, int64_t src_n, int d, void *out, float *sc, float *norm,
+                           unsigned int *max_bits, bool vec, hipStream_t stream) {
+    const int64_t blocks = split_blocks(n, G);
     unsigned char *o = static_cast<unsigned char *>(out);
     const int64_t ldo = split_row_bytes(d);
     if (vec)
-        hipLaunchKernelGGL((split_rows_kernel<G, true>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, o, ldo,
-                           sc, norm, max_bits);
+        hipLaunchKernelGGL((split_rows_kernel<G, true>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, src_n,
+                           d, o, ldo, sc, norm, max_bits);
     else
-        hipLaunchKernelGGL((split_rows_kernel<G, false>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, o, ldo,
-                           sc, norm, max_bits);
+        hipLaunchKernelGGL((split_rows_kernel<G, false>), dim3((unsigned)blocks), dim3(256), 0, stream, X, n, src_n,
+                           d, o, ldo, sc, norm, max_bits);
 }
 
 hipError_t launch_split(const float *X, int64_t n, int d, void *out, float *scale_out, float *norm,
-                        unsigned int *max_bits, hipStream_t stream) {
+                        unsigned int *max_bits, hipStream_t stream, int64_t src_n) {
     if (n == 0) return hipSuccess;
     const bool vec = d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
     // (the lane grouping of launch_sqnorm, so that the norms are the same bits)
     switch (lanes_for(d, vec)) {
-        case 16: launch_split_g<16>(X, n, d, out, scale_out, norm, max_bits, vec, stream); break;
-        case 32: launch_split_g<32>(X, n, d, out, scale_out, norm, max_bits, vec, stream); break;
-        case 64: launch_split_g<64>(X, n, d, out, scale_out, norm, max_bits, vec, stream); break;
+        case 16: launch_split_g<16>(X, n, src_n, d, out, scale_out, norm, max_bits, vec, stream); break;
+        case 32: launch_split_g<32>(X, n, src_n, d, out, scale_out, norm, max_bits, vec, stream); break;
+        case 64: launch_split_g<64>(X, n, src_n, d, out, scale_out, norm, max_bits, vec, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -671,8 +712,8 @@ hipError_t launch_gather_rows(const float *src, int64_t n, int d, const int32_t 
 hipError_t launch_flag_rows(const uint32_t *cnt, int64_t m, uint32_t need, uint32_t cap, int force, uint32_t *nflag,
                             int32_t *flags, hipStream_t stream) {
     if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(flag_rows_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, stream, cnt, m, need, cap,
-                       force, nflag, flags);
+    hipLaunchKernelGGL(flag_rows_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, stream,
+                       FlagSeg{cnt, m, need, cap, force, nflag, flags});
     return hipGetLastError();
 }
 
@@ -685,11 +726,11 @@ hipError_t launch_scatter_fallback(const int32_t *rows, int64_t nrows, const flo
 }
 
 hipError_t launch_quantize(const float *X, int64_t n, int d, int prec, void *out, float *scale_out,
-                           hipStream_t stream) {
+                           hipStream_t stream, int64_t src_n) {
     if (n == 0) return hipSuccess;
     const int dq = (d + kQuantPad - 1) / kQuantPad * kQuantPad;
-    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream, X, n, d, prec, dq, out,
-                       scale_out);
+    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream, X, n, src_n, d, prec,
+                       dq, out, scale_out);
     return hipGetLastError();
 }
 
@@ -747,6 +788,219 @@ hipError_t launch_rerank(const RerankArgs &a, hipStream_t stream) {
         case 32: launch_rerank_g<32>(a, vec, stream); break;
         default: launch_rerank_g<64>(a, vec, stream); break;
     }
+    return hipGetLastError();
+}
+
+// ---- the same steps over many matrices in one launch ---------------------------
+// A batch has hundreds of matrices, most of them a few microseconds of work: a
+// launch each costs more than the work (96 jobs: 1100 launches, 0.4 to 0.5 ms of
+// every 4.5 us step, and the small ones leave most CUs idle).  One launch per
+// kernel instance instead: workgroup b finds its segment by a search over the
+// segments' first workgroups (uniform: scalar loads).
+__device__ __forceinline__ uint32_t segment_of(const uint32_t *__restrict__ first, uint32_t nseg, uint32_t b) {
+    uint32_t lo = 0, hi = nseg;  // first[lo] <= b < first[hi]
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (first[mid] <= b) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+template <int G, bool VEC>
+__global__ __launch_bounds__(256) void sqnorm_group_kernel(const PrepSeg *__restrict__ segs,
+                                                           const uint32_t *__restrict__ first, uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    const PrepSeg &a = segs[s];
+    sqnorm_body<G, VEC>(a.X, a.n, a.src_n, a.d, a.norm, a.max_bits, blockIdx.x - first[s], first[s + 1] - first[s]);
+}
+
+template <int G, bool VEC>
+__global__ __launch_bounds__(256) void split_group_kernel(const PrepSeg *__restrict__ segs,
+                                                          const uint32_t *__restrict__ first, uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    const PrepSeg &a = segs[s];
+    split_body<G, VEC>(a.X, a.n, a.src_n, a.d, static_cast<unsigned char *>(a.out), (int64_t)((a.d + 31) / 32) * 128,
+                       a.scale, a.norm, a.max_bits, blockIdx.x - first[s], first[s + 1] - first[s]);
+}
+
+__global__ __launch_bounds__(256) void quantize_group_kernel(const PrepSeg *__restrict__ segs,
+                                                             const uint32_t *__restrict__ first, uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    const PrepSeg &a = segs[s];
+    const int dq = (a.d + kQuantPad - 1) / kQuantPad * kQuantPad;
+    const int64_t step = (int64_t)(first[s + 1] - first[s]) * 4;
+    for (int64_t i = (int64_t)(blockIdx.x - first[s]) * 4 + threadIdx.x / kWave; i < a.n; i += step)
+        quantize_row(a.X, a.n, a.src_n, a.d, a.prec, dq, a.out, a.scale, i);
+}
+
+__global__ __launch_bounds__(256) void gather_group_kernel(const PrepSeg *__restrict__ segs,
+                                                           const uint32_t *__restrict__ first, uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    const PrepSeg &a = segs[s];
+    const int64_t i = (int64_t)(blockIdx.x - first[s]) * 4 + threadIdx.x / kWave;
+    if (i >= a.n) return;
+    const float *x = a.X + source_row(i, a.n, a.src_n) * a.d;
+    float *o = static_cast<float *>(a.out) + i * a.d;
+    for (int c = (int)lane_id(); c < a.d; c += kWave) o[c] = x[c];
+}
+
+__global__ __launch_bounds__(256) void flag_group_kernel(const FlagSeg *__restrict__ segs,
+                                                         const uint32_t *__restrict__ first, uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    flag_body(segs[s], (int64_t)(blockIdx.x - first[s]) * 256 + threadIdx.x);
+}
+
+__global__ __launch_bounds__(256) void certify_group_kernel(const CertifyArgs *__restrict__ segs,
+                                                            const uint32_t *__restrict__ first, uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    certify_body(segs[s], (int64_t)(blockIdx.x - first[s]) * 256 + threadIdx.x);
+}
+
+template <int G, bool VEC>
+__global__ __launch_bounds__(kRerankThreads) void rerank_group_kernel(const RerankArgs *__restrict__ segs,
+                                                                      const uint32_t *__restrict__ first,
+                                                                      uint32_t nseg) {
+    const uint32_t s = segment_of(first, nseg, blockIdx.x);
+    rerank_body<G, VEC>(segs[s], blockIdx.x - first[s]);
+}
+
+namespace {
+
+// Sorts the segments by class, and lists the classes and the segments' first
+// workgroups (each class's from 0, with its end; at most 2^30 workgroups a class).
+template <class Seg, class ClassOf, class BlocksOf>
+std::vector<SegClass> group_segments(std::vector<Seg> &segs, std::vector<uint32_t> &first, ClassOf class_of,
+                                     BlocksOf blocks_of) {
+    std::stable_sort(segs.begin(), segs.end(), [&](const Seg &x, const Seg &y) { return class_of(x) < class_of(y); });
+    std::vector<SegClass> out;
+    first.clear();
+    int64_t total = 0;
+    for (size_t i = 0; i < segs.size(); ++i) {
+        const int c = class_of(segs[i]);
+        const int64_t nb = blocks_of(segs[i]);
+        if (out.empty() || out.back().key != c || total + nb > (1 << 30)) {
+            if (!out.empty()) first.push_back((uint32_t)total);
+            out.push_back(SegClass{c, (uint32_t)i, 0, (uint32_t)first.size(), 0});
+            total = 0;
+        }
+        first.push_back((uint32_t)total);
+        total += nb;
+        out.back().nseg += 1;
+        out.back().blocks = (uint32_t)total;
+    }
+    if (!out.empty()) first.push_back((uint32_t)total);
+    return out;
+}
+
+bool vec_rows(const float *X, int d) { return d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0; }
+
+// A class: the step, the lanes per row (or one class for all) and 16-byte loads.
+int prep_class(const PrepSeg &a) {
+    if (a.kind == kPrepQuant || a.kind == kPrepGather) return a.kind * 256;
+    const bool vec = vec_rows(a.X, a.d);
+    return a.kind * 256 + lanes_for(a.d, vec) * 2 + vec;
+}
+
+}  // namespace
+
+std::vector<SegClass> group_prep(std::vector<PrepSeg> &segs, std::vector<uint32_t> &first) {
+    return group_segments(segs, first, prep_class, [](const PrepSeg &a) -> int64_t {
+        const int G = prep_class(a) % 256 / 2;
+        if (a.kind == kPrepNorm) return sqnorm_blocks(a.n, G);
+        if (a.kind == kPrepSplit) return split_blocks(a.n, G);
+        const int64_t b = (a.n + 3) / 4;
+        return a.kind == kPrepQuant && b > 65536 ? 65536 : b;
+    });
+}
+
+std::vector<SegClass> group_rerank(std::vector<RerankArgs> &segs, std::vector<uint32_t> &first) {
+    return group_segments(
+        segs, first,
+        [](const RerankArgs &a) {
+            const bool vec = vec_rows(a.Q, a.d) && vec_rows(a.C, a.d);
+            return lanes_for(a.d, vec) * 2 + (int)vec;
+        },
+        [](const RerankArgs &a) { return a.m; });
+}
+
+std::vector<SegClass> group_flags(std::vector<FlagSeg> &segs, std::vector<uint32_t> &first) {
+    return group_segments(
+        segs, first, [](const FlagSeg &) { return 0; }, [](const FlagSeg &a) { return (a.m + 255) / 256; });
+}
+
+std::vector<SegClass> group_certify(std::vector<CertifyArgs> &segs, std::vector<uint32_t> &first) {
+    return group_segments(
+        segs, first, [](const CertifyArgs &) { return 0; }, [](const CertifyArgs &a) { return (a.m + 255) / 256; });
+}
+
+// One instance per (lanes, 16-byte loads).
+#define KNN_LANES_CASE(KERNEL, G)                                                                              \
+    case 2 * G: hipLaunchKernelGGL((KERNEL<G, false>), g, b, 0, stream, s, f, c.nseg); break;                   \
+    case 2 * G + 1: hipLaunchKernelGGL((KERNEL<G, true>), g, b, 0, stream, s, f, c.nseg); break;
+
+hipError_t launch_prep_group(const SegClass &c, const PrepSeg *segs, const uint32_t *first, hipStream_t stream) {
+    if (c.blocks == 0) return hipSuccess;
+    const dim3 g(c.blocks), b(256);
+    const PrepSeg *s = segs + c.seg0;
+    const uint32_t *f = first + c.first0;
+    const int kind = c.key / 256, inst = c.key % 256;
+    if (kind == kPrepQuant) {
+        hipLaunchKernelGGL(quantize_group_kernel, g, b, 0, stream, s, f, c.nseg);
+    } else if (kind == kPrepGather) {
+        hipLaunchKernelGGL(gather_group_kernel, g, b, 0, stream, s, f, c.nseg);
+    } else if (kind == kPrepSplit) {
+        switch (inst) {
+            KNN_LANES_CASE(split_group_kernel, 16)
+            KNN_LANES_CASE(split_group_kernel, 32)
+            KNN_LANES_CASE(split_group_kernel, 64)
+            default: return hipErrorInvalidValue;
+        }
+    } else {
+        switch (inst) {
+            KNN_LANES_CASE(sqnorm_group_kernel, 1)
+            KNN_LANES_CASE(sqnorm_group_kernel, 2)
+            KNN_LANES_CASE(sqnorm_group_kernel, 4)
+            KNN_LANES_CASE(sqnorm_group_kernel, 8)
+            KNN_LANES_CASE(sqnorm_group_kernel, 16)
+            KNN_LANES_CASE(sqnorm_group_kernel, 32)
+            KNN_LANES_CASE(sqnorm_group_kernel, 64)
+            default: return hipErrorInvalidValue;
+        }
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_rerank_group(const SegClass &c, const RerankArgs *segs, const uint32_t *first, hipStream_t stream) {
+    if (c.blocks == 0) return hipSuccess;
+    const dim3 g(c.blocks), b(kRerankThreads);
+    const RerankArgs *s = segs + c.seg0;
+    const uint32_t *f = first + c.first0;
+    switch (c.key) {
+        KNN_LANES_CASE(rerank_group_kernel, 1)
+        KNN_LANES_CASE(rerank_group_kernel, 2)
+        KNN_LANES_CASE(rerank_group_kernel, 4)
+        KNN_LANES_CASE(rerank_group_kernel, 8)
+        KNN_LANES_CASE(rerank_group_kernel, 16)
+        KNN_LANES_CASE(rerank_group_kernel, 32)
+        KNN_LANES_CASE(rerank_group_kernel, 64)
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+#undef KNN_LANES_CASE
+
+hipError_t launch_flag_group(const SegClass &c, const FlagSeg *segs, const uint32_t *first, hipStream_t stream) {
+    if (c.blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(flag_group_kernel, dim3(c.blocks), dim3(256), 0, stream, segs + c.seg0, first + c.first0, c.nseg);
+    return hipGetLastError();
+}
+
+hipError_t launch_certify_group(const SegClass &c, const CertifyArgs *segs, const uint32_t *first,
+                                hipStream_t stream) {
+    if (c.blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(certify_group_kernel, dim3(c.blocks), dim3(256), 0, stream, segs + c.seg0, first + c.first0,
+                       c.nseg);
     return hipGetLastError();
 }
 

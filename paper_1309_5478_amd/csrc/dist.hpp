@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace knn {
 
 enum : int { kEpiDense = 0, kEpiFilter = 1 };
@@ -158,8 +160,9 @@ hipError_t launch_sqnorm(const float *X, int64_t n, int d, float *out, unsigned 
 // The two-half operands of n rows of d floats (rows of split_row_bytes(d) bytes)
 // with their scales 2^-e, and in the same read the squared norms (norm and
 // max_bits as launch_sqnorm's, the same bits; norm may be null).  d >= 64.
+// With src_n the n points are rows floor(i src_n / n) of src_n rows.
 hipError_t launch_split(const float *X, int64_t n, int d, void *out, float *scale_out, float *norm,
-                        unsigned int *max_bits, hipStream_t stream);
+                        unsigned int *max_bits, hipStream_t stream, int64_t src_n = 0);
 hipError_t launch_gather_rows(const float *src, int64_t n, int d, const int32_t *idx, int64_t rows, float *dst,
                               const float *norms, float *dst_norms, hipStream_t stream);
 hipError_t launch_flag_rows(const uint32_t *cnt, int64_t m, uint32_t need, uint32_t cap, int force, uint32_t *nflag,
@@ -171,7 +174,7 @@ hipError_t launch_rerank(const RerankArgs &a, hipStream_t stream);
 // power-of-two scale (prec 2) into rows of dq = round_up(d, kQuantPad)
 // elements; scale_out (FP8 only) receives 2^-e per row.
 hipError_t launch_quantize(const float *X, int64_t n, int d, int prec, void *out, float *scale_out,
-                           hipStream_t stream);
+                           hipStream_t stream, int64_t src_n = 0);
 // Per-row certificate of a candidate list.  The reduced key of column j,
 // ||c_j||^2 - 2 q_i.c_j, is computed with an error of at most
 //   E_i = (gamma + 2u) max ||c||^2 + 2 (rel + 2u) ||q_i|| max ||c||
@@ -227,5 +230,47 @@ hipError_t launch_fixup(const FixupArgs &a, hipStream_t stream);
 // norm, into out (n x d FP32).  A row without a direction (zero or non-finite
 // norm after centring; a constant row for Pearson) becomes all NaN.
 hipError_t launch_unit_rows(const float *X, int64_t n, int d, bool centre, float *out, hipStream_t stream);
+
+// ---- the same steps over many matrices in one launch (batches) -----------------
+enum : int { kPrepNorm = 0, kPrepSplit = 1, kPrepQuant = 2, kPrepGather = 3 };
+// One matrix of a preparation step: its n rows, or (src_n > 0) rows
+// floor(i src_n / n) of its src_n.  Norms (launch_sqnorm), two-half operands with
+// norms (launch_split), quantised rows (launch_quantize), or copied rows.
+struct PrepSeg {
+    int kind;
+    const float *X;
+    int64_t n, src_n;
+    int d, prec;
+    void *out;
+    float *scale, *norm;
+    unsigned int *max_bits;
+};
+// One matrix of launch_flag_rows.
+struct FlagSeg {
+    const uint32_t *cnt;
+    int64_t m;
+    uint32_t need, cap;
+    int force;
+    uint32_t *nflag;
+    int32_t *flags;
+};
+// The segments of one launch: nseg from seg0 on, their first workgroups (and the
+// end) from first0 on.
+struct SegClass {
+    int key;
+    uint32_t seg0, nseg, first0, blocks;
+};
+// Classes of a list of segments (sorted by class in place) and the first
+// workgroups: at most segments + classes entries.  Rows are taken as aligned as
+// their pointers are.
+std::vector<SegClass> group_prep(std::vector<PrepSeg> &segs, std::vector<uint32_t> &first);
+std::vector<SegClass> group_rerank(std::vector<RerankArgs> &segs, std::vector<uint32_t> &first);
+std::vector<SegClass> group_flags(std::vector<FlagSeg> &segs, std::vector<uint32_t> &first);
+std::vector<SegClass> group_certify(std::vector<CertifyArgs> &segs, std::vector<uint32_t> &first);
+// Their launches; segs and first are the lists in device memory.
+hipError_t launch_prep_group(const SegClass &c, const PrepSeg *segs, const uint32_t *first, hipStream_t stream);
+hipError_t launch_rerank_group(const SegClass &c, const RerankArgs *segs, const uint32_t *first, hipStream_t stream);
+hipError_t launch_flag_group(const SegClass &c, const FlagSeg *segs, const uint32_t *first, hipStream_t stream);
+hipError_t launch_certify_group(const SegClass &c, const CertifyArgs *segs, const uint32_t *first, hipStream_t stream);
 
 }  // namespace knn

@@ -260,15 +260,15 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     const void *Csq = Cq;
     const float *css = csc;
     if (p.gathered) {
-        KNN_TRY(launch_gather_rows(C, n, d, nullptr, p.S, b.Cs, b.cnorm, b.csn, stream));
-        Cs = b.Cs;
         csn = b.csn;
-        if (p.prec != kPrecF32) {
-            KNN_TRY(launch_quantize(b.Cs, p.S, d, p.prec, b.Csq, b.css, stream));
-            Csq = b.Csq;
-            css = b.css;
-        } else if (p.split) {
-            KNN_TRY(launch_split(b.Cs, p.S, d, b.Csq, b.css, nullptr, nullptr, stream));
+        if (p.split) {
+            KNN_TRY(launch_split(C, p.S, d, b.Csq, b.css, b.csn, nullptr, stream, n));
+        } else {
+            KNN_TRY(launch_gather_rows(C, n, d, nullptr, p.S, b.Cs, b.cnorm, b.csn, stream));
+            Cs = b.Cs;
+            if (p.prec != kPrecF32) KNN_TRY(launch_quantize(b.Cs, p.S, d, p.prec, b.Csq, b.css, stream));
+        }
+        if (p.split || p.prec != kPrecF32) {
             Csq = b.Csq;
             css = b.css;
         }
@@ -326,6 +326,8 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         if (p.split && ftile != kTilePipe) {  // an FP32 tile is faster here
             p.split = false;
             p.rel = p.gamma;
+            KNN_TRY(launch_gather_rows(C, n, d, nullptr, p.S, b.Cs, b.cnorm, b.csn, stream));
+            Cs = b.Cs;
             if (!graph) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
         }
     }
