@@ -26,9 +26,8 @@
 //    the fastest of the candidates, timed on the batch itself with a threshold
 //    of -inf (nothing is kept, so the timing run has no effect on the results).
 // Jobs with more than kRowBlock queries are split into parts of at most that
-// many rows; each part has its own candidate lists.  Jobs whose threshold
-// sample is their whole corpus are finished in the first phase, as in
-// knn_search.
+// many rows; each part has its own candidate lists.  Parts whose threshold
+// sample is their whole corpus have no product but the sample's.
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>

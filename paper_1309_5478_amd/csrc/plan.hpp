@@ -384,16 +384,21 @@ inline Plan make_plan(int64_t m, int64_t n, int d, int k, bool graph, const knn_
         // they save: with a small expected sample rank the margin above it lets
         // several kk through.  A kept candidate (its slot reservation and key
         // write in the product, its share of the candidate selection) costs
-        // about 0.19 ns of the device (measured on the 2^20 x 256 BF16 graph);
-        // a sample column costs, per row, its share of the sample product
-        // (2 d flops) and a written and re-read distance.  Short reduced-
-        // precision rows gain (2^20 x 256 BF16, kk = 256: 8192 -> 16384
-        // columns, 1536 -> 1024 candidates per row expected, 1544 -> 1038
-        // measured); long FP32 rows keep theirs.
+        // about 0.19 ns of the device with the tiles of gemm.hip (measured on
+        // the 2^20 x 256 BF16 graph), 0.048 with the pipelined product; a
+        // sample column costs, per row, its share of the sample product (2 d
+        // flops) and a written and re-read distance, and above 8192 columns of
+        // a selection that fewer rows share a CU for.  Pipelined, d = 256,
+        // 262144 points, ms at 2048 / 4096 / 8192 / 16384 columns: FP8 kk = 256 53.0 /
+        // 49.5 / 47.8 / 50.5, kk = 64 40.7 / 36.9 / 34.9 / 37.2, BF16 kk = 256 62.7 / 59.9 /
+        // 59.4 / 62.3; 131072 x 1024, kk = 128: BF16 48.2 / 47.7 / 48.9 / 51.9, FP8 30.6 /
+        // 30.0 / 30.7 / 33.5; FP32 131072 x 128, kk = 64 15.9 / 15.7 / 15.4 / 17.2.
         {
-            const double t_keep = 1.9e-10;
-            const double t_col = 2.0 * d / (p.prec == kPrecF32 ? 1.25e14 : 6.0e14) + 2.0e-12;
+            const bool pipe = pipe_fills(m, n) && (p.prec != kPrecF32 || (d >= 64 && m >= 128));
+            const double t_keep = pipe ? 4.8e-11 : 1.9e-10;
+            const double flops = p.prec != kPrecF32 ? (pipe ? 8.0e14 : 6.0e14) : (pipe ? 4.2e14 : 1.25e14);
             while (2 * S <= kSampleColsMax && 2 * S < n) {
+                const double t_col = 2.0 * d / flops + (pipe ? (S < 8192 ? 3.0e-13 : 1.3e-12) : 2.0e-12);
                 double e2 = 0;
                 rank_for(2 * S, e2);
                 if (2.0 * e2 > kSelectKeysCap) break;
