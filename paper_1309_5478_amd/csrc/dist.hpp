@@ -150,6 +150,11 @@ inline int few_passes(int64_t m, int d) {
 }
 hipError_t launch_dist_few(const float *Q, int64_t m, const float *C, int64_t n, int d, float *out, float *qnorm2,
                            unsigned int *max_bits, int num_cu, hipStream_t stream);
+// The product with resident query rows for BF16 / FP8 rows of at most 256 bytes
+// and the FILTER epilogue (gemm_rows.hip): whether it serves `a`
+// (KNN_GEMM_ROWS=0 turns it off), and its launch.
+bool gemm_rows_applies(const DistArgs &a, int epi);
+hipError_t launch_dist_gemm_rows(const DistArgs &a, hipStream_t stream);
 // Compute units of the current device.
 int device_cus();
 // Tile shape launch_dist_gemm uses for `a` (kTile*).

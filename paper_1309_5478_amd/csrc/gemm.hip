@@ -426,6 +426,8 @@ int gemm_tile_choice(const DistArgs &a) {
 
 hipError_t launch_dist_gemm(const DistArgs &a, int epi, hipStream_t stream) {
     if (a.m == 0 || a.n == 0) return hipSuccess;
+    // short reduced-precision rows: the product with resident rows (gemm_rows.hip)
+    if (gemm_rows_applies(a, epi)) return launch_dist_gemm_rows(a, stream);
     // enough work for 256 x 256 tiles: the pipelined product (gemm_pipe.hip)
     if (gemm_pipe_applies(a, epi)) return launch_dist_gemm_pipe(a, epi, stream);
     switch (gemm_tile_choice(a)) {

@@ -36,10 +36,11 @@
 // to the rows, a lane per key so that the slot reservations (global atomics) are
 // in flight together, when it is half full or the wave's rows change: a
 // workgroup's tiles follow each other along a row tile, so most tiles pass
-// without touching memory.  For short rows this path is the bound: the overflow
+// without touching memory (four keys per lane at a time: 3.60 -> 3.44 ms below).  For short rows this path is the bound: the overflow
 // branch, 128 times inline as first written, took 1.3 of 4.1 ms (FP8, 32768 x
 // 262144, d = 256, 554 keys kept per row) in instruction fetch alone; with the
-// test once per four registers, marked unlikely, 3.6 ms (2.6 with no key kept).
+// test once per four registers, marked unlikely, 3.6 ms (2.6 with no key kept;
+// gemm_rows.hip takes the largest of these).
 // Nothing in front of a tile's first products waits for its thresholds, norms
 // and scales (2.70 -> 2.55 ms with no key kept).
 //
@@ -345,14 +346,27 @@ __global__ __launch_bounds__(kPipeThreads, 2) void dist_pipe_kernel(DistArgs one
             uint2 *const mine = list[wave];
             auto drain = [&]() {
                 __builtin_amdgcn_wave_barrier();
-                for (uint32_t p = lane; p < kept; p += kWave) {
-                    const uint2 e = mine[p];
-                    const uint32_t row = gr0 + (e.y >> kListColBits);
-                    const uint32_t col = (uint32_t)a.col_base + list_col0 + (e.y & ((1u << kListColBits) - 1));
-                    if (a.self_offset >= 0 && (int64_t)col == a.self_offset + row) continue;  // own point
-                    const uint32_t slot = atomicAdd(&a.cnt[row], 1u);
-                    if (slot < (uint32_t)a.cap)
-                        a.cand[(size_t)row * a.cap + slot] = key_of(ord32_not_nan(__uint_as_float(e.x)), col);
+                // four keys per lane at a time: their slots are asked for together
+                for (uint32_t p0 = 0; p0 < kept; p0 += 4 * kWave) {
+                    uint32_t slot[4], row[4], col[4];
+                    float v[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const uint32_t p = p0 + x * kWave + lane;
+                        slot[x] = 0xffffffffu;
+                        if (p < kept) {
+                            const uint2 e = mine[p];
+                            v[x] = __uint_as_float(e.x);
+                            row[x] = gr0 + (e.y >> kListColBits);
+                            col[x] = (uint32_t)a.col_base + list_col0 + (e.y & ((1u << kListColBits) - 1));
+                            if (a.self_offset < 0 || (int64_t)col[x] != a.self_offset + row[x])  // (not its own point)
+                                slot[x] = atomicAdd(&a.cnt[row[x]], 1u);
+                        }
+                    }
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        if (slot[x] < (uint32_t)a.cap)
+                            a.cand[(size_t)row[x] * a.cap + slot[x]] = key_of(ord32_not_nan(v[x]), col[x]);
                 }
                 __builtin_amdgcn_wave_barrier();
                 kept = 0;

@@ -57,11 +57,15 @@ def points(kind, n, d, seed):
 
 def both(env, off, fn):
     a = fn()
+    was = os.environ.get(env)
     os.environ[env] = off
     try:
         b = fn()
     finally:
-        del os.environ[env]
+        if was is None:
+            del os.environ[env]
+        else:
+            os.environ[env] = was
     return a, b
 
 
@@ -179,3 +183,23 @@ def test_batch_low_precision_matches_small_tiles(torch, prec):
     a, b = both("KNN_GEMM_PIPE", "0", lambda: knn.Handle(0).batch_search(jobs, precision=prec))
     for x, y in zip(a, b):
         same(x, y)
+
+
+# resident rows: row tiles of 512 (remainders, fewer rows than a wave's), an XCD
+# without columns, column remainders, both row lengths and a half-used one, lists
+# that overflow in a step (kk = 1024 of 3000), d at the ends of each form
+@pytest.mark.parametrize("prec,d", [("fp8", 128), ("fp8", 129), ("fp8", 256), ("fp8", 20), ("bf16", 64), ("bf16", 65),
+                                    ("bf16", 128), ("bf16", 17)])
+@pytest.mark.parametrize("m,n,k", [(513, 20011, 7), (40, 3000, 256), (5003, 2100, 60), (0, 9001, 12)])
+def test_resident_rows_match_tiles(h, torch, prec, d, m, n, k):
+    print(f"rows {prec} {m}x{n}x{d} k={k}", flush=True)
+    C = points("scales" if d == 129 else "gmm", n, d, 41)
+    Q = torch.from_numpy(points("gmm", m, d, 42)).cuda()
+    C = torch.from_numpy(C).cuda()
+    run = (lambda: h.search(Q, C, k, precision=prec)) if m else (lambda: h.graph(C, k, precision=prec))
+    os.environ["KNN_GEMM_ROWS"] = "1"
+    try:
+        a, b = both("KNN_GEMM_ROWS", "0", run)
+    finally:
+        os.environ.pop("KNN_GEMM_ROWS", None)
+    same(a, b)
