@@ -69,6 +69,7 @@ void batch_release(knn_handle_t h);
 knn_status_t fail_msg(knn_handle_t h, knn_status_t s, const std::string &msg) { return fail(h, s, msg); }
 uint32_t *host_counter(knn_handle_t h) { return h->pinned; }
 unsigned long long *stats_ptr(knn_handle_t h) { return h->stats_dev; }
+uint32_t *search_words(knn_handle_t h) { return reinterpret_cast<uint32_t *>(h->stats_dev + kStatCount); }
 int handle_num_cu(knn_handle_t h) { return h->num_cu; }
 const uint16_t *handle_net(knn_handle_t h) { return h->has_net ? h->net_bf16 : nullptr; }
 void add_host_stats(knn_handle_t h, int64_t rows, int64_t fallback_rows) {
@@ -166,7 +167,8 @@ knn_status_t knn_create(knn_handle_t *out, int device) {
     h->scratch = scr;
     h->num_cu = prop.multiProcessorCount;
     h->arch = arch;
-    if ((e = hipMalloc(&h->stats_dev, kStatCount * sizeof(unsigned long long))) != hipSuccess) {
+    if ((e = hipMalloc(&h->stats_dev, kStatCount * sizeof(unsigned long long) + kWordCount * sizeof(uint32_t))) !=
+        hipSuccess) {
         delete h;
         return hip_fail(nullptr, e, "hipMalloc(stats)");
     }
@@ -176,7 +178,7 @@ knn_status_t knn_create(knn_handle_t *out, int device) {
         delete h;
         return hip_fail(nullptr, e, "hipMalloc(selection totals)");
     }
-    if ((e = hipHostMalloc(&h->pinned, sizeof(uint32_t), hipHostMallocDefault)) != hipSuccess) {
+    if ((e = hipHostMalloc(&h->pinned, kWordCount * sizeof(uint32_t), hipHostMallocDefault)) != hipSuccess) {
         hipFree(h->stats_dev);
         hipFree(h->slots_dev);
         delete h;
@@ -211,8 +213,10 @@ knn_status_t knn_destroy(knn_handle_t h) {
 // counters (nothing to clear: each workgroup writes its own); 0 for other calls.
 static knn_status_t begin_stats(knn_handle_t h, hipStream_t stream, int slots = 0) {
     if (slots == 0) {
-        hipError_t e = launch_zero_u64(h->stats_dev, kStatCount, stream);
+        static_assert(kWordCount % 2 == 0, "whole 64-bit words");
+        hipError_t e = launch_zero_u64(h->stats_dev, kStatCount + kWordCount / 2, stream);
         if (e != hipSuccess) return hip_fail(h, e, "stats reset");
+        h->words_clear = true;
     }
     h->last_slots = slots;
     h->last_stream = stream;
@@ -543,7 +547,8 @@ knn_status_t knn_get_stats(knn_handle_t h, knn_stats_t *out) {
         t.product_ms = h->host_product_ms;
         t.product_flops = h->host_product_flops;
         t.product_launches = h->host_product_launches;
-        t.rows_uncertified = (int64_t)s[kStatUncertified];
+        // (FP32 rows without a certificate are the ones re-run)
+        t.rows_uncertified = (int64_t)s[kStatUncertified] + h->host_rerun;
         t.rows_rerun = h->host_rerun;
         t.candidates_total = (int64_t)s[kStatCandidates];
         t.phase_cycles[0] = (int64_t)s[kStatCycSample];

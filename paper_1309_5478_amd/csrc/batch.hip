@@ -51,7 +51,6 @@ void add_host_rerun(knn_handle_t h, int64_t rows);
 int handle_num_cu(knn_handle_t h);
 const uint16_t *handle_net(knn_handle_t h);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream);
-hipError_t launch_sum_u32(const uint32_t *p, int64_t n, unsigned long long *out, hipStream_t stream);
 knn_status_t ensure_unit_ws(knn_handle_t h, size_t bytes, hipStream_t stream, void **out);
 knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *C, int64_t n, int d, int k, bool graph,
                         float *out_dist, int32_t *out_idx, hipStream_t stream, const knn_options_t *opt);
@@ -116,6 +115,8 @@ struct BatchShared {
     void *selws = nullptr;
     size_t selws_bytes = 0;
     float *ninf = nullptr;
+    uint32_t *zeros = nullptr;    // cmax2, nflag, nu and cnt_all, cleared by each call
+    int64_t nzeros = 0;
     uint32_t *cnt_all = nullptr;  // the candidate counts of all parts, contiguous
     int64_t cnt_rows = 0;
     DistArgs *table = nullptr, *probe = nullptr, *stable = nullptr;
@@ -316,7 +317,18 @@ constexpr size_t kPrepSegs = 7;  // preparation segments of a job, at most
 // each phase can run as one launch over all parts.
 size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
     BatchShared &s = b.sh;
-    s.cmax2 = c.take<unsigned int>(b.jobs.size());
+    // everything that a call starts from zero
+    int64_t cnt_rows = 0;
+    for (const BatchPart &pt : b.parts)
+        if (!pt.direct) cnt_rows += pt.mb;
+    const size_t njobs = b.jobs.size(), nparts = b.parts.size();
+    s.nzeros = (int64_t)(njobs + 2 * nparts) + cnt_rows;
+    s.zeros = c.take<uint32_t>((size_t)s.nzeros);
+    s.cmax2 = s.zeros;
+    s.nflag = s.zeros ? s.zeros + njobs : nullptr;
+    s.nu = s.zeros ? s.nflag + nparts : nullptr;
+    s.cnt_all = s.zeros ? s.nu + nparts : nullptr;
+    s.cnt_rows = cnt_rows;
     for (size_t j = 0; j < b.jobs.size(); ++j) b.jobs[j].cmax2 = s.cmax2 ? s.cmax2 + j : nullptr;
     size_t qf = 0, df = 0, fv = 0, qfq = 0, fb = 0, selws = 0;
     for (BatchJob &js : b.jobs) {
@@ -355,11 +367,6 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
         const int cap2 = select_cap_for_k(p.kk);
         selws = std::max(selws, select_ws_bytes(cap2, (uint32_t)js.n, select_grid(cap2, p.Fb, num_cu)));
     }
-    int64_t cnt_rows = 0;
-    for (const BatchPart &pt : b.parts)
-        if (!pt.direct) cnt_rows += pt.mb;
-    s.cnt_all = c.take<uint32_t>((size_t)std::max<int64_t>(cnt_rows, 1));
-    s.cnt_rows = cnt_rows;
     int64_t cnt_off = 0;
     for (BatchPart &pt : b.parts) {
         const Plan &p = b.jobs[pt.job].p;
@@ -413,8 +420,6 @@ size_t carve_batch(Carve &c, BatchState &b, int num_cu, bool probe) {
             b.npitems += (size_t)((pt.mb + kPipeTileDim - 1) / kPipeTileDim) *
                          (size_t)((b.jobs[pt.job].n + kPipeTileDim - 1) / kPipeTileDim);
     s.pitems = c.take<GemmItem>(std::max<size_t>(b.npitems, 1));
-    s.nflag = c.take<uint32_t>(b.parts.size());
-    s.nu = c.take<uint32_t>(b.parts.size());
     s.queues = c.take<uint32_t>(8);
     const size_t np = kPrepSegs * b.jobs.size(), parts = b.parts.size();
     s.preps = c.take<PrepSeg>(np);
@@ -515,6 +520,10 @@ RerankArgs rerank_args(const BatchState &b, size_t pi) {
         rr.cmax2_bits = js.cmax2;
         rr.rel = p.rel;
         rr.gamma = p.gamma;
+        rr.ulist = pt.ulist;
+        rr.nu = b.sh.nu + pi;
+        rr.tfix = pt.tfix;
+        rr.force = p.force_rerun;
     }
     return rr;
 }
@@ -555,8 +564,7 @@ hipError_t enqueue_prep(const BatchState &b, int num_cu, hipStream_t s) {
     do {                                           \
         if ((e = (call)) != hipSuccess) return e;  \
     } while (0)
-    BTRY(launch_fill_u32(sh.nu, (int64_t)b.parts.size(), 0u, s));
-    BTRY(launch_fill_u32(sh.cmax2, (int64_t)b.jobs.size(), 0u, s));
+    BTRY(launch_fill_u32(sh.zeros, sh.nzeros, 0u, s));
     for (const SegClass &c : b.preps) BTRY(launch_prep_group(c, sh.preps, sh.preps_first, s));
     // all sample products in one launch per form (FP32 parts with d % 4 != 0 on their own)
     BTRY(launch_dist_gemm_pipe_grouped(sh.stable, sh.psitems, (int64_t)b.npsitems, kPrecSplit, s, kEpiDense));
@@ -570,7 +578,6 @@ hipError_t enqueue_prep(const BatchState &b, int num_cu, hipStream_t s) {
         if (L.cap == 0) BTRY(launch_select_short(sa, num_cu, s));
         else BTRY(launch_select(sa, L.cap, select_grid(L.cap, L.rows, num_cu), sh.selws, s));
     }
-    if (sh.cnt_rows) BTRY(launch_fill_u32(sh.cnt_all, sh.cnt_rows, 0u, s));
     return e;
 }
 
@@ -600,8 +607,6 @@ hipError_t enqueue_product(const BatchState &b, const DistArgs *table, int tile,
 
 hipError_t enqueue_flags(const BatchState &b, knn_handle_t h, hipStream_t s) {
     hipError_t e = hipSuccess;
-    BTRY(launch_fill_u32(b.sh.nflag, (int64_t)b.parts.size(), 0u, s));
-    if (b.sh.cnt_rows) BTRY(launch_sum_u32(b.sh.cnt_all, b.sh.cnt_rows, stats_ptr(h) + kStatCandidates, s));
     for (const SegClass &c : b.flags) BTRY(launch_flag_group(c, b.sh.flags, b.sh.flags_first, s));
     return hipMemcpyAsync(b.nflag_host, b.sh.nflag, b.parts.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s);
 }
@@ -639,7 +644,7 @@ hipError_t refinal_part(const BatchState &b, knn_handle_t h, int num_cu, size_t 
     ka.mode = b.smode;
     ka.net = b.smode == kPivotLearned ? b.net : nullptr;
     BTRY(launch_select_keys(ka, num_cu, s));
-    if (part_certified(b, pt)) BTRY(launch_certify(certify_args(b, h, pi), s));
+    if (part_certified(b, pt) && p.prec != kPrecF32) BTRY(launch_certify(certify_args(b, h, pi), s));
     BTRY(launch_rerank(rerank_args(b, pi), s));
     return hipMemcpyAsync(b.nflag_host + b.parts.size() + pi, b.sh.nu + pi, sizeof(uint32_t), hipMemcpyDeviceToHost,
                           s);
@@ -1013,8 +1018,9 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
             const Plan &p = b.jobs[pt.job].p;
             if (!pt.direct)
                 flags.push_back(FlagSeg{pt.cnt, pt.mb, (uint32_t)p.kk, (uint32_t)p.cap, b.force, b.sh.nflag + pi,
-                                        pt.flags});
-            if (part_certified(b, pt)) certs.push_back(certify_args(b, h, pi));
+                                        pt.flags, stats_ptr(h) + kStatCandidates});
+            // (FP32 parts are certified with their re-rank)
+            if (part_certified(b, pt) && p.prec != kPrecF32) certs.push_back(certify_args(b, h, pi));
             reranks.push_back(rerank_args(b, pi));
         }
         std::vector<uint32_t> fpreps, fflags, fcerts, freranks;

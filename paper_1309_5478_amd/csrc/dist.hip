@@ -301,13 +301,18 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float *__restric
 // ---- candidate bookkeeping ----------------------------------------------------
 // Rows whose candidate count is below `need` or above `cap` are listed for the
 // exact fallback.
+// The counts are summed on the way.
 __device__ __forceinline__ void flag_body(const FlagSeg &a, int64_t i) {
-    if (i >= a.m) return;
-    const uint32_t c = a.cnt[i];
-    if (a.force || c < a.need || c > a.cap) {
+    const uint32_t c = i < a.m ? a.cnt[i] : 0u;
+    if (i < a.m && (a.force || c < a.need || c > a.cap)) {
         uint32_t p = atomicAdd(a.nflag, 1u);
         a.flags[p] = (int32_t)i;
     }
+    // (256 counts of at most 2^31 - 1: in 64 bits from the waves on)
+    unsigned long long t = c;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+    if (lane_id() == 0 && t) atomicAdd(a.total, t);
 }
 __global__ __launch_bounds__(256) void flag_rows_kernel(FlagSeg a) {
     flag_body(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
@@ -388,7 +393,15 @@ __device__ __forceinline__ void rerank_body(const RerankArgs &a, int64_t i) {
         const float E = (a.gamma + kKeyU2) * c2 + 2.0f * (a.rel + kKeyU2) * qm * cm;
         // (1.001: slack for the FP32 evaluation; 4 u: the differences, products
         // and the last sums of the direct form)
-        const float T = key[a.k - 1] + 2.002f * (E + (a.gamma + 2.0f * kKeyU2) * (qm + cm) * (qm + cm));
+        const float ak = key[a.k - 1], T = ak + 2.002f * (E + (a.gamma + 2.0f * kKeyU2) * (qm + cm) * (qm + cm));
+        if (a.ulist && tid == 0) {
+            // the row's certificate (as certify_body's)
+            const float C = 1.001f * E;
+            if (a.force || !(key[a.kk - 1] - ak > 2.0f * C)) {
+                a.ulist[atomicAdd(a.nu, 1u)] = (int32_t)i;
+                a.tfix[i] = ak + 2.0f * C;
+            }
+        }
         if (fabsf(T) <= 3.4028235e38f) {  // a bound exists (false for NaN): the keys up to T, in order
             kk = 0;
             for (uint32_t t0 = 0; t0 < a.kk; t0 += kRerankThreads) {
@@ -710,10 +723,10 @@ hipError_t launch_gather_rows(const float *src, int64_t n, int d, const int32_t 
 }
 
 hipError_t launch_flag_rows(const uint32_t *cnt, int64_t m, uint32_t need, uint32_t cap, int force, uint32_t *nflag,
-                            int32_t *flags, hipStream_t stream) {
+                            int32_t *flags, unsigned long long *total, hipStream_t stream) {
     if (m == 0) return hipSuccess;
     hipLaunchKernelGGL(flag_rows_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, stream,
-                       FlagSeg{cnt, m, need, cap, force, nflag, flags});
+                       FlagSeg{cnt, m, need, cap, force, nflag, flags, total});
     return hipGetLastError();
 }
 

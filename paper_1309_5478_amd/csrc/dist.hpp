@@ -81,6 +81,12 @@ struct RerankArgs {
     const float *qnorm2 = nullptr;
     const unsigned int *cmax2_bits = nullptr;
     float rel = 0.f, gamma = 0.f;
+    // With keys, optional: the certificate of every row (CertifyArgs: list, nlist,
+    // tfix, force), in the same launch.
+    int32_t *ulist = nullptr;
+    uint32_t *nu = nullptr;
+    float *tfix = nullptr;
+    int force = 0;
 };
 
 hipError_t launch_dist_gemm(const DistArgs &a, int epi, hipStream_t stream);
@@ -170,8 +176,9 @@ hipError_t launch_split(const float *X, int64_t n, int d, void *out, float *scal
                         unsigned int *max_bits, hipStream_t stream, int64_t src_n = 0);
 hipError_t launch_gather_rows(const float *src, int64_t n, int d, const int32_t *idx, int64_t rows, float *dst,
                               const float *norms, float *dst_norms, hipStream_t stream);
+// (total: the sum of the counts is added to it)
 hipError_t launch_flag_rows(const uint32_t *cnt, int64_t m, uint32_t need, uint32_t cap, int force, uint32_t *nflag,
-                            int32_t *flags, hipStream_t stream);
+                            int32_t *flags, unsigned long long *total, hipStream_t stream);
 hipError_t launch_scatter_fallback(const int32_t *rows, int64_t nrows, const float *val, const int32_t *idx, int kk,
                                    uint64_t *cand, uint32_t *cnt, int cap, hipStream_t stream);
 hipError_t launch_rerank(const RerankArgs &a, hipStream_t stream);
@@ -258,6 +265,7 @@ struct FlagSeg {
     int force;
     uint32_t *nflag;
     int32_t *flags;
+    unsigned long long *total;
 };
 // The segments of one launch: nseg from seg0 on, their first workgroups (and the
 // end) from first0 on.

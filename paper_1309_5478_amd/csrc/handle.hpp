@@ -23,7 +23,9 @@ struct knn_handle_s {
     hipEvent_t ooc_ev[4] = {nullptr, nullptr, nullptr, nullptr};  // copied[2], freed[2]
     void *scratch = nullptr;   // device address of this device's static scratch array
     size_t ws_bytes = 0;
-    unsigned long long *stats_dev = nullptr;  // kStatCount counters
+    // kStatCount counters, then the words of a search (kWord*), cleared together
+    unsigned long long *stats_dev = nullptr;
+    bool words_clear = false;  // and not used since
     unsigned long long *slots_dev = nullptr;  // per-workgroup totals of a selection (SelectArgs::slots)
     int last_slots = 0;                       // workgroups of the last knn_select_k (0: another call)
     hipStream_t last_stream = nullptr;
@@ -33,7 +35,7 @@ struct knn_handle_s {
     double host_product_ms = 0, host_product_flops = 0;
     int64_t host_product_launches = 0;
     int32_t last_split_parts = 1;              // parts per row of the last knn_select_k
-    uint32_t *pinned = nullptr;                 // one pinned word for device-to-host counts
+    uint32_t *pinned = nullptr;                 // pinned words for device-to-host counts
     std::string err;
     // pivot network: FP32 master weights, their BF16-rounded values (as FP32 for
     // training, as BF16 for inference) and the Adam moments

@@ -25,6 +25,9 @@ enum StatSlot : int {
     kStatUncertified = 13,
     kStatCount = 14
 };
+// Words of a search behind the counters: the largest squared corpus norm, the
+// uncertified rows and the rows for the exact fallback of the current block.
+enum : int { kWordCmax2 = 0, kWordNu = 1, kWordNflag = 2, kWordCount = 4 };
 
 // Row statistics of one selection workgroup (see SelectArgs::slots).
 enum SelSlot : int {

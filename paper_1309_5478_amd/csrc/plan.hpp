@@ -101,7 +101,6 @@ inline size_t dense_split_bytes(int64_t rows, int64_t cols, int k, int num_cu) {
 inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
     b.cnorm = c.take<float>(p.n);
     b.qn2 = c.take<float>(p.m);
-    b.cmax2 = c.take<unsigned int>(1);
     if (p.prec != kPrecF32) {
         b.Cq = c.take<char>((size_t)p.n * p.ldq);
         b.cs = c.take<float>(p.n);
@@ -131,7 +130,6 @@ inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
         const int64_t rows = p.unfused ? p.Mu : p.Mb;
         b.ulist = c.take<int32_t>((size_t)rows);
         b.tfix = c.take<float>((size_t)rows);
-        b.nu = c.take<uint32_t>(1);
     }
     if (p.unfused) {
         b.Dm = c.take<float>((size_t)p.Mu * p.n);
@@ -151,7 +149,6 @@ inline size_t carve(Carve &c, const Plan &p, Bufs &b, int num_cu) {
         b.cnt = c.take<uint32_t>(p.Mb);
         b.cand = c.take<uint64_t>((size_t)p.Mb * p.cap);
         b.flags = c.take<int32_t>(p.Mb);
-        b.nflag = c.take<uint32_t>(1);
         b.sv = c.take<float>((size_t)p.Mb * p.kk);
         b.si = c.take<int32_t>((size_t)p.Mb * p.kk);
         b.Qf = c.take<float>((size_t)p.Fb * p.d);

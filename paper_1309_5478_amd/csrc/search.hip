@@ -38,6 +38,7 @@ knn_status_t ensure_unit_ws(knn_handle_t h, size_t bytes, hipStream_t stream, vo
 knn_status_t fail_msg(knn_handle_t h, knn_status_t s, const std::string &msg);
 uint32_t *host_counter(knn_handle_t h);
 unsigned long long *stats_ptr(knn_handle_t h);
+uint32_t *search_words(knn_handle_t h);
 void add_host_stats(knn_handle_t h, int64_t rows, int64_t fallback_rows);
 void add_host_rerun(knn_handle_t h, int64_t rows);
 void add_product_time(knn_handle_t h, double ms, double flops);
@@ -45,7 +46,6 @@ int handle_num_cu(knn_handle_t h);
 const uint16_t *handle_net(knn_handle_t h);
 
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream);
-hipError_t launch_sum_u32(const uint32_t *p, int64_t n, unsigned long long *out, hipStream_t stream);
 
 knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *C, int64_t n, int d, int k, bool graph,
                         float *out_dist, int32_t *out_idx, hipStream_t stream, const knn_options_t *opt) {
@@ -100,7 +100,14 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
                                                                                  hipGetErrorString(e)); \
     } while (0)
 
-    KNN_TRY(launch_fill_u32(b.cmax2, 1, 0u, stream));
+    // (cleared with the counters for the first search of a call)
+    uint32_t *const words = search_words(h);
+    b.cmax2 = words + kWordCmax2;
+    b.nu = words + kWordNu;
+    b.nflag = words + kWordNflag;
+    if (!h->words_clear) KNN_TRY(launch_fill_u32(words, kWordCount, 0u, stream));
+    h->words_clear = false;
+    bool counts_clear = true;  // nu and nflag: a block's
     // split operands of the whole corpus: made once, with the norms
     const bool whole = p.split && p.Nb >= n;
     if (whole) KNN_TRY(launch_split(C, n, d, b.Cq, b.cs, b.cnorm, b.cmax2, stream));
@@ -148,19 +155,10 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     const bool refix = certify && p.prec == kPrecF32;
 
     // certificate and exact re-rank of one block's kk candidates (ascending
-    // reduced keys `keys`, corpus indices `cidx`), then the exact re-run of the
-    // uncertified rows, from the block's materialised reduced-key rows when
-    // there are (Dblock, row stride ldd), else from rows materialised here
-    auto finish = [&](const float *keys, const int32_t *cidx, int64_t i0, int64_t mb, const float *Dblock,
-                      int64_t ldd) -> knn_status_t {
-        const float *Qb = Q + i0 * d;
-        if (certify) {
-            if (refix) KNN_TRY(launch_fill_u32(b.nu, 1, 0u, stream));
-            CertifyArgs ca{keys, mb, p.kk, k, qn2 + i0, b.cmax2, p.rel, p.gamma, stats_ptr(h) + kStatUncertified,
-                           refix ? b.ulist : nullptr, b.nu, b.tfix, refix && p.force_rerun};
-            KNN_TRY(launch_certify(ca, stream));
-        }
-        RerankArgs rr{Qb, mb, C, n, d, cidx, (uint32_t)p.kk, k, out_dist + i0 * k, out_idx + i0 * k,
+    // reduced keys `keys`, corpus indices `cidx`): FP32 rows without a certificate
+    // are listed for the re-run, b.nu of them
+    auto candidates = [&](const float *keys, const int32_t *cidx, int64_t i0, int64_t mb) -> knn_status_t {
+        RerankArgs rr{Q + i0 * d, mb, C, n, d, cidx, (uint32_t)p.kk, k, out_dist + i0 * k, out_idx + i0 * k,
                       graph ? i0 : -1, oscale};
         if (refix) {
             rr.keys = keys;
@@ -168,13 +166,36 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             rr.cmax2_bits = b.cmax2;
             rr.rel = p.rel;
             rr.gamma = p.gamma;
+            rr.ulist = b.ulist;
+            rr.nu = b.nu;
+            rr.tfix = b.tfix;
+            rr.force = p.force_rerun;
         }
         KNN_TRY(launch_rerank(rr, stream));
-        if (!refix) return KNN_SUCCESS;
-        KNN_TRY(hipMemcpyAsync(hcount, b.nu, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+        return KNN_SUCCESS;
+    };
+    // the uncertified rows of a reduced precision are counted (nothing is re-run)
+    auto count_uncertified = [&](const float *keys, int64_t i0, int64_t mb) -> knn_status_t {
+        if (!certify || refix) return KNN_SUCCESS;
+        CertifyArgs ca{keys, mb, p.kk, k, qn2 + i0, b.cmax2, p.rel, p.gamma, stats_ptr(h) + kStatUncertified,
+                       nullptr, b.nu, b.tfix, 0};
+        KNN_TRY(launch_certify(ca, stream));
+        return KNN_SUCCESS;
+    };
+    // the block's counts on the host
+    auto fetch = [&]() -> knn_status_t {
+        KNN_TRY(hipMemcpyAsync(hcount, words, kWordCount * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
         KNN_TRY(hipStreamSynchronize(stream));
-        const int64_t nu = *hcount;
+        return KNN_SUCCESS;
+    };
+    // the exact re-run of the block's nu uncertified rows, from the block's
+    // materialised reduced-key rows when there are (Dblock, row stride ldd), else
+    // from rows materialised here
+    auto rerun = [&](int64_t i0, int64_t mb, const float *Dblock, int64_t ldd) -> knn_status_t {
+        const float *Qb = Q + i0 * d;
+        const int64_t nu = refix ? hcount[kWordNu] : 0;
         rerun_total += nu;
+        if (nu == 0) return KNN_SUCCESS;
         FixupArgs fx{};
         fx.out_scale = oscale;
         fx.tfix = b.tfix;
@@ -218,6 +239,17 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             KNN_TRY(launch_fixup(fx, stream));
         }
         return KNN_SUCCESS;
+    };
+    // a block whose rows' keys are all stored: certificate, re-rank, re-run
+    auto finish = [&](const float *keys, const int32_t *cidx, int64_t i0, int64_t mb, const float *Dblock,
+                      int64_t ldd) -> knn_status_t {
+        if (refix && !counts_clear) KNN_TRY(launch_fill_u32(b.nu, 1, 0u, stream));
+        counts_clear = false;
+        knn_status_t fs = candidates(keys, cidx, i0, mb);
+        if (fs != KNN_SUCCESS) return fs;
+        if (!refix) return count_uncertified(keys, i0, mb);
+        if ((fs = fetch()) != KNN_SUCCESS) return fs;
+        return rerun(i0, mb, Dblock, ldd);
     };
 
     if (p.unfused) {
@@ -398,15 +430,43 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             KNN_TRY(launch_dist_gemm(fa, kEpiFilter, stream));
         }
         KNN_TRY(timer.end(stream));
-        KNN_TRY(launch_sum_u32(b.cnt, mb, stats_ptr(h) + kStatCandidates, stream));
-        // 3. exact re-do of rows whose candidate list is unusable
-        KNN_TRY(launch_fill_u32(b.nflag, 1, 0u, stream));
-        KNN_TRY(launch_flag_rows(b.cnt, mb, (uint32_t)p.kk, (uint32_t)p.cap, p.force, b.nflag, b.flags, stream));
-        KNN_TRY(hipMemcpyAsync(hcount, b.nflag, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-        KNN_TRY(hipStreamSynchronize(stream));
+        // 3. rows whose candidate list is unusable are listed, 4. the kk smallest
+        // candidates, their certificate and exact re-rank
+        if (!counts_clear) KNN_TRY(launch_fill_u32(b.nu, 2, 0u, stream));
+        counts_clear = false;
+        static_assert(kWordNflag == kWordNu + 1, "cleared together");
+        KNN_TRY(launch_flag_rows(b.cnt, mb, (uint32_t)p.kk, (uint32_t)p.cap, p.force, b.nflag, b.flags,
+                                 stats_ptr(h) + kStatCandidates, stream));
+        auto select = [&]() -> knn_status_t {
+            SelectArgs ka{};
+            ka.keys = b.cand;
+            ka.key_cnt = b.cnt;
+            ka.rows = mb;
+            ka.cols = (uint32_t)p.cap;
+            ka.ld = p.cap;
+            ka.k = (uint32_t)p.kk;
+            ka.out_val = b.sv;
+            ka.out_idx = b.si;
+            ka.mode = smode;
+            KNN_TRY(launch_select_keys(ka, num_cu, stream));
+            return candidates(b.sv, b.si, i0, mb);
+        };
+        // Flagged rows are rare (a few in 10^5): a small block does not wait for
+        // their number before it goes on, and starts 4 again where there are any.
+        const bool ahead = mb <= 8192 && !p.force;
+        knn_status_t fs;
+        if (ahead && (fs = select()) != KNN_SUCCESS) return fs;
+        if ((fs = fetch()) != KNN_SUCCESS) return fs;
         KNN_TRY(timer.collect(h));
-        const int64_t nf = *hcount;
+        const int64_t nf = hcount[kWordNflag];
         fallback_total += nf;
+        if (ahead && nf == 0) {
+            if ((fs = rerun(i0, mb, nullptr, 0)) != KNN_SUCCESS) return fs;
+            if ((fs = count_uncertified(b.sv, i0, mb)) != KNN_SUCCESS) return fs;
+            continue;
+        }
+        if (ahead) KNN_TRY(launch_fill_u32(b.nu, 1, 0u, stream));
+        // exact re-do of the flagged rows
         for (int64_t f0 = 0; f0 < nf; f0 += p.Fb) {
             const int64_t fb = nf - f0 < p.Fb ? nf - f0 : p.Fb;
             KNN_TRY(launch_gather_rows(Qb, mb, d, b.flags + f0, fb, b.Qf, nullptr, nullptr, stream));
@@ -427,20 +487,12 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             KNN_TRY(select_dense(b.Df, fb, n, n, p.kk, b.fv, b.fi, b.selws, b.selws_bytes, num_cu, smode, net, stream));
             KNN_TRY(launch_scatter_fallback(b.flags + f0, fb, b.fv, b.fi, p.kk, b.cand, b.cnt, p.cap, stream));
         }
-        // 4. kk smallest candidates, exact re-rank, final k
-        SelectArgs ka{};
-        ka.keys = b.cand;
-        ka.key_cnt = b.cnt;
-        ka.rows = mb;
-        ka.cols = (uint32_t)p.cap;
-        ka.ld = p.cap;
-        ka.k = (uint32_t)p.kk;
-        ka.out_val = b.sv;
-        ka.out_idx = b.si;
-        ka.mode = smode;
-        KNN_TRY(launch_select_keys(ka, num_cu, stream));
-        knn_status_t fs = finish(b.sv, b.si, i0, mb, nullptr, 0);
-        if (fs != KNN_SUCCESS) return fs;
+        if ((fs = select()) != KNN_SUCCESS) return fs;
+        if (refix) {
+            if ((fs = fetch()) != KNN_SUCCESS) return fs;
+            if ((fs = rerun(i0, mb, nullptr, 0)) != KNN_SUCCESS) return fs;
+        }
+        if ((fs = count_uncertified(b.sv, i0, mb)) != KNN_SUCCESS) return fs;
     }
 #undef KNN_TRY
     add_host_stats(h, m, fallback_total);

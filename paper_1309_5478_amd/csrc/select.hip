@@ -797,17 +797,6 @@ __global__ void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v) {
     if (i < n) p[i] = v;
 }
 
-// Adds the sum of n uint32 values to *out (one atomic per workgroup).
-__global__ __launch_bounds__(256) void sum_u32_kernel(const uint32_t *p, int64_t n, unsigned long long *out) {
-    __shared__ unsigned long long part[4];
-    unsigned long long s = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) s += p[i];
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane_id() == 0) part[threadIdx.x / kWave] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(out, part[0] + part[1] + part[2] + part[3]);
-}
-
 __global__ void zero_u64_kernel(unsigned long long *p, int n) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0ull;
@@ -1020,14 +1009,6 @@ hipError_t launch_partition(const float *in, int64_t rows, uint32_t cols, int64_
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, n, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_sum_u32(const uint32_t *p, int64_t n, unsigned long long *out, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(sum_u32_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p, n, out);
     return hipGetLastError();
 }
 
