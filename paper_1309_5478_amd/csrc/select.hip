@@ -139,7 +139,7 @@ constexpr uint32_t kTile4 = kSelThreads * kStreamU;   // float4s per tile
 // case) the writes skip the per-entry workspace test.
 template <int CAP>
 __device__ __forceinline__ void vote_tile_le(SelSmem<CAP> &sm, const GBuf &gb, const f32x4 *x, uint32_t t,
-                                             float tv) {
+                                             uint32_t first, float tv) {
     const uint32_t tid = threadIdx.x;
     uint64_t m[kStreamU * 4];
     uint32_t total = 0;
@@ -157,7 +157,7 @@ __device__ __forceinline__ void vote_tile_le(SelSmem<CAP> &sm, const GBuf &gb, c
     if (lane_id() == 0) base = atomicAdd(&sm.cnt_lt, total);
     base = wave_bcast0(base);
     const bool in_lds = base + total <= 2u * CAP;  // (uniform)
-    const uint32_t j0 = (t * kTile4 + tid) * 4;
+    const uint32_t j0 = first + (t * kTile4 + tid) * 4;
 #pragma unroll
     for (uint32_t u = 0; u < kStreamU; ++u) {
 #pragma unroll
@@ -179,14 +179,14 @@ __device__ __forceinline__ void vote_tile_le(SelSmem<CAP> &sm, const GBuf &gb, c
     }
 }
 
-// Full tiles of 256 lanes x 4 x 16 bytes against a threshold value, unmasked,
-// software-pipelined over two register sets: the loads of one tile are in flight
-// while the other is voted on (no copies between the sets, so the wait counts
-// only cover the tile being voted on).
+// Full tiles of 256 lanes x 4 x 16 bytes from entry `first` on against a threshold
+// value, unmasked, software-pipelined over two register sets: the loads of one
+// tile are in flight while the other is voted on (no copies between the sets, so
+// the wait counts only cover the tile being voted on).
 template <int CAP>
-__device__ __forceinline__ void stream_tiles_le(SelSmem<CAP> &sm, const GBuf &gb, const f32x4 *__restrict__ r4,
-                                                uint32_t full, float tv) {
-    const f32x4 *p = r4 + threadIdx.x;
+__device__ __forceinline__ void stream_tiles_le(SelSmem<CAP> &sm, const GBuf &gb, const float *__restrict__ row,
+                                                uint32_t first, uint32_t full, float tv) {
+    const f32x4 *p = reinterpret_cast<const f32x4 *>(row + first) + threadIdx.x;
     f32x4 A[kStreamU], B[kStreamU];
     auto load = [&](f32x4 *dst, uint32_t t) {
 #pragma unroll
@@ -196,39 +196,47 @@ __device__ __forceinline__ void stream_tiles_le(SelSmem<CAP> &sm, const GBuf &gb
     uint32_t t = 0;
     for (; t + 2 < full; t += 2) {
         load(B, t + 1);
-        vote_tile_le(sm, gb, A, t, tv);
+        vote_tile_le(sm, gb, A, t, first, tv);
         load(A, t + 2);
-        vote_tile_le(sm, gb, B, t + 1, tv);
+        vote_tile_le(sm, gb, B, t + 1, first, tv);
     }
     if (t + 1 < full) {
         load(B, t + 1);
-        vote_tile_le(sm, gb, A, t, tv);
-        vote_tile_le(sm, gb, B, t + 1, tv);
+        vote_tile_le(sm, gb, A, t, first, tv);
+        vote_tile_le(sm, gb, B, t + 1, first, tv);
     } else {
-        vote_tile_le(sm, gb, A, t, tv);
+        vote_tile_le(sm, gb, A, t, first, tv);
     }
 }
 
 // One streaming pass over the row, appending to buffer 0 the keys below P.  A
-// threshold-form pivot (index ~0u) of a finite value class on 16-byte aligned
-// rows takes the tiled fast path for all full tiles; everything else (NaN-class
-// pivots, the +infinity sentinel, misaligned rows, the ragged tail) takes the
-// generic one-entry-per-lane loop.
+// threshold-form pivot (index ~0u) of a finite value class takes the tiled fast
+// path for all full tiles, from the first 128-byte boundary on: most matrices have
+// a row length that is no multiple of four, so that three rows in four begin off
+// a 16-byte boundary (3051 x 176637, k = 1: 1280 us when such rows went entry by
+// entry, 395 now; 16384 x 65535, k = 256: 2400, 890).  Everything else (NaN-class
+// pivots, the +infinity sentinel, the entries before and behind the tiles) takes
+// the generic one-entry-per-lane loop.
 template <int CAP>
 __device__ __forceinline__ void stream_pass(SelSmem<CAP> &sm, const GBuf &gb, const float *__restrict__ row,
-                                            uint32_t N, bool vec, const Pivot &P) {
+                                            uint32_t N, const Pivot &P) {
     const uint32_t tid = threadIdx.x;
-    uint32_t done = 0;
-    if (vec && !P.nan && !P.inf && P.pidx == 0xFFFFFFFFu) {
-        const uint32_t full = (N >> 2) / kTile4;
-        if (full > 0) stream_tiles_le(sm, gb, reinterpret_cast<const f32x4 *>(row), full, P.pv);
+    uint32_t first = 0, done = 0;  // the tiles' entries: done from first on
+    if (!P.nan && !P.inf && P.pidx == 0xFFFFFFFFu) {
+        first = (uint32_t)((0u - (uint32_t)(reinterpret_cast<uintptr_t>(row) >> 2)) & 31u);
+        first = first < N ? first : N;
+        const uint32_t full = ((N - first) >> 2) / kTile4;
+        if (full > 0) stream_tiles_le(sm, gb, row, first, full, P.pv);
         done = full * kTile4 * 4;
     }
-    for (uint32_t j0 = done; j0 < N; j0 += kSelThreads) {
-        uint32_t j = j0 + tid;
-        bool valid = j < N;
-        float v = valid ? row[j] : 0.f;
-        vote_generic<CAP>(sm, gb, v, j, valid, P);
+    const uint32_t rest = N - done;
+    auto entry = [&](uint32_t p) -> uint32_t { return p < first ? p : p + done; };
+    float next = tid < rest ? row[entry(tid)] : 0.f;
+    for (uint32_t p0 = 0; p0 < rest; p0 += kSelThreads) {  // (the next entry is in flight)
+        const uint32_t p = p0 + tid;
+        const float v = next;
+        if (p + kSelThreads < rest) next = row[entry(p + kSelThreads)];
+        vote_generic<CAP>(sm, gb, v, entry(p), p < rest, P);
     }
 }
 
@@ -465,7 +473,6 @@ __global__ __launch_bounds__(kSelThreads, CAP == kSelectCap ? 5 : (CAP == 2048 ?
             out_idx = sg.out_idx;
         }
         const float *row = dist + lr * ld + col_off;
-        const bool vec = ((reinterpret_cast<uintptr_t>(row) & 15u) == 0) && ((ld & 3) == 0);
         uint32_t nstack = 0, agg = 0, passes = 0, stream_passes = 0, spill = 0, first = 0;
         uint32_t wide_lo = 0, wide_hi = 0;  // streamed range of buffer 0 still in the streaming layout
         long long cyc_sample = 0, cyc_stream = 0;
@@ -567,7 +574,7 @@ __global__ __launch_bounds__(kSelThreads, CAP == kSelectCap ? 5 : (CAP == 2048 ?
                 if (tid == 0) sm.cnt_lt = 0;
                 __syncthreads();
                 const Pivot Pv = make_pivot(P);
-                stream_pass<CAP>(sm, gb, row, N, vec, Pv);
+                stream_pass<CAP>(sm, gb, row, N, Pv);
                 __syncthreads();
                 const uint32_t total = sm.cnt_lt;
                 __syncthreads();
