@@ -22,69 +22,103 @@ namespace knn {
 // wave per row: lane-strided sums in a fixed order reduced by a lane tree; the
 // norm is taken of the row scaled by its largest magnitude (no overflow or
 // underflow in the squares), and every element is divided once.
-__device__ __forceinline__ float wave_sum(float s) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    return s;
-}
-__device__ __forceinline__ float wave_max(float s) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s = fmaxf(s, __shfl_xor(s, off));
-    return s;
-}
-__device__ __forceinline__ float wave_min(float s) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s = fminf(s, __shfl_xor(s, off));
-    return s;
-}
 
+// V > 0: rows of at most 64 V elements, held in registers, 64 / G of them to a
+// wave (G lanes each; V = 1 below 64): one read and one write of memory.  V = 0:
+// longer rows, read again for every step.  The sums run over the same elements in
+// the same order either way.  Memory-bound: cosine searches, with a row read four
+// times / once: 5003 x 150001 x 300 1795 / 1601 us, 16 x 10^6 x 128 697 / 489, 16 x
+// 10^6 x 16 324 / 140 (half of that from four rows to a wave).
+template <int V, int G>
 __global__ __launch_bounds__(256) void unit_rows_kernel(const float *__restrict__ X, int64_t n, int d, int centre,
                                                         float *__restrict__ out) {
-    const uint32_t lane = lane_id();
-    const int64_t i = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-    if (i >= n) return;
-    const float *x = X + i * d;
+    const uint32_t lane = lane_id() % G;
+    const int64_t i = ((int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * (kWave / G) + lane_id() / G;
+    if (G == kWave && i >= n) return;
+    const bool in = i < n;
+    const float *x = X + (in ? i : n - 1) * d;
     float *o = out + i * d;
+    float held[V > 0 ? V : 1];
+    if (V > 0) {
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const int t = (int)lane + u * G;
+            held[u] = t < d ? x[t] : 0.f;
+        }
+    }
+    // f(element, its register) over this lane's elements, in order
+    auto each = [&](auto f) {
+        if constexpr (V > 0) {
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+                if ((int)lane + u * G < d) f((int)lane + u * G, held[u]);
+        } else {
+            for (int t = (int)lane; t < d; t += G) {
+                float v = x[t];
+                f(t, v);
+            }
+        }
+    };
+    auto tree = [&](float v, auto op) {
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) v = op(v, shfl_xor_any(v, off));
+        return v;
+    };
+    auto add = [](float p, float q) { return p + q; };
+    auto low = [](float p, float q) { return fminf(p, q); };
+    auto high = [](float p, float q) { return fmaxf(p, q); };
     float mu = 0.f;
     bool flat = false;
     if (centre) {
         float s = 0.f, lo = __uint_as_float(0x7f800000u), hi = -lo;
-        for (int t = (int)lane; t < d; t += kWave) {
-            const float v = x[t];
+        each([&](int, float &v) {
             s += v;
             lo = fminf(lo, v);
             hi = fmaxf(hi, v);
-        }
-        mu = wave_sum(s) / (float)d;
+        });
+        mu = tree(s, add) / (float)d;
         // a constant row is exactly zero once centred, whatever the rounding of its mean
-        flat = wave_min(lo) == wave_max(hi);
+        flat = tree(lo, low) == tree(hi, high);
     }
-    float amax = 0.f;
-    bool nan = false;
-    for (int t = (int)lane; t < d; t += kWave) {
-        const float v = x[t] - mu;
-        nan |= v != v;
+    float amax = 0.f, nans = 0.f;
+    each([&](int, float &v) {
+        v = v - mu;
+        nans = v != v ? 1.f : nans;
         amax = fmaxf(amax, fabsf(v));
-    }
-    amax = wave_max(amax);
-    nan = __ballot(nan) != 0;
-    const bool ok = !flat && !nan && amax > 0.f && amax <= 3.4028235e38f;
+    });
+    amax = tree(amax, high);
+    nans = tree(nans, high);
+    const bool ok = !flat && nans == 0.f && amax > 0.f && amax <= 3.4028235e38f;
     float ss = 0.f;
     if (ok)
-        for (int t = (int)lane; t < d; t += kWave) {
-            const float v = (x[t] - mu) / amax;
+        each([&](int, float &v) {
+            v = (V > 0 ? v : v - mu) / amax;
             ss = fmaf(v, v, ss);
-        }
-    const float nrm = sqrtf(wave_sum(ss));
+        });
+    const float nrm = sqrtf(tree(ss, add));
     const float qnan = __uint_as_float(0x7fc00000u);
-    for (int t = (int)lane; t < d; t += kWave) o[t] = ok ? ((x[t] - mu) / amax) / nrm : qnan;
+    if (in)
+        each([&](int t, float &v) { o[t] = ok ? (V > 0 ? v : (v - mu) / amax) / nrm : qnan; });
+}
+
+template <int V, int G>
+static void launch_unit_t(const float *X, int64_t n, int d, bool centre, float *out, hipStream_t stream) {
+    const int64_t per = 4 * (kWave / G);
+    hipLaunchKernelGGL((unit_rows_kernel<V, G>), dim3((unsigned)((n + per - 1) / per)), dim3(256), 0, stream, X, n, d,
+                       centre ? 1 : 0, out);
 }
 
 hipError_t launch_unit_rows(const float *X, int64_t n, int d, bool centre, float *out, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    const int64_t blocks = (n + 3) / 4;
-    if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(unit_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, X, n, d, centre ? 1 : 0, out);
+    if ((n + 3) / 4 > 0x7fffffffll) return hipErrorInvalidValue;
+    if (d <= 16) launch_unit_t<1, 16>(X, n, d, centre, out, stream);
+    else if (d <= 32) launch_unit_t<1, 32>(X, n, d, centre, out, stream);
+    else if (d <= 64) launch_unit_t<1, 64>(X, n, d, centre, out, stream);
+    else if (d <= 128) launch_unit_t<2, 64>(X, n, d, centre, out, stream);
+    else if (d <= 256) launch_unit_t<4, 64>(X, n, d, centre, out, stream);
+    else if (d <= 512) launch_unit_t<8, 64>(X, n, d, centre, out, stream);
+    else if (d <= 1024) launch_unit_t<16, 64>(X, n, d, centre, out, stream);
+    else launch_unit_t<0, 64>(X, n, d, centre, out, stream);
     return hipGetLastError();
 }
 
@@ -135,7 +169,7 @@ __device__ __forceinline__ void sqnorm_body(const float *__restrict__ X, int64_t
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
 #pragma unroll
-            for (int off = G / 2; off > 0; off >>= 1) acc[u] += __shfl_xor(acc[u], off);
+            for (int off = G / 2; off > 0; off >>= 1) acc[u] += shfl_xor_any(acc[u], off);
             const int64_t i = base + u * stride + grp;
             if (i < n && sub == 0) out[i] = acc[u];
             mx = fmaxf(mx, acc[u]);
@@ -143,7 +177,7 @@ __device__ __forceinline__ void sqnorm_body(const float *__restrict__ X, int64_t
     }
     if (max_bits) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, shfl_xor_any(mx, off));
         if (lane == 0) wmax[wave] = mx;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -200,8 +234,8 @@ __device__ __forceinline__ void split_body(const float *__restrict__ X, int64_t 
         }
 #pragma unroll
         for (int off = G / 2; off > 0; off >>= 1) {
-            s += __shfl_xor(s, off);
-            am = fmaxf(am, __shfl_xor(am, off));
+            s += shfl_xor_any(s, off);
+            am = fmaxf(am, shfl_xor_any(am, off));
         }
         int e = 0;
         if (am > 0.f) {
@@ -256,7 +290,7 @@ __device__ __forceinline__ void split_body(const float *__restrict__ X, int64_t 
     }
     if (max_bits) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, shfl_xor_any(mx, off));
         if (lane == 0) wmax[wave] = mx;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -424,8 +458,8 @@ __device__ __forceinline__ void rerank_body(const RerankArgs &a, int64_t i) {
         float s1 = ok1 ? rerank_dist<G, VEC>(q, a.C + (int64_t)j1 * a.d, a.d, sub) : 0.f;
 #pragma unroll
         for (int off = G / 2; off > 0; off >>= 1) {
-            s0 += __shfl_xor(s0, off);
-            s1 += __shfl_xor(s1, off);
+            s0 += shfl_xor_any(s0, off);
+            s1 += shfl_xor_any(s1, off);
         }
         if (sub == 0) {
             keys[c0] = ok0 ? make_key(s0, j0) : kKeyMax;
@@ -502,7 +536,7 @@ __device__ __forceinline__ void quantize_row(const float *__restrict__ X, int64_
         if (v <= 3.4028235e38f) amax = fmaxf(amax, v);  // finite magnitudes only
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, shfl_xor_any(amax, off));
     int e = 0;
     if (amax > 0.f) {
         // amax = f 2^E with f in [0.5, 1): amax 2^e <= 448 = 0.875 * 2^9 exactly
@@ -587,7 +621,7 @@ __global__ __launch_bounds__(kFixThreads) void exact_rows_kernel(FixupArgs a) {
             const uint32_t j = cidx[c0];
             float s = rerank_dist<G, VEC>(q, a.C + (int64_t)j * a.d, a.d, sub);
 #pragma unroll
-            for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
+            for (int off = G / 2; off > 0; off >>= 1) s += shfl_xor_any(s, off);
             if (sub == 0) batch[c0] = (int64_t)j == own ? kKeyMax : make_key(s, j);
         }
         for (uint32_t t = c + tid; t < (uint32_t)kFixTop; t += kFixThreads) batch[t] = kKeyMax;

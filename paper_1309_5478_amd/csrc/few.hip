@@ -58,7 +58,7 @@ __global__ __launch_bounds__(few_waves(MT) * kWave) void dist_few_kernel(const f
             float s = 0.f;
             for (int c = (int)lane; c < d; c += kWave) s = fmaf(sq[r * ld + c], sq[r * ld + c], s);
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+            for (int off = 32; off > 0; off >>= 1) s += shfl_xor_any(s, off);
             if (lane == 0) qnorm2[r] = s;
         }
 
@@ -125,8 +125,8 @@ __global__ __launch_bounds__(few_waves(MT) * kWave) void dist_few_kernel(const f
             for (int t = 0; t < kFewLoads; ++t) cur[t] = nxt[t];
         }
         row = next;
-        nrm += __shfl_xor(nrm, 16);
-        nrm += __shfl_xor(nrm, 32);
+        nrm += shfl_xor_any(nrm, 16);
+        nrm += shfl_xor_any(nrm, 32);
         mx = fmaxf(mx, nrm);
         const int64_t j = tile * 16 + l16;
         if (j < n) {
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(few_waves(MT) * kWave) void dist_few_kernel(const f
         }
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, shfl_xor_any(mx, off));
     if (lane == 0) wmax[wave] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -137,6 +137,9 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
 
 __device__ __forceinline__ uint64_t shfl_xor_any(uint64_t v, int mask) { return shfl_xor_u64(v, mask); }
 __device__ __forceinline__ uint32_t shfl_xor_any(uint32_t v, int mask) { return xor_lanes32(v, mask); }
+__device__ __forceinline__ float shfl_xor_any(float v, int mask) {
+    return __uint_as_float(xor_lanes32(__float_as_uint(v), mask));
+}
 
 // For masks only known at run time: one LDS-crossbar permute per half.
 __device__ __forceinline__ uint64_t shfl_xor_u64_rt(uint64_t v, int mask) {
