@@ -310,7 +310,7 @@ void plan_selects(BatchState &b) {
     b.keys_sel = std::move(K);
 }
 
-constexpr size_t kPrepSegs = 7;  // preparation segments of a job, at most
+constexpr size_t kPrepSegs = 4;  // preparation segments of a job, at most
 
 // Lays out the batch workspace (sizing pass with base == nullptr).  Every
 // part keeps its own sample distances, selections and candidate lists, so
@@ -538,12 +538,10 @@ std::vector<PrepSeg> prep_segs(const BatchState &b) {
         const bool quant = p.prec != kPrecF32;
         auto add = [&](const float *X, int64_t n, int64_t src_n, const void *out, const float *scale, const float *norm,
                        unsigned int *max_bits) {
-            const int kind = p.split ? kPrepSplit : kPrepNorm;
-            v.push_back(PrepSeg{kind, X, n, src_n, js.d, p.prec, p.split ? const_cast<void *>(out) : nullptr,
-                                p.split ? const_cast<float *>(scale) : nullptr, const_cast<float *>(norm), max_bits});
-            if (quant)
-                v.push_back(PrepSeg{kPrepQuant, X, n, src_n, js.d, p.prec, const_cast<void *>(out),
-                                    const_cast<float *>(scale), nullptr, nullptr});
+            const int kind = p.split ? kPrepSplit : (quant ? kPrepQuant : kPrepNorm);
+            const bool operands = kind != kPrepNorm;
+            v.push_back(PrepSeg{kind, X, n, src_n, js.d, p.prec, operands ? const_cast<void *>(out) : nullptr,
+                                operands ? const_cast<float *>(scale) : nullptr, const_cast<float *>(norm), max_bits});
         };
         add(js.C, js.n, 0, js.Cq, js.cs, js.cnorm, js.cmax2);
         if (!js.graph) add(js.Q, js.m, 0, js.Qq, js.qs, js.qn2, nullptr);

@@ -517,45 +517,128 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
-// One wave per point.  FP8: e = the largest integer with amax * 2^e <= 448,
-// amax the largest finite magnitude of the point (e = 0 without a finite
-// non-zero element; e limited to [-100, 100]), elements x * 2^e rounded to
-// e4m3, scale 2^-e.
-__device__ __forceinline__ void quantize_row(const float *__restrict__ X, int64_t n, int64_t src_n, int d, int prec,
-                                             int dq, void *__restrict__ out, float *__restrict__ scale_out, int64_t i) {
-    const uint32_t lane = lane_id();
-    const float *x = X + source_row(i, n, src_n) * d;
-    if (prec == kPrecBF16) {
-        uint16_t *o = static_cast<uint16_t *>(out) + i * dq;
-        for (int t = lane; t < dq; t += kWave) o[t] = t < d ? f32_to_bf16_rne(x[t]) : (uint16_t)0;
-        return;
-    }
-    float amax = 0.f;
-    for (int t = lane; t < d; t += kWave) {
-        const float v = fabsf(x[t]);
-        if (v <= 3.4028235e38f) amax = fmaxf(amax, v);  // finite magnitudes only
-    }
+// FP8: e = the largest integer with amax * 2^e <= 448, amax the largest finite
+// magnitude of the point (e = 0 without a finite non-zero element; e limited to
+// [-100, 100]), elements x * 2^e rounded to e4m3, scale 2^-e.  The squared norms
+// come from the same read, in sqnorm_kernel's order and lane grouping.
+// Memory-bound (FP8's second pass over a row finds it in L1).  whole: out is
+// aligned to 8 bytes (a caller's own buffer may not be).
+template <int G, bool VEC>
+__device__ __forceinline__ void quantize_body(const float *__restrict__ X, int64_t n, int64_t src_n, int d, int prec,
+                                              void *__restrict__ out, float *__restrict__ scale_out,
+                                              float *__restrict__ norm, unsigned int *__restrict__ max_bits,
+                                              uint32_t block, uint32_t blocks, bool whole) {
+    constexpr int PPW = kWave / G, W = VEC ? 4 : 1;
+    __shared__ float wmax[256 / kWave];
+    const uint32_t lane = lane_id(), sub = lane % G, grp = lane / G, wave = threadIdx.x / kWave;
+    const int64_t stride = (int64_t)blocks * (256 / kWave) * PPW;
+    const int dq = (d + kQuantPad - 1) / kQuantPad * kQuantPad;
+    const bool fp8 = prec == kPrecFP8;
+    float mx = 0.f;
+    for (int64_t base = ((int64_t)block * (256 / kWave) + wave) * PPW; base < n; base += stride) {
+        const int64_t i = base + grp;
+        const bool in = i < n;
+        const float *x = X + source_row(in ? i : n - 1, n, src_n) * d;
+        // f(t, V elements from t on, zeros beyond the row) over this lane's part, V =
+        // W for the sums; operands are written four at a time either way
+        auto each = [&](auto width, int end, auto f) {
+            constexpr int V = decltype(width)::value;
+            for (int t = (int)sub * V; t < end; t += G * V) {
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (VEC) {
+                    if (t < d) v = *reinterpret_cast<const f32x4 *>(x + t);
+                } else if constexpr (V == 1) {
+                    if (t < d) v[0] = x[t];
+                } else {
+                    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+                    if (t + 4 <= d) {
+                        v = *reinterpret_cast<const f32x4_any *>(x + t);
+                    } else {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, shfl_xor_any(amax, off));
-    int e = 0;
-    if (amax > 0.f) {
-        // amax = f 2^E with f in [0.5, 1): amax 2^e <= 448 = 0.875 * 2^9 exactly
-        // when e <= 9 - E, less one when f > 0.875
-        int E;
-        const float f = frexpf(amax, &E);
-        e = 9 - E - (f > 0.875f ? 1 : 0);
-        e = e < -100 ? -100 : (e > 100 ? 100 : e);
+                        for (int c = 0; c < 4; ++c)
+                            if (t + c < d) v[c] = x[t + c];
+                    }
+                }
+                f(t, v);
+            }
+        };
+        const std::integral_constant<int, W> wide{};
+        const std::integral_constant<int, 4> four{};
+        float s = 0.f, amax = 0.f;
+        auto see = [&](const f32x4 &v) {
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                s = fmaf(v[c], v[c], s);
+                const float m = fabsf(v[c]);
+                if (m <= 3.4028235e38f) amax = fmaxf(amax, m);  // finite magnitudes only
+            }
+        };
+        unsigned char *const o = static_cast<unsigned char *>(out) + (in ? i : n - 1) * dq * (fp8 ? 1 : 2);
+        if (!VEC || fp8) each(wide, d, [&](int, const f32x4 &v) { see(v); });
+        if (!fp8)
+            each(four, dq, [&](int t, const f32x4 &v) {
+                if (VEC && t < d) see(v);  // (one pass)
+                typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+                u16x4 q;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) q[c] = f32_to_bf16_rne(v[c]);
+                if (!in) return;
+                if (whole) {
+                    *reinterpret_cast<u16x4 *>(o + 2 * t) = q;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) reinterpret_cast<uint16_t *>(o)[t + c] = q[c];
+                }
+            });
+#pragma unroll
+        for (int off = G / 2; off > 0; off >>= 1) {
+            s += shfl_xor_any(s, off);
+            amax = fmaxf(amax, shfl_xor_any(amax, off));
+        }
+        if (in && norm && sub == 0) norm[i] = s;
+        if (in) mx = fmaxf(mx, s);
+        if (!fp8) continue;
+        int e = 0;
+        if (amax > 0.f) {
+            // amax = f 2^E with f in [0.5, 1): amax 2^e <= 448 = 0.875 * 2^9 exactly
+            // when e <= 9 - E, less one when f > 0.875
+            int E;
+            const float f = frexpf(amax, &E);
+            e = 9 - E - (f > 0.875f ? 1 : 0);
+            e = e < -100 ? -100 : (e > 100 ? 100 : e);
+        }
+        each(four, dq, [&](int t, const f32x4 &v) {
+            uint32_t q = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) q |= (uint32_t)f32_to_e4m3(ldexpf(v[c], e)) << (8 * c);
+            if (!in) return;
+            if (whole) {
+                *reinterpret_cast<uint32_t *>(o + t) = q;
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[t + c] = (unsigned char)(q >> (8 * c));
+            }
+        });
+        if (in && sub == 0) scale_out[i] = ldexpf(1.0f, -e);
     }
-    uint8_t *o = static_cast<uint8_t *>(out) + i * dq;
-    for (int t = lane; t < dq; t += kWave) o[t] = t < d ? f32_to_e4m3(ldexpf(x[t], e)) : (uint8_t)0;
-    if (lane == 0) scale_out[i] = ldexpf(1.0f, -e);
+    if (max_bits) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, shfl_xor_any(mx, off));
+        if (lane == 0) wmax[wave] = mx;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float m = wmax[0];
+            for (int w = 1; w < 256 / kWave; ++w) m = fmaxf(m, wmax[w]);
+            atomicMax(max_bits, __float_as_uint(m));
+        }
+    }
 }
-
+template <int G, bool VEC>
 __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ X, int64_t n, int64_t src_n, int d,
-                                                       int prec, int dq, void *__restrict__ out,
-                                                       float *__restrict__ scale_out) {
-    const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave;
-    if (i < n) quantize_row(X, n, src_n, d, prec, dq, out, scale_out, i);
+                                                       int prec, void *__restrict__ out, float *__restrict__ scale_out,
+                                                       float *__restrict__ norm, unsigned int *__restrict__ max_bits,
+                                                       bool whole) {
+    quantize_body<G, VEC>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, blockIdx.x, gridDim.x, whole);
 }
 
 // Per-row candidate certificate (see launch_certify in dist.hpp for the bound).
@@ -772,12 +855,32 @@ hipError_t launch_scatter_fallback(const int32_t *rows, int64_t nrows, const flo
     return hipGetLastError();
 }
 
+template <int G>
+static void launch_quantize_g(const float *X, int64_t n, int64_t src_n, int d, int prec, void *out, float *sc,
+                              float *norm, unsigned int *max_bits, bool vec, hipStream_t stream) {
+    const dim3 g((unsigned)split_blocks(n, G)), b(256);
+    const bool whole = (reinterpret_cast<uintptr_t>(out) & 7u) == 0;
+    if (vec)
+        hipLaunchKernelGGL((quantize_kernel<G, true>), g, b, 0, stream, X, n, src_n, d, prec, out, sc, norm, max_bits,
+                           whole);
+    else
+        hipLaunchKernelGGL((quantize_kernel<G, false>), g, b, 0, stream, X, n, src_n, d, prec, out, sc, norm, max_bits,
+                           whole);
+}
+
 hipError_t launch_quantize(const float *X, int64_t n, int d, int prec, void *out, float *scale_out,
-                           hipStream_t stream, int64_t src_n) {
+                           hipStream_t stream, float *norm, unsigned int *max_bits, int64_t src_n) {
     if (n == 0) return hipSuccess;
-    const int dq = (d + kQuantPad - 1) / kQuantPad * kQuantPad;
-    hipLaunchKernelGGL(quantize_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream, X, n, src_n, d, prec,
-                       dq, out, scale_out);
+    const bool vec = d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
+    switch (lanes_for(d, vec)) {
+        case 1: launch_quantize_g<1>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+        case 2: launch_quantize_g<2>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+        case 4: launch_quantize_g<4>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+        case 8: launch_quantize_g<8>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+        case 16: launch_quantize_g<16>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+        case 32: launch_quantize_g<32>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+        default: launch_quantize_g<64>(X, n, src_n, d, prec, out, scale_out, norm, max_bits, vec, stream); break;
+    }
     return hipGetLastError();
 }
 
@@ -871,14 +974,13 @@ __global__ __launch_bounds__(256) void split_group_kernel(const PrepSeg *__restr
                        a.scale, a.norm, a.max_bits, blockIdx.x - first[s], first[s + 1] - first[s]);
 }
 
+template <int G, bool VEC>
 __global__ __launch_bounds__(256) void quantize_group_kernel(const PrepSeg *__restrict__ segs,
                                                              const uint32_t *__restrict__ first, uint32_t nseg) {
     const uint32_t s = segment_of(first, nseg, blockIdx.x);
     const PrepSeg &a = segs[s];
-    const int dq = (a.d + kQuantPad - 1) / kQuantPad * kQuantPad;
-    const int64_t step = (int64_t)(first[s + 1] - first[s]) * 4;
-    for (int64_t i = (int64_t)(blockIdx.x - first[s]) * 4 + threadIdx.x / kWave; i < a.n; i += step)
-        quantize_row(a.X, a.n, a.src_n, a.d, a.prec, dq, a.out, a.scale, i);
+    quantize_body<G, VEC>(a.X, a.n, a.src_n, a.d, a.prec, a.out, a.scale, a.norm, a.max_bits, blockIdx.x - first[s],
+                          first[s + 1] - first[s], true);
 }
 
 __global__ __launch_bounds__(256) void gather_group_kernel(const PrepSeg *__restrict__ segs,
@@ -944,7 +1046,7 @@ bool vec_rows(const float *X, int d) { return d % 4 == 0 && (reinterpret_cast<ui
 
 // A class: the step, the lanes per row (or one class for all) and 16-byte loads.
 int prep_class(const PrepSeg &a) {
-    if (a.kind == kPrepQuant || a.kind == kPrepGather) return a.kind * 256;
+    if (a.kind == kPrepGather) return a.kind * 256;
     const bool vec = vec_rows(a.X, a.d);
     return a.kind * 256 + lanes_for(a.d, vec) * 2 + vec;
 }
@@ -955,9 +1057,8 @@ std::vector<SegClass> group_prep(std::vector<PrepSeg> &segs, std::vector<uint32_
     return group_segments(segs, first, prep_class, [](const PrepSeg &a) -> int64_t {
         const int G = prep_class(a) % 256 / 2;
         if (a.kind == kPrepNorm) return sqnorm_blocks(a.n, G);
-        if (a.kind == kPrepSplit) return split_blocks(a.n, G);
-        const int64_t b = (a.n + 3) / 4;
-        return a.kind == kPrepQuant && b > 65536 ? 65536 : b;
+        if (a.kind == kPrepSplit || a.kind == kPrepQuant) return split_blocks(a.n, G);
+        return (a.n + 3) / 4;
     });
 }
 
@@ -993,7 +1094,16 @@ hipError_t launch_prep_group(const SegClass &c, const PrepSeg *segs, const uint3
     const uint32_t *f = first + c.first0;
     const int kind = c.key / 256, inst = c.key % 256;
     if (kind == kPrepQuant) {
-        hipLaunchKernelGGL(quantize_group_kernel, g, b, 0, stream, s, f, c.nseg);
+        switch (inst) {
+            KNN_LANES_CASE(quantize_group_kernel, 1)
+            KNN_LANES_CASE(quantize_group_kernel, 2)
+            KNN_LANES_CASE(quantize_group_kernel, 4)
+            KNN_LANES_CASE(quantize_group_kernel, 8)
+            KNN_LANES_CASE(quantize_group_kernel, 16)
+            KNN_LANES_CASE(quantize_group_kernel, 32)
+            KNN_LANES_CASE(quantize_group_kernel, 64)
+            default: return hipErrorInvalidValue;
+        }
     } else if (kind == kPrepGather) {
         hipLaunchKernelGGL(gather_group_kernel, g, b, 0, stream, s, f, c.nseg);
     } else if (kind == kPrepSplit) {

@@ -186,7 +186,8 @@ hipError_t launch_rerank(const RerankArgs &a, hipStream_t stream);
 // power-of-two scale (prec 2) into rows of dq = round_up(d, kQuantPad)
 // elements; scale_out (FP8 only) receives 2^-e per row.
 hipError_t launch_quantize(const float *X, int64_t n, int d, int prec, void *out, float *scale_out,
-                           hipStream_t stream, int64_t src_n = 0);
+                           hipStream_t stream, float *norm = nullptr, unsigned int *max_bits = nullptr,
+                           int64_t src_n = 0);
 // Per-row certificate of a candidate list.  The reduced key of column j,
 // ||c_j||^2 - 2 q_i.c_j, is computed with an error of at most
 //   E_i = (gamma + 2u) max ||c||^2 + 2 (rel + 2u) ||q_i|| max ||c||
@@ -246,8 +247,8 @@ hipError_t launch_unit_rows(const float *X, int64_t n, int d, bool centre, float
 // ---- the same steps over many matrices in one launch (batches) -----------------
 enum : int { kPrepNorm = 0, kPrepSplit = 1, kPrepQuant = 2, kPrepGather = 3 };
 // One matrix of a preparation step: its n rows, or (src_n > 0) rows
-// floor(i src_n / n) of its src_n.  Norms (launch_sqnorm), two-half operands with
-// norms (launch_split), quantised rows (launch_quantize), or copied rows.
+// floor(i src_n / n) of its src_n.  Norms (launch_sqnorm), two-half operands or
+// quantised rows with norms (launch_split, launch_quantize), or copied rows.
 struct PrepSeg {
     int kind;
     const float *X;

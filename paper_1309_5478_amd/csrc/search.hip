@@ -111,21 +111,21 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     // split operands of the whole corpus: made once, with the norms
     const bool whole = p.split && p.Nb >= n;
     if (whole) KNN_TRY(launch_split(C, n, d, b.Cq, b.cs, b.cnorm, b.cmax2, stream));
-    else if (!p.few) KNN_TRY(launch_sqnorm(C, n, d, b.cnorm, b.cmax2, stream));
+    else if (p.prec == kPrecF32 && !p.few) KNN_TRY(launch_sqnorm(C, n, d, b.cnorm, b.cmax2, stream));
     const float *qn2 = b.qn2;  // a graph's queries are its corpus
     if (graph) qn2 = b.cnorm;
-    else if (!p.split && !p.few) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
+    else if (p.prec == kPrecF32 && !p.split && !p.few) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
     const void *Qq = nullptr, *Cq = nullptr;
     const float *qsc = nullptr, *csc = nullptr;
-    if (p.prec != kPrecF32) {
-        KNN_TRY(launch_quantize(C, n, d, p.prec, b.Cq, b.cs, stream));
+    if (p.prec != kPrecF32) {  // quantised rows, and the norms from the same read
+        KNN_TRY(launch_quantize(C, n, d, p.prec, b.Cq, b.cs, stream, b.cnorm, b.cmax2));
         Cq = b.Cq;
         csc = b.cs;
         if (graph) {
             Qq = b.Cq;
             qsc = b.cs;
         } else {
-            KNN_TRY(launch_quantize(Q, m, d, p.prec, b.Qq, b.qs, stream));
+            KNN_TRY(launch_quantize(Q, m, d, p.prec, b.Qq, b.qs, stream, b.qn2));
             Qq = b.Qq;
             qsc = b.qs;
         }
@@ -295,10 +295,11 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         csn = b.csn;
         if (p.split) {
             KNN_TRY(launch_split(C, p.S, d, b.Csq, b.css, b.csn, nullptr, stream, n));
+        } else if (p.prec != kPrecF32) {
+            KNN_TRY(launch_quantize(C, p.S, d, p.prec, b.Csq, b.css, stream, b.csn, nullptr, n));
         } else {
             KNN_TRY(launch_gather_rows(C, n, d, nullptr, p.S, b.Cs, b.cnorm, b.csn, stream));
             Cs = b.Cs;
-            if (p.prec != kPrecF32) KNN_TRY(launch_quantize(b.Cs, p.S, d, p.prec, b.Csq, b.css, stream));
         }
         if (p.split || p.prec != kPrecF32) {
             Csq = b.Csq;
