@@ -170,9 +170,10 @@ const char *knn_last_error(knn_handle_t h);
  *
  * Few long rows: the paper's GPU is only saturated with enough rows in flight
  * (Results, Figure 8; Discussion).  When the rows are too few to give every
- * resident workgroup one, each row is cut into parts of at least
- * max(65536, 32 k) columns (a power of two of them; max(4096, 32 k) when
- * forced), every part's k smallest keys are selected by its own workgroup, and
+ * resident workgroup one, each row is cut into a power of two of parts: of at
+ * most 16384 columns, selected on chip (sample pivots and k <= 512; rows longer
+ * than that), else of at least max(65536, 32 k) (max(4096, 32 k) when forced).
+ * Every part's k smallest keys are selected by its own workgroup, and
  * the parts' lists are merged by key-list selections; the result is the same,
  * bit for bit.  The flags KNN_FLAG_NO_SPLIT / KNN_FLAG_FORCE_SPLIT turn this
  * off / force it.

@@ -904,7 +904,16 @@ SplitPlan select_split_plan(int64_t rows, uint32_t cols, uint32_t k, int num_cu,
     uint32_t group = 2;
     while (2ull * group * k <= (uint64_t)kSelectKeysCap) group *= 2;
     uint32_t parts = 1;
-    const bool in_registers = !force && sample && k <= kShortMaxK && cols > kShortMaxCols;  // (chunks of 4 Ki and up)
+    // Parts of at most 16384 columns, selected on chip (chunks of 4 Ki and up),
+    // pay for little data and few keys: their number grows with the data and each
+    // hands k keys to the merges, where the longer streamed parts only get longer.
+    // Up to 2^25 entries, from k = 65 on to 20 * 2^20 (streamed / on chip, us, rows x
+    // columns: k = 10 32 x 2^20 54 / 44, 100 x 300001 56 / 52, 64 x 2^20 71 / 75, 256 x
+    // 2^20 215 / 249; k = 100 64 x 300001 62 / 48, 32 x 2^20 63 / 63, 64 x 2^20 83 / 106;
+    // k = 400 64 x 300001 109 / 102, 400 x 65536 83 / 92, 128 x 2^20 153 / 322).
+    const uint64_t entries = (uint64_t)rows * cols;
+    const bool in_registers = !force && sample && k <= kShortMaxK && cols > kShortMaxCols &&
+                              entries <= (k <= 64 ? 32ull : 20ull) << 20;
     if (in_registers) {
         while (parts < (1u << 20) && ((uint64_t)cols + parts - 1) / parts > kShortMaxCols) parts *= 2;
         while (rows * (int64_t)parts < num_cu && 2 * parts <= group && cols / parts >= 8192u &&
