@@ -609,8 +609,10 @@ __device__ __forceinline__ void quantize_body(const float *__restrict__ X, int64
         }
         each(four, dq, [&](int t, const f32x4 &v) {
             uint32_t q = 0;
+            if (t < d) {  // (the padding of a short row is most of it)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) q |= (uint32_t)f32_to_e4m3(ldexpf(v[c], e)) << (8 * c);
+                for (int c = 0; c < 4; ++c) q |= (uint32_t)f32_to_e4m3(ldexpf(v[c], e)) << (8 * c);
+            }
             if (!in) return;
             if (whole) {
                 *reinterpret_cast<uint32_t *>(o + t) = q;

@@ -569,8 +569,18 @@ __global__ __launch_bounds__(kShortThreads, PER == 16 ? 4 : 6) void select_keys_
 // ---- host side --------------------------------------------------------------
 // Only for the sample rule, which leaves the first pivot to the library (the
 // plain and learned rules name theirs).
+// With thousands of rows what counts is the work per row, and there the streamed
+// selection is ahead for many keys of the shortest and the longest rows
+// (streamed / on chip, us: 2500 rows of 1500, k = 200 60 / 70; 5000 rows k = 300 9000
+// columns 117 / 127, 16384 127 / 156; 16384 rows k = 128 14000 309 / 326, 16384 289 /
+// 346, k = 200 1500 278 / 390, 9000 282 / 328; on chip ahead at 1200 rows, and from
+// 4096 to 8192 columns everywhere).
 bool select_short_applies(const SelectArgs &a) {
-    return a.mode == kPivotSample && !a.keys && select_short_shape(a.cols, a.k);
+    if (a.mode != kPivotSample || a.keys || !select_short_shape(a.cols, a.k)) return false;
+    if (a.split > 1) return true;
+    if (a.k > 128 && a.cols <= kShortSortCols) return a.rows < 2000;
+    if (a.k > 128 && a.cols > 8192) return a.rows < 4096;
+    return !(a.k > 64 && a.cols > 13000 && a.rows >= 8192);
 }
 
 // Resident workgroups per CU of an instance.
