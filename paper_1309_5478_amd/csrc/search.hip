@@ -18,8 +18,11 @@
 //     final k, in (distance, index) order.
 // When the sample is the whole corpus (small corpora), step 1 already selects
 // each row's kk smallest keys and steps 2-3 are skipped.
-// Unfused path (KNN_FLAG_UNFUSED): blocks of the distance matrix are
-// materialised and selected directly, then re-ranked the same way.
+// FP32 products run on two FP16 halves per operand where those serve (plan_split),
+// the operands made with the norms; BF16 and FP8 rows likewise.
+// Unfused path (KNN_FLAG_UNFUSED, a few queries (plan_few) and short corpora
+// (plan_dense)): blocks of the distance matrix are materialised and selected
+// directly, then re-ranked the same way.
 #include <cmath>
 #include <string>
 #include <vector>
