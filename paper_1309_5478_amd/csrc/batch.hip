@@ -524,6 +524,7 @@ RerankArgs rerank_args(const BatchState &b, size_t pi) {
         rr.nu = b.sh.nu + pi;
         rr.tfix = pt.tfix;
         rr.force = p.force_rerun;
+        rr.rel_fix = pt.direct ? p.rel : p.gamma;  // (other parts: re-run from the FP32 product)
     }
     return rr;
 }

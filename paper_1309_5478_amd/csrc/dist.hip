@@ -411,6 +411,26 @@ __device__ __forceinline__ float rerank_dist(const float *__restrict__ q, const 
     return s;
 }
 
+// The certificate of row i (RerankArgs), whose k-th candidate by distance is
+// `kth`.  In FP64: nothing is added to the bounds for their own evaluation.
+__device__ __forceinline__ void rerank_certify(const RerankArgs &a, int64_t i, uint64_t kth) {
+    const double u2 = kKeyU2, g = a.gamma, gd = g + 2.0 * u2;
+    const double q2 = a.qnorm2[i], c2 = __uint_as_float(*a.cmax2_bits), qc = sqrt(q2 * c2);
+    // (1.001: norms and products of them that are themselves rounded)
+    const double nrm = (g + u2) * c2, E = 1.001 * (nrm + 2.0 * (a.rel + u2) * qc);
+    const double Ef = 1.001 * (nrm + 2.0 * (a.rel_fix + u2) * qc);
+    const float *key = a.keys + i * a.kk;
+    double U = (double)key[a.k - 1] + E;
+    const double byd = (double)ord_to_float(key_ord(kth)) / (1.0 - gd) - q2 * (1.0 - g);
+    if (byd < U) U = byd;  // (false for NaN)
+    if (!a.force && (double)key[a.kk - 1] - E > U) return;
+    const double t = U + Ef;
+    float tf = (float)t;
+    if ((double)tf < t) tf = nextafterf(tf, __uint_as_float(0x7f800000u));
+    a.tfix[i] = tf;
+    a.ulist[atomicAdd(a.nu, 1u)] = (int32_t)i;
+}
+
 template <int G, bool VEC>
 __device__ __forceinline__ void rerank_body(const RerankArgs &a, int64_t i) {
     constexpr uint32_t PPW = kWave / G;                       // candidates per wave per pass
@@ -428,14 +448,6 @@ __device__ __forceinline__ void rerank_body(const RerankArgs &a, int64_t i) {
         // (1.001: slack for the FP32 evaluation; 4 u: the differences, products
         // and the last sums of the direct form)
         const float ak = key[a.k - 1], T = ak + 2.002f * (E + (a.gamma + 2.0f * kKeyU2) * (qm + cm) * (qm + cm));
-        if (a.ulist && tid == 0) {
-            // the row's certificate (as certify_body's)
-            const float C = 1.001f * E;
-            if (a.force || !(key[a.kk - 1] - ak > 2.0f * C)) {
-                a.ulist[atomicAdd(a.nu, 1u)] = (int32_t)i;
-                a.tfix[i] = ak + 2.0f * C;
-            }
-        }
         if (fabsf(T) <= 3.4028235e38f) {  // a bound exists (false for NaN): the keys up to T, in order
             kk = 0;
             for (uint32_t t0 = 0; t0 < a.kk; t0 += kRerankThreads) {
@@ -468,6 +480,7 @@ __device__ __forceinline__ void rerank_body(const RerankArgs &a, int64_t i) {
     }
     __syncthreads();
     block_sort<kRerankThreads>(keys, kk);
+    if (a.ulist && tid == 0) rerank_certify(a, i, a.k <= (int)kk ? keys[a.k - 1] : kKeyMax);
     for (uint32_t t = tid; t < (uint32_t)a.k; t += kRerankThreads) {
         const uint64_t key = t < kk ? keys[t] : kKeyMax;
         if (key == kKeyMax) {

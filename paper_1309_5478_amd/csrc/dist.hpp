@@ -81,12 +81,21 @@ struct RerankArgs {
     const float *qnorm2 = nullptr;
     const unsigned int *cmax2_bits = nullptr;
     float rel = 0.f, gamma = 0.f;
-    // With keys, optional: the certificate of every row (CertifyArgs: list, nlist,
-    // tfix, force), in the same launch.
+    // With keys, optional: the certificate of every row, in the same launch.  E and
+    // E' are CertifyArgs' bound with rel and with rel_fix (of the keys that a re-run
+    // reads).  Every one of the k nearest has an exact key of at most
+    //   U = min(key_k + E, D / (1 - gamma') - |q|^2 (1 - gamma)),
+    // D the k-th direct-form distance among the candidates and gamma' that form's
+    // error, and every point outside the candidates one of at least key_kk - E.  A
+    // row with key_kk - E <= U is appended to ulist (count in *nu), with the bound U +
+    // E' of what a re-run has to look at in tfix (NaN or infinite: everything).
+    // The second bound of U needs E once where the gap of two keys needs it twice,
+    // and decides where |q| is near max |c|: points far from the origin.
     int32_t *ulist = nullptr;
     uint32_t *nu = nullptr;
     float *tfix = nullptr;
-    int force = 0;
+    int force = 0;             // list every row
+    float rel_fix = 0.f;
 };
 
 hipError_t launch_dist_gemm(const DistArgs &a, int epi, hipStream_t stream);

@@ -240,9 +240,19 @@ inline bool split_serves(const Plan &p) { return p.gathered && !p.unfused && spl
 inline void use_split(Plan &p) {
     p.split = true;
     p.ldq = split_row_bytes(p.d);
-    // three times the terms, each with a rounding (one accumulation of 3 d
-    // products); both operands within 2^-23 of themselves; low x low left out
-    p.rel = (float)(std::ldexp(1.0, -21) + 3.0 * p.gamma);
+    // Both operands are within 2^-23 of themselves, and low x low is left out: 2^-21.
+    // The sums: one instruction adds 16 products to its accumulator with an error
+    // of at most 2 u + u / 2 per product that is not zero, of the sum of all their
+    // magnitudes (products are cut where they lie 25 bits below the largest term;
+    // over 4 10^8 sums of one to 16 products, of every sign, spread and ratio to
+    // the accumulator up to 2^30: at most 2.0 u of one product, 5.4 u of 16); three
+    // products per element, three instructions per 16 elements.  That is less than
+    // twice the FP32 instruction's gamma; the certificate (RerankArgs) asks for no
+    // more than the gap of two keys of that one did: points of a mean far above
+    // their spread keep theirs (32768 uniform points in [8, 9)^128: with 3 gamma and the
+    // gap of two keys 32070 rows re-run, 7.4 ms, this way 6, 1.7 ms; in [4, 5)^1024 all
+    // rows either way, 286 and 38 ms, and 65 with the FP32 instruction and that gap).
+    p.rel = (float)(std::ldexp(1.0, -21) + std::ldexp(1.5 * p.d + 6.0 * ((p.d + 15) / 16), -24));
 }
 
 // The single call's choice: also once there is work for the large tiles

@@ -160,7 +160,8 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     // certificate and exact re-rank of one block's kk candidates (ascending
     // reduced keys `keys`, corpus indices `cidx`): FP32 rows without a certificate
     // are listed for the re-run, b.nu of them
-    auto candidates = [&](const float *keys, const int32_t *cidx, int64_t i0, int64_t mb) -> knn_status_t {
+    // (stored: the re-run reads the block's own keys, not ones of the FP32 product)
+    auto candidates = [&](const float *keys, const int32_t *cidx, int64_t i0, int64_t mb, bool stored) -> knn_status_t {
         RerankArgs rr{Q + i0 * d, mb, C, n, d, cidx, (uint32_t)p.kk, k, out_dist + i0 * k, out_idx + i0 * k,
                       graph ? i0 : -1, oscale};
         if (refix) {
@@ -173,6 +174,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             rr.nu = b.nu;
             rr.tfix = b.tfix;
             rr.force = p.force_rerun;
+            rr.rel_fix = stored ? p.rel : p.gamma;
         }
         KNN_TRY(launch_rerank(rr, stream));
         return KNN_SUCCESS;
@@ -248,7 +250,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
                       int64_t ldd) -> knn_status_t {
         if (refix && !counts_clear) KNN_TRY(launch_fill_u32(b.nu, 1, 0u, stream));
         counts_clear = false;
-        knn_status_t fs = candidates(keys, cidx, i0, mb);
+        knn_status_t fs = candidates(keys, cidx, i0, mb, true);
         if (fs != KNN_SUCCESS) return fs;
         if (!refix) return count_uncertified(keys, i0, mb);
         if ((fs = fetch()) != KNN_SUCCESS) return fs;
@@ -453,7 +455,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             ka.out_idx = b.si;
             ka.mode = smode;
             KNN_TRY(launch_select_keys(ka, num_cu, stream));
-            return candidates(b.sv, b.si, i0, mb);
+            return candidates(b.sv, b.si, i0, mb, false);
         };
         // Flagged rows are rare (a few in 10^5): a small block does not wait for
         // their number before it goes on, and starts 4 again where there are any.
