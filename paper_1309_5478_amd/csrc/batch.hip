@@ -22,7 +22,8 @@
 //    replayed by later calls with the same job table; one synchronisation then
 //    brings the counts of rows needing the exact fallback or re-run (rare) to the
 //    host;
-//  * with autotuning on, the tile shape and form of the grouped launch are
+//  * with autotuning on, the tile shape and form of the grouped launch (of the
+//    parts that are neither pipelined nor selected from their sample) are
 //    the fastest of the candidates, timed on the batch itself with a threshold
 //    of -inf (nothing is kept, so the timing run has no effect on the results).
 // Jobs with more than kRowBlock queries are split into parts of at most that
@@ -595,6 +596,7 @@ hipError_t enqueue_product(const BatchState &b, const DistArgs *table, int tile,
     for (const BatchPart &pt : b.parts) {
         if (pt.grouped || pt.pipe || pt.direct) continue;
         DistArgs fa = part_args(b, pt);
+        fa.tile = tile;
         if (table == b.sh.probe) {
             fa.tau = b.sh.ninf;
             fa.tau_stride = 0;
@@ -1067,19 +1069,26 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
             if (ue == hipSuccess) uploaded = tile;
             return ue;
         };
-        if (tune) {
-            // key: device, precision, work-weighted dimension and corpus size, total work
+        // the parts whose product takes a tile shape: neither pipelined nor selected
+        // from their sample (without one there is nothing to choose)
+        auto tiled = [&](const BatchPart &pt) { return !pt.pipe && !pt.direct; };
+        if (tune && std::any_of(b.parts.begin(), b.parts.end(), tiled)) {
+            // key: device, precision, and the work-weighted dimension and corpus
+            // size and the work of those parts ("tiled": entries without it counted
+            // every job, timed or not)
             double w = 0, wd = 0, wn = 0;
-            for (const BatchJob &js : b.jobs) {
-                w += js.cost;
-                wd += js.cost * js.d;
-                wn += js.cost * (double)js.n;
+            for (const BatchPart &pt : b.parts) {
+                if (!tiled(pt)) continue;
+                const BatchJob &js = b.jobs[pt.job];
+                const double cost = 2.0 * (double)pt.mb * (double)js.n * js.d;
+                w += cost;
+                wd += cost * js.d;
+                wn += cost * (double)js.n;
             }
-            w = w > 0 ? w : 1;
             const std::string tkey = "grouped|" + h->arch + "|cu" + std::to_string(num_cu) + "|p" +
                                      std::to_string(prec) + "|d" + std::to_string(size_bucket((int64_t)(wd / w))) +
                                      "|n" + std::to_string(size_bucket((int64_t)(wn / w))) + "|f" +
-                                     std::to_string(size_bucket((int64_t)(w / 1e6)));
+                                     std::to_string(size_bucket((int64_t)(w / 1e6))) + "|tiled";
             int choice = autotune_lookup(tkey);
             if (choice < 0) {
                 std::vector<DistArgs> probe = table;
