@@ -196,7 +196,8 @@ __global__ __launch_bounds__(256) void sqnorm_kernel(const float *__restrict__ X
 
 // ---- FP32 operands as two FP16 halves ----------------------------------------
 // The point scaled by 2^e, its largest finite magnitude into [2^14, 2^15) (e in
-// [-113, 100]; 0 for a zero point), each element as h = FP16(x 2^e) and l =
+// [-113, 126]; 0 for a zero point; at e = 126, magnitudes below 2^-111, two halves
+// still hold what an FP32 element holds), each element as h = FP16(x 2^e) and l =
 // FP16(x 2^e - h), both to nearest even; the subtraction is exact.  A
 // non-finite element keeps its infinity or NaN in h with l = 0.  The squared
 // norms come from the same read, in sqnorm_kernel's order.  Memory-bound: 4 d
@@ -242,7 +243,7 @@ __device__ __forceinline__ void split_body(const float *__restrict__ X, int64_t 
             int E;
             (void)frexpf(am, &E);  // am = f 2^E, f in [0.5, 1)
             e = 15 - E;
-            e = e < -113 ? -113 : (e > 100 ? 100 : e);
+            e = e < -113 ? -113 : (e > 126 ? 126 : e);
         }
         const float up = ldexpf(1.0f, e);
         if (in && sub == 0) {
