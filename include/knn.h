@@ -129,7 +129,8 @@ typedef struct {
     int64_t rows;                 /* rows processed by the last call; with        */
                                   /* split_parts > 1 the counters below sum (and  */
                                   /* passes_max maximises) over the parts         */
-    int64_t passes_total;         /* partition passes summed over rows            */
+    int64_t passes_total;         /* partition passes summed over rows (rows held */
+                                  /* on chip whole: counting passes)              */
     int32_t passes_max;           /* most partition passes on one row             */
     int32_t split_parts;          /* select_k: parts each row was cut into (1:    */
                                   /* whole rows, one workgroup each)              */

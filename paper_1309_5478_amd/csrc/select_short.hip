@@ -59,8 +59,12 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
     uint64_t *const xchg = reinterpret_cast<uint64_t *>(xs);
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const float qnan = __uint_as_float(0x7fc00000u);
-    unsigned long long survivors = 0;
-    uint32_t rows_done = 0;
+    // row statistics (the same in every thread; the last thing that the workgroup writes)
+    unsigned long long survivors = 0, passes = 0, cyc_pivot = 0, cyc_read = 0, cyc_keep = 0, cyc_sort = 0;
+    uint32_t rows_done = 0, passes_max = 0;
+    // (a reading waits for the wave's LDS accesses: 0.4 of 19 us with a row per workgroup)
+    const bool timed = a.slots != nullptr;
+    auto now = [timed]() -> long long { return timed ? clock64() : 0; };
     for (int64_t r = blockIdx.x; r < a.rows; r += gridDim.x) {
         const float *dist = a.dist;
         int64_t ld = a.ld, lr = r, orow = r;
@@ -87,6 +91,7 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
             out_idx = sg.out_idx;
         }
         const float *row = dist + lr * ld + col_off;
+        const long long t0 = now();
 
         // the row, 16 bytes per load whatever its alignment (load u of a thread:
         // columns 1024 u + 4 tid .. + 3), into LDS and the minima of four groups
@@ -127,6 +132,7 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
         // (each thread reads back only what it wrote)
         auto values = [&](uint32_t u) -> f32x4 { return *reinterpret_cast<const f32x4 *>(xs + u * kBlock + 4 * tid); };
 
+        const long long t1 = now();
         // groups merged to two or one per thread when k leaves fewer enough
         uint32_t pord = kOrdNaN;
         // short enough to sort whole, and too short (a row's last part) or k too large for groups
@@ -154,7 +160,9 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
             for (int w = 1; w < kShortWaves; ++w) pord = pord > red[0][w] ? pord : red[0][w];
         }
 
+        const long long t2 = now();
         // survivors, in the wave's own segment; a wave with too many counts on
+        uint32_t row_passes = 0;  // counting passes
         uint32_t c = 0, start[kShortWaves];
         bool fits = true;
         if (all) {
@@ -220,6 +228,7 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
             };
             auto count_upto = [&](uint32_t t) -> uint32_t {
                 uint32_t n = 0;
+                ++row_passes;
 #pragma unroll 1
                 for (uint32_t u = 0; u < blocks; ++u) {
                     const f32x4 v = values(u);
@@ -320,6 +329,9 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
         __syncthreads();  // keys written, the row read
         survivors += c;
         ++rows_done;
+        passes += row_passes;
+        passes_max = passes_max > row_passes ? passes_max : row_passes;
+        const long long t3 = now();
 
         // the segments' keys as one list, sorted in registers
         auto load = [&](uint32_t p) -> uint64_t {
@@ -364,10 +376,26 @@ __global__ __launch_bounds__(kShortThreads) void select_short_kernel(SelectArgs 
             for (uint32_t t = tid; t < k; t += kShortThreads) emit(t, xchg[t]);
         }
         __syncthreads();  // keys, row and counts are reused by the next row
+        cyc_read += (unsigned long long)(t1 - t0);
+        cyc_pivot += (unsigned long long)(t2 - t1);
+        cyc_keep += (unsigned long long)(t3 - t2);
+        cyc_sort += (unsigned long long)(now() - t3);
     }
-    if (a.slots && tid < (uint32_t)kSelSlot)
-        a.slots[(size_t)blockIdx.x * kSelSlot + tid] =
-            tid == kSlotRows || tid == kSlotStreamPasses ? rows_done : (tid == kSlotFirstSurvivors ? survivors : 0ull);
+    if (a.slots && tid < (uint32_t)kSelSlot) {
+        unsigned long long v = 0;
+        switch (tid) {
+            case kSlotRows:
+            case kSlotStreamPasses: v = rows_done; break;
+            case kSlotPasses: v = passes; break;
+            case kSlotPassesMax: v = passes_max; break;
+            case kSlotFirstSurvivors: v = survivors; break;
+            case kSlotCycles + 0: v = cyc_pivot; break;
+            case kSlotCycles + 1: v = cyc_read; break;
+            case kSlotCycles + 2: v = cyc_keep; break;
+            case kSlotCycles + 3: v = cyc_sort; break;
+        }
+        a.slots[(size_t)blockIdx.x * kSelSlot + tid] = v;
+    }
 }
 
 // Selection of the k smallest of each row's list of at most 4096 distinct keys
