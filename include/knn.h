@@ -138,7 +138,10 @@ typedef struct {
     int64_t spill_rows;           /* rows whose candidates left on-chip memory    */
     int64_t first_pass_survivors; /* keys kept by the first pass, summed          */
     int64_t fallback_rows;        /* search / graph rows re-run on the exact path */
-    int64_t candidates_total;     /* search / graph candidates, summed            */
+    int64_t candidates_total;     /* search / graph candidates, summed (oversample */
+                                  /* * k per row where its keys are stored; 0     */
+                                  /* with KNN_FLAG_UNFUSED and where the corpus   */
+                                  /* is its own threshold sample)                 */
     int64_t phase_cycles[4];      /* shader clocks summed over rows: first pivot, */
                                   /* streaming passes, on-chip passes, final sort */
     double product_ms;            /* KNN_FLAG_TIMING: summed duration of the main  */

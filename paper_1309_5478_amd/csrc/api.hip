@@ -77,6 +77,7 @@ void add_host_stats(knn_handle_t h, int64_t rows, int64_t fallback_rows) {
     h->host_fallback += fallback_rows;
 }
 void add_host_rerun(knn_handle_t h, int64_t rows) { h->host_rerun += rows; }
+void add_host_candidates(knn_handle_t h, int64_t n) { h->host_candidates += n; }
 void add_product_time(knn_handle_t h, double ms, double flops) {
     h->host_product_ms += ms;
     h->host_product_flops += flops;
@@ -224,6 +225,7 @@ static knn_status_t begin_stats(knn_handle_t h, hipStream_t stream, int slots = 
     h->host_rows = 0;
     h->host_fallback = 0;
     h->host_rerun = 0;
+    h->host_candidates = 0;
     h->host_product_ms = 0;
     h->host_product_flops = 0;
     h->host_product_launches = 0;
@@ -550,7 +552,7 @@ knn_status_t knn_get_stats(knn_handle_t h, knn_stats_t *out) {
         // (FP32 rows without a certificate are the ones re-run)
         t.rows_uncertified = (int64_t)s[kStatUncertified] + h->host_rerun;
         t.rows_rerun = h->host_rerun;
-        t.candidates_total = (int64_t)s[kStatCandidates];
+        t.candidates_total = (int64_t)s[kStatCandidates] + h->host_candidates;
         t.phase_cycles[0] = (int64_t)s[kStatCycSample];
         t.phase_cycles[1] = (int64_t)s[kStatCycStream];
         t.phase_cycles[2] = (int64_t)s[kStatCycSelect];

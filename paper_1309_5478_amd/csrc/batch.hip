@@ -49,6 +49,7 @@ knn_status_t fail_msg(knn_handle_t h, knn_status_t s, const std::string &msg);
 unsigned long long *stats_ptr(knn_handle_t h);
 void add_host_stats(knn_handle_t h, int64_t rows, int64_t fallback_rows);
 void add_host_rerun(knn_handle_t h, int64_t rows);
+void add_host_candidates(knn_handle_t h, int64_t n);
 int handle_num_cu(knn_handle_t h);
 const uint16_t *handle_net(knn_handle_t h);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t stream);
@@ -1204,6 +1205,8 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
 #undef KTRY
     add_host_stats(h, rows, fallback);
     add_host_rerun(h, rerun);
+    for (const BatchJob &js : b.jobs)
+        if (js.p.stored) add_host_candidates(h, js.m * js.p.kk);
     return KNN_SUCCESS;
 }
 

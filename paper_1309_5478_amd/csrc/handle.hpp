@@ -31,7 +31,7 @@ struct knn_handle_s {
     hipStream_t last_stream = nullptr;
     knn_stats_t last{};
     bool stats_pending = false;
-    int64_t host_rows = 0, host_fallback = 0, host_rerun = 0;  // host-side counters of the last call
+    int64_t host_rows = 0, host_fallback = 0, host_rerun = 0, host_candidates = 0;  // host-side counters of the last call
     double host_product_ms = 0, host_product_flops = 0;
     int64_t host_product_launches = 0;
     int32_t last_split_parts = 1;              // parts per row of the last knn_select_k

@@ -48,6 +48,7 @@ struct Plan {
     bool graph, unfused;
     int force;
     int force_rerun;
+    bool stored;       // keys stored and selected from where the corpus is larger than its sample: k' candidates a row
     bool few;          // a few queries: their distance rows stored in one pass over the corpus (with unfused)
     bool split;        // FP32 product on two-half operands (ldq: bytes per split row)
     int64_t Nb;        // corpus points whose operands are held at a time
@@ -284,6 +285,7 @@ inline void plan_few(Plan &p) {
     if (few_passes(p.m, p.d) == 0 || (p.m > 3 * (int64_t)p.d && p.m * p.n > (1 << 25))) return;
     if ((size_t)p.m * (size_t)p.n * sizeof(float) > kDenseBytes) return;
     p.few = p.unfused = true;
+    p.stored = p.gathered;
     p.Mu = p.m;
 }
 
@@ -321,6 +323,7 @@ inline void plan_dense(Plan &p, int smode) {
     p.Mu = mu < p.m ? mu : p.m;
     p.Mb = p.Mu;
     p.unfused = true;
+    p.stored = p.gathered;
 }
 
 // The same in a batch, whose jobs keep their sample distances: the sample is the
@@ -328,6 +331,7 @@ inline void plan_dense(Plan &p, int smode) {
 inline void plan_direct(Plan &p) {
     p.S = (int)p.n;
     p.gathered = false;
+    p.stored = true;
     p.r = p.kk - 1;
 }
 

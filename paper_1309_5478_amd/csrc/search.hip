@@ -44,6 +44,7 @@ unsigned long long *stats_ptr(knn_handle_t h);
 uint32_t *search_words(knn_handle_t h);
 void add_host_stats(knn_handle_t h, int64_t rows, int64_t fallback_rows);
 void add_host_rerun(knn_handle_t h, int64_t rows);
+void add_host_candidates(knn_handle_t h, int64_t n);
 void add_product_time(knn_handle_t h, double ms, double flops);
 int handle_num_cu(knn_handle_t h);
 const uint16_t *handle_net(knn_handle_t h);
@@ -290,6 +291,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         }
         add_host_stats(h, m, 0);
         add_host_rerun(h, rerun_total);
+        if (p.stored) add_host_candidates(h, m * p.kk);
         return KNN_SUCCESS;
     }
 
