@@ -1,12 +1,12 @@
 """candidates_total of searches whose keys are stored (few queries, short corpora):
 the candidates that each row's selection hands on."""
 import pytest
+import torch
 
 pytestmark = pytest.mark.gpu
 
 
 def pts(n, d, seed):
-    import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     return torch.randn((n, d), generator=g, device="cuda")
