@@ -80,7 +80,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     Plan p = make_plan(m, n, d, k, graph, opt, m);
     const bool asked = p.unfused;
     plan_few(p);
-    if (!autotune_enabled(opt)) plan_dense(p, smode);  // (autotuning times the fused product)
+    plan_dense(p, smode);
     plan_split(p);
     Bufs b;
     auto need = [&]() {
@@ -258,9 +258,12 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         return rerun(i0, mb, Dblock, ldd);
     };
 
+    const std::string tune_key = "fused|" + h->arch + "|cu" + std::to_string(num_cu) + "|p" + std::to_string(p.prec) +
+                                 "|d" + std::to_string(d) + "|m" + std::to_string(size_bucket(p.unfused ? p.Mu : p.Mb)) +
+                                 "|n" + std::to_string(size_bucket(n));
     if (p.unfused) {
-        for (int64_t i0 = 0; i0 < m; i0 += p.Mu) {
-            const int64_t mb = m - i0 < p.Mu ? m - i0 : p.Mu;
+        // rows i0 .. + mb - 1 against the corpus, keys stored
+        auto dense_args = [&](int64_t i0, int64_t mb, int tile) -> DistArgs {
             DistArgs a{};
             a.Q = Q + i0 * d;
             a.m = mb;
@@ -271,12 +274,43 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
             a.self_offset = graph ? i0 : -1;
             a.out = b.Dm;
             a.ldo = n;
-            if (p.split) {
-                if (!Qq) KNN_TRY(launch_split(a.Q, mb, d, b.Qq, b.qs, b.qn2 + i0, nullptr, stream));
-                set_prec(a, Qq ? qrow(i0) : b.Qq, Qq ? qsrow(i0) : b.qs, b.Cq, b.cs);
-            } else {
-                set_prec(a, qrow(i0), qsrow(i0), Cq, csc);
+            a.tile = tile;
+            if (p.split) set_prec(a, Qq ? qrow(i0) : b.Qq, Qq ? qsrow(i0) : b.qs, b.Cq, b.cs);
+            else set_prec(a, qrow(i0), qsrow(i0), Cq, csc);
+            return a;
+        };
+        // tile shape of the product where the rows are stored by the library's
+        // choice, measured once per shape class when autotuning is on (the timed
+        // launches' keys are written again below)
+        int dtile = -1;
+        if (autotune_enabled(opt) && !asked && !p.few) {
+            const std::string key = tune_key + "|stored" + (p.split ? "|pipe" : "");
+            dtile = autotune_lookup(key);
+            if (dtile < 0) {
+                const int64_t mb = p.Mu < 8192 ? p.Mu : 8192;
+                if (p.split && !Qq) KNN_TRY(launch_split(Q, mb, d, b.Qq, b.qs, nullptr, nullptr, stream));
+                DistArgs pa = dense_args(0, mb, -1);
+                std::vector<int> cands = {kTileSmall1, kTileSmall, kTileWide};
+                if (p.prec != kPrecFP8) cands.push_back(kTileBig);
+                if (p.split) cands.insert(cands.begin(), kTilePipe);
+                auto run = [&](int t) -> hipError_t {
+                    pa.tile = t;
+                    pa.prec = p.split && t == kTilePipe ? kPrecSplit : p.prec;
+                    return launch_dist_gemm(pa, kEpiDense, stream);
+                };
+                KNN_TRY(autotune_pick(key, cands, run, stream, 2, &dtile, 0.03f));
             }
+            if (p.split && dtile != kTilePipe) {  // an FP32 tile is faster here
+                p.split = false;
+                p.rel = p.gamma;
+                if (!graph) KNN_TRY(launch_sqnorm(Q, m, d, b.qn2, nullptr, stream));
+            }
+        }
+        for (int64_t i0 = 0; i0 < m; i0 += p.Mu) {
+            const int64_t mb = m - i0 < p.Mu ? m - i0 : p.Mu;
+            if (p.split && !Qq)
+                KNN_TRY(launch_split(Q + i0 * d, mb, d, b.Qq, b.qs, b.qn2 + i0, nullptr, stream));
+            const DistArgs a = dense_args(i0, mb, dtile);
             KNN_TRY(timer.begin(stream, 2.0 * (double)mb * (double)n * d));
             if (p.few) KNN_TRY(launch_dist_few(a.Q, mb, C, n, d, b.Dm, b.qn2, b.cmax2, num_cu, stream));
             else KNN_TRY(launch_dist_gemm(a, kEpiDense, stream));
@@ -333,9 +367,7 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
         pa.cap = p.cap;
         set_prec(pa, qrow(0), qsrow(0), Cq, csc);
         const bool pipe = gemm_pipe_applies(pa, kEpiFilter);
-        const std::string key = "fused|" + h->arch + "|cu" + std::to_string(num_cu) + "|p" + std::to_string(p.prec) +
-                                "|d" + std::to_string(d) + "|m" + std::to_string(size_bucket(p.Mb)) + "|n" +
-                                std::to_string(size_bucket(n)) + (pipe ? "|pipe" : "");
+        const std::string key = tune_key + (pipe ? "|pipe" : "");
         ftile = autotune_lookup(key);
         if (ftile < 0) {
             if (p.split) {  // the timed block's operands (remade below where a block's are)
