@@ -341,7 +341,18 @@ typedef struct {
  * with a null pointer, m < 0, n < 1, d < 1, k < 1, a graph job (null queries,
  * m > 0) with m != n or n < 2, or a bad option; UNSUPPORTED for k > 1024 or n > INT32_MAX; the
  * message names the first offending job.  OUT_OF_MEMORY when the batch's
- * workspace (kept by the handle for replays) cannot be allocated.
+ * workspace cannot be allocated.
+ *
+ * Memory: the handle keeps the workspace of its last batch for replays, until a
+ * batch that needs more replaces it or the handle is destroyed.  It holds every
+ * job's candidate lists, sample distances and reduced-precision operands.  FP32 jobs
+ * add two-half operands (4 bytes per element of the job's points), the jobs with
+ * the most work first, up to 64 GiB in all, and jobs with short corpora their
+ * distance rows, up to 8 GiB in all; no more than a third and a sixth of the
+ * device memory that is free when the batch is planned, and neither of them if the
+ * workspace cannot be allocated with them.  The environment variable
+ * KNN_SPLIT_BYTES lowers the first limit (and that of 8 GiB of knn_search and
+ * knn_graph, which pass a larger corpus in blocks).  Results do not depend on it.
  */
 knn_status_t knn_batch_search(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, void *stream,
                               const knn_options_t *opt);

@@ -868,15 +868,15 @@ knn_status_t run_batch(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, hip
         b.timed = timed;
         const bool tune = autotune_enabled(&o);
         // two-half operands (as large as the points themselves) for the longest
-        // jobs first, up to a third of the memory that is free: the rest is the
-        // workspace's and the program's
-        // and, up to a sixth, whole distance rows of the jobs with short corpora
+        // jobs first, and whole distance rows of the jobs with short corpora, each
+        // within its budget: the rest is the workspace's and the program's
         size_t split_left = 0, direct_left = 0;
         if (!std::getenv("KNN_BATCH_QUEUE")) {
             size_t free_bytes = 0, total_bytes = 0;
             KTRY(hipMemGetInfo(&free_bytes, &total_bytes));
-            split_left = (free_bytes + b.ws_bytes) / 3;
-            direct_left = split_left / 2;
+            const BatchBudget most = batch_budget(free_bytes + b.ws_bytes);
+            split_left = most.split;
+            direct_left = most.rows;
         }
         for (int32_t j = 0; j < njobs; ++j) {
             const knn_job_t &jb = jobs[j];

@@ -37,6 +37,11 @@ constexpr int64_t kRowBlock = 32768;
 // against 2 Mb flops)
 constexpr size_t kSplitBytes = size_t(8) << 30;
 constexpr size_t kDenseBytes = size_t(1) << 30;  // materialised distance block budget
+// A batch holds the operands and the stored rows of all its jobs at once, and
+// keeps them for its replays: at most this much of each, and a third and a sixth
+// of what is free when it is planned (512 jobs with 101 GB of corpora want 105 and 4.3
+// GiB, and have about 55 and 4.3 beside them).
+constexpr size_t kBatchSplitBytes = size_t(64) << 30, kBatchRowBytes = size_t(8) << 30;
 
 struct Plan {
     int64_t m, n, n_eff;
@@ -256,17 +261,29 @@ inline void use_split(Plan &p) {
     p.rel = (float)(std::ldexp(1.0, -21) + std::ldexp(1.5 * p.d + 6.0 * ((p.d + 15) / 16), -24));
 }
 
+// A cap on the operands held, from the environment (KNN_SPLIT_BYTES), or `most`.
+inline size_t split_budget(size_t most) {
+    if (const char *e = std::getenv("KNN_SPLIT_BYTES")) {
+        const long long v = std::atoll(e);
+        if (v > 0 && (size_t)v < most) return (size_t)v;
+    }
+    return most;
+}
+// What a batch may take for its jobs' operands and stored rows.
+struct BatchBudget {
+    size_t split, rows;
+};
+inline BatchBudget batch_budget(size_t free_bytes) {
+    return BatchBudget{split_budget(std::min(free_bytes / 3, kBatchSplitBytes)),
+                       std::min(free_bytes / 6, kBatchRowBytes)};
+}
+
 // The single call's choice: also once there is work for the large tiles
-// (pipe_fills in gemm_pipe.hip).  KNN_SPLIT_BYTES caps the operands held (tests).
+// (pipe_fills in gemm_pipe.hip).
 inline void plan_split(Plan &p) {
     const int64_t bytes = split_row_bytes(p.d);
     if (!split_serves(p) || !pipe_fills(p.m < p.Mb ? p.m : p.Mb, p.n)) return;
-    size_t budget = kSplitBytes;
-    if (const char *e = std::getenv("KNN_SPLIT_BYTES")) {
-        const long long v = std::atoll(e);
-        if (v > 0) budget = (size_t)v;
-    }
-    int64_t nb = (int64_t)(budget / (size_t)bytes) / 256 * 256;
+    int64_t nb = (int64_t)(split_budget(kSplitBytes) / (size_t)bytes) / 256 * 256;
     if (nb < 256) nb = 256;
     p.Nb = nb < p.n ? nb : p.n;
     use_split(p);
