@@ -506,8 +506,7 @@ CertifyArgs certify_args(const BatchState &b, knn_handle_t h, size_t pi) {
     const BatchJob &js = b.jobs[pt.job];
     const Plan &p = js.p;
     return CertifyArgs{part_keys(pt), pt.mb, p.kk, js.k, js.qn2 + pt.i0, js.cmax2, p.rel, p.gamma,
-                       stats_ptr(h) + kStatUncertified, pt.ulist, b.sh.nu + pi, pt.tfix,
-                       pt.ulist != nullptr && p.force_rerun};
+                       stats_ptr(h) + kStatUncertified};
 }
 
 RerankArgs rerank_args(const BatchState &b, size_t pi) {

@@ -668,12 +668,7 @@ __device__ __forceinline__ void certify_body(const CertifyArgs &a, int64_t i) {
         const float c2 = __uint_as_float(*a.cmax2_bits), cm = sqrtf(c2), qm = sqrtf(a.qnorm2[i]);
         // 1.001: slack for the FP32 evaluation of the bound itself
         const float E = 1.001f * ((a.gamma + kKeyU2) * c2 + 2.0f * (a.rel + kKeyU2) * qm * cm);
-        bad = a.force || !(gap > 2.0f * E);
-        if (bad && a.list) {
-            const uint32_t p = atomicAdd(a.nlist, 1u);
-            a.list[p] = (int32_t)i;
-            a.tfix[i] = ak + 2.0f * E;
-        }
+        bad = !(gap > 2.0f * E);
     }
     const uint64_t b = __ballot(bad);
     if (lane_id() == 0 && b) atomicAdd(a.count, (unsigned long long)__popcll(b));

@@ -205,10 +205,8 @@ hipError_t launch_quantize(const float *X, int64_t n, int d, int prec, void *out
 // is certified when the gap between its kk-th and k-th candidate keys exceeds
 // 2 E_i: then every point outside the candidates has a larger exact key than the
 // k-th candidate, so the exact top k lie among the candidates.  Uncertified rows
-// are counted into *count and, when `list` is set, appended to list (count in
-// *nlist) with the threshold key_k + 2 E_i in tfix[i], which bounds the reduced
-// key of every exact top-k point of the row (NaN or infinite when no bound
-// exists).
+// of the reduced precisions are counted into *count.  (FP32 rows are certified
+// with their re-rank, see RerankArgs.)
 struct CertifyArgs {
     const float *sorted_keys;  // m x kk, ascending
     int64_t m;
@@ -217,10 +215,6 @@ struct CertifyArgs {
     const unsigned int *cmax2_bits;
     float rel, gamma;
     unsigned long long *count;
-    int32_t *list;             // or null
-    uint32_t *nlist;
-    float *tfix;               // m thresholds (only uncertified rows written)
-    int force;                 // treat every row as uncertified
 };
 hipError_t launch_certify(const CertifyArgs &a, hipStream_t stream);
 

@@ -141,13 +141,6 @@ __device__ __forceinline__ float shfl_xor_any(float v, int mask) {
     return __uint_as_float(xor_lanes32(__float_as_uint(v), mask));
 }
 
-// For masks only known at run time: one LDS-crossbar permute per half.
-__device__ __forceinline__ uint64_t shfl_xor_u64_rt(uint64_t v, int mask) {
-    const uint32_t lo = __shfl_xor((unsigned int)(uint32_t)v, mask);
-    const uint32_t hi = __shfl_xor((unsigned int)(uint32_t)(v >> 32), mask);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 // A structure at an address that is the same in every lane, held in scalar
 // registers (vector loads of the same words, then the first lane's copy).
 template <class T>
@@ -266,13 +259,13 @@ __device__ __forceinline__ K wave_key(const K (&k)[J], uint32_t p) {
 //
 // The direction of a step depends on bits of t: below 64 lanes it is a constant
 // lane mask, above it is the same for a whole wave.
-template <int NT, int J, bool SYNC, class K, class Load>
-__device__ __forceinline__ void block_sort_any(K *buf, Load load) {
+template <int NT, int J, bool SYNC, class Load>
+__device__ __forceinline__ void block_sort_regs_from(uint64_t *buf, Load load) {
     constexpr uint32_t N = (uint32_t)NT * J, UJ = J, W = kWave;
     uint32_t t = threadIdx.x;
     asm volatile("" : "+v"(t));  // (opaque: nothing below is formed ahead of a caller's loop and kept)
     const uint32_t wave = __builtin_amdgcn_readfirstlane(t / kWave);
-    K k[J];
+    uint64_t k[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) k[j] = load(t * J + j);
     if (SYNC) __syncthreads();
@@ -288,7 +281,7 @@ __device__ __forceinline__ void block_sort_any(K *buf, Load load) {
 #pragma unroll
             for (int j = 0; j < J; ++j)
                 if ((j & stride) == 0) {
-                    const K a = k[j], b = k[j + stride];
+                    const uint64_t a = k[j], b = k[j + stride];
                     bool swap;
                     if constexpr (size < UJ) swap = (a > b) == ((j & size) == 0);
                     else swap = mine(flip<~D>(__ballot(a > b)) ^ dyn);
@@ -299,7 +292,7 @@ __device__ __forceinline__ void block_sort_any(K *buf, Load load) {
             // partners in other threads: the direction is the same for all J keys
             // of a thread (stride and size are multiples of J)
             constexpr uint32_t ls = stride / UJ;
-            K o[J];
+            uint64_t o[J];
             if constexpr (ls < W) {
 #pragma unroll
                 for (int j = 0; j < J; ++j) o[j] = shfl_xor_any(k[j], (int)ls);
@@ -322,10 +315,6 @@ __device__ __forceinline__ void block_sort_any(K *buf, Load load) {
 #pragma unroll
     for (int j = 0; j < J; ++j) buf[t * J + j] = k[j];
     __syncthreads();
-}
-template <int NT, int J, bool SYNC, class Load>
-__device__ __forceinline__ void block_sort_regs_from(uint64_t *buf, Load load) {
-    block_sort_any<NT, J, SYNC, uint64_t>(buf, load);
 }
 
 // In place: every thread loads exactly the positions it later writes.

@@ -183,9 +183,9 @@ knn_status_t run_search(knn_handle_t h, const float *Q, int64_t m, const float *
     // the uncertified rows of a reduced precision are counted (nothing is re-run)
     auto count_uncertified = [&](const float *keys, int64_t i0, int64_t mb) -> knn_status_t {
         if (!certify || refix) return KNN_SUCCESS;
-        CertifyArgs ca{keys, mb, p.kk, k, qn2 + i0, b.cmax2, p.rel, p.gamma, stats_ptr(h) + kStatUncertified,
-                       nullptr, b.nu, b.tfix, 0};
-        KNN_TRY(launch_certify(ca, stream));
+        KNN_TRY(launch_certify(CertifyArgs{keys, mb, p.kk, k, qn2 + i0, b.cmax2, p.rel, p.gamma,
+                                           stats_ptr(h) + kStatUncertified},
+                               stream));
         return KNN_SUCCESS;
     };
     // the block's counts on the host
