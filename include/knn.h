@@ -67,7 +67,14 @@ typedef enum {
 /* Operand precision of the distance product in knn_search / knn_graph.  The
  * candidates it ranks are always re-ranked with exact FP32 distances. */
 typedef enum {
-    KNN_PREC_FP32 = 0,      /* FP32 inputs on the FP32 matrix cores                */
+    KNN_PREC_FP32 = 0,      /* FP32 inputs: on the FP32 matrix cores, or, where that  */
+                            /* ranks candidates faster (d >= 64, 128 queries, and     */
+                            /* enough points), each as two FP16 halves with a         */
+                            /* per-point power-of-two scale, h + l within 2^-23 of    */
+                            /* the input, hh + hl + lh accumulated in FP32.  The      */
+                            /* results are the same: the k nearest by the FP32 direct */
+                            /* form; rows whose candidates either product's rounding  */
+                            /* leaves in doubt are re-run exactly                     */
     KNN_PREC_BF16 = 1,      /* BF16 (round to nearest even) inputs, FP32 accumulation */
     KNN_PREC_FP8_E4M3 = 2   /* OCP e4m3 (round to nearest even, saturating) after a   */
                             /* per-point power-of-two scale 2^e, e the largest with   */
@@ -113,7 +120,9 @@ typedef struct {
 #define KNN_FLAG_NO_GRAPH 0x8
 /* Choose the tile shape of the distance product by timing the candidate shapes
  * on the call's own operands the first time a shape class is seen (cached per
- * handle, and in the JSON file named by KNN_AUTOTUNE_CACHE when that is set).
+ * process, and in the JSON file named by KNN_AUTOTUNE_CACHE when that is set).
+ * A few queries (at most 127) and the pipelined parts of a batch have no shape
+ * to choose.
  * Also enabled by the environment variable KNN_AUTOTUNE=1. */
 #define KNN_FLAG_AUTOTUNE 0x10
 /* search / graph / batch with FP32 products: treat every row as uncertified, so
@@ -148,8 +157,10 @@ typedef struct {
     int64_t product_launches;     /* distance-product launches (fused or dense),   */
     double product_flops;         /* their count, and their algorithmic flops      */
                                   /* (2 * rows * cols * d each)                    */
-    int64_t rows_uncertified;     /* search / graph rows whose candidate margin    */
-                                  /* does not exceed twice the key error bound     */
+    int64_t rows_uncertified;     /* search / graph rows whose candidates the key  */
+                                  /* error bound leaves in doubt: the last one's   */
+                                  /* key within the bound of the k-th's, or (FP32) */
+                                  /* of the k-th distance                          */
     int64_t rows_rerun;           /* FP32 rows among them re-run exactly: every    */
                                   /* point whose reduced key is within the bound   */
                                   /* of the k-th candidate re-ranked by its exact  */
@@ -444,7 +455,8 @@ knn_status_t knn_pivot_predict(knn_handle_t h, const float *feats, int64_t rows,
                                void *stream);
 /*
  * Mean pinball loss at `quantile` (0 < q < 1) of a batch and its gradient with
- * respect to the (BF16-rounded) weights, FP32, summed over the batch in order.
+ * respect to the (BF16-rounded) weights, FP32, summed over the batch in a fixed
+ * order.
  *   feats (B x 8), targets (B), grad (KNN_PIVOT_NPARAM), loss (1)   [device]
  */
 knn_status_t knn_pivot_grad(knn_handle_t h, const float *feats, const float *targets, int64_t B,

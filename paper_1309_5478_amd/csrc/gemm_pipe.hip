@@ -9,7 +9,9 @@
 // accumulated in FP32, hl + lh + hh, on matrix cores 16 times as fast as for
 // FP32 operands; 2^-22 |x||y| of every product (the ll term) is left out.  That
 // is less than what the FP32 matrix instruction loses: it rounds its sum at
-// every second k, this one at every sixteenth.  Error of the dot product against
+// every second k, this one at every sixteenth (where it also cuts products 25
+// bits below the largest term: the bound that certificates take of both is in
+// plan.hpp, use_split).  Error of the dot product against
 // FP64, rms over 512 x 512 pairs in units of 2^-24 |q||c|, FP32 instruction /
 // two halves: uniform points 1.44 / 0.82 (d = 64), 5.4 / 3.3 (d = 1024); normal
 // 0.30 / 0.24, 0.30 / 0.19; mixture 0.36 / 0.25, 0.79 / 0.49; unit vectors
@@ -46,8 +48,8 @@
 //
 // Measured (32768 x 131072, d = 1024, about 450 keys kept per row): halves
 // 19.3 ms = 451 TFLOP/s of FP32 work, 1352 on the matrix cores (FP32 instruction
-// 69.0 ms, 128); the cores are 73 % busy at the 1.8 GHz that the power limit
-// leaves.  BF16 7.5 ms = 1133 TFLOP/s (128 x 128 tiles 12.0 ms, 731), FP8 3.7 ms
+// 69.0 ms, 128); on a mixture graph of 262144 points the cores are 69 % busy at
+// the 1.72 GHz that the power limit leaves, without a bank conflict.  BF16 7.5 ms = 1133 TFLOP/s (128 x 128 tiles 12.0 ms, 731), FP8 3.7 ms
 // = 2315 (871 at 128 x 128).  Whole k-NN graphs against a product that kept the
 // corpus in registers and streamed the queries past it, which it replaced (k =
 // 32; BF16 262144 x 256 56.9 -> 54.7 ms, 2^20 x 256 681 -> 660, 262144 x 64 38.5 ->
