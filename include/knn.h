@@ -362,8 +362,9 @@ typedef struct {
  * distance rows, up to 8 GiB in all; no more than a third and a sixth of the
  * device memory that is free when the batch is planned, and neither of them if the
  * workspace cannot be allocated with them.  The environment variable
- * KNN_SPLIT_BYTES lowers the first limit (and that of 8 GiB of knn_search and
- * knn_graph, which pass a larger corpus in blocks).  Results do not depend on it.
+ * KNN_SPLIT_BYTES lowers the first limit (and sets that of knn_search and
+ * knn_graph, 8 GiB, which pass a larger corpus in blocks).  Results do not depend
+ * on it.
  */
 knn_status_t knn_batch_search(knn_handle_t h, const knn_job_t *jobs, int32_t njobs, void *stream,
                               const knn_options_t *opt);

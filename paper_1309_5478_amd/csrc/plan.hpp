@@ -263,21 +263,19 @@ inline void use_split(Plan &p) {
     p.rel = (float)(std::ldexp(1.0, -21) + std::ldexp(1.5 * p.d + 6.0 * ((p.d + 15) / 16), -24));
 }
 
-// A cap on the operands held, from the environment (KNN_SPLIT_BYTES), or `most`.
-inline size_t split_budget(size_t most) {
-    if (const char *e = std::getenv("KNN_SPLIT_BYTES")) {
-        const long long v = std::atoll(e);
-        if (v > 0 && (size_t)v < most) return (size_t)v;
-    }
-    return most;
+// Bytes of operands held at a time that the environment asks for (KNN_SPLIT_BYTES), or 0.
+inline size_t split_bytes_asked() {
+    const char *e = std::getenv("KNN_SPLIT_BYTES");
+    const long long v = e ? std::atoll(e) : 0;
+    return v > 0 ? (size_t)v : 0;
 }
 // What a batch may take for its jobs' operands and stored rows.
 struct BatchBudget {
     size_t split, rows;
 };
 inline BatchBudget batch_budget(size_t free_bytes) {
-    return BatchBudget{split_budget(std::min(free_bytes / 3, kBatchSplitBytes)),
-                       std::min(free_bytes / 6, kBatchRowBytes)};
+    const size_t asked = split_bytes_asked(), split = std::min(free_bytes / 3, kBatchSplitBytes);
+    return BatchBudget{asked ? std::min(asked, split) : split, std::min(free_bytes / 6, kBatchRowBytes)};
 }
 
 // The single call's choice: also once there is work for the large tiles
@@ -285,7 +283,8 @@ inline BatchBudget batch_budget(size_t free_bytes) {
 inline void plan_split(Plan &p) {
     const int64_t bytes = split_row_bytes(p.d);
     if (!split_serves(p) || !pipe_fills(p.m < p.Mb ? p.m : p.Mb, p.n)) return;
-    int64_t nb = (int64_t)(split_budget(kSplitBytes) / (size_t)bytes) / 256 * 256;
+    const size_t asked = split_bytes_asked();
+    int64_t nb = (int64_t)((asked ? asked : kSplitBytes) / (size_t)bytes) / 256 * 256;
     if (nb < 256) nb = 256;
     p.Nb = nb < p.n ? nb : p.n;
     use_split(p);
